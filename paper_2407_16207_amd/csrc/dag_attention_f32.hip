@@ -1,106 +1,265 @@
-// fp32 DAG-masked attention (paper Sections 4.1 / 5.4): the small-shape, full-precision variant.
+// fp32 DAG-masked attention (paper Sections 4.1 / 5.4): the full-precision variant, on the fp32 matrix instructions.
 //
-// One wavefront per (packed node, query head).  Lane l scores keys l, l+64, ... of the node's visible set
-// (all prefix rows, then the draft rows whose mask bit is set), keeping its own running (max, sum, output);
-// the 64 partial states are merged with wave shuffles at the end.  Plain FMA arithmetic, no matrix cores:
-// this path exists for fp32 inputs and tight tolerances, the bf16 path is the fast one.
+// The G query heads of a KV head share K/V, so the (node, head) pairs of one (sequence, KV head) are packed into one
+// row space r = node*G + g and cut into tiles of 16 rows.  A work-group of 4 wavefronts owns one tile; the keys
+// [prefix ; draft nodes] are dealt to the wavefronts in runs of 16 (wavefront w takes runs w, w+4, ...), each keeps its
+// own running (max, sum, output) and the four states are merged through LDS at the end.
+//
+// v_mfma_f32_16x16x4_f32 (fp32 products, fp32 accumulation).  Scores are computed transposed, S^T = K Q^T: a lane owns
+// one query row (column l%16) and the four keys 4*(l/16)+r, and exactly these four registers are the B operands of the
+// second contraction O^T += V^T P^T when its step r is fed with the V rows 4*(l/16)+r: nothing is exchanged between
+// lanes.  Loads follow memory, not operands: neighbouring lanes fetch neighbouring 16-byte chunks of a row.  For V that
+// is an operand layout (the order of the output channels is free); K goes through a part of LDS that is the
+// wavefront's own (loaded in operand layout, a line per lane: 32.6 us instead of 30.0 on the case below).  The next V
+// and K runs are in flight while the matrix instructions of a run execute.
+//
+// What bounds it: a SIMD's matrix and vector instructions one after the other (a second wavefront per SIMD hides
+// nothing: 8 wavefronts over the same tiles take the same time), 64 matrix instructions of 14 ns per run at head_dim
+// 128 and a third of that again for softmax and addresses; with fewer tiles than CUs, the idle CUs.
+// 32 heads of 64 rows over 1088 keys, head_dim 128 (128 tiles, half the chip): 29.4 us = 38 TFLOP/s; 8 groups of 960
+// rows over 1120 keys: 53 us = 78 TFLOP/s of the 154 that a large fp32 matrix product reaches.  The plain-FMA kernel
+// before this one (a lane per key, every lane reading a K and a V row of its own) took 313 and 1147 us, and 24.8 us
+// where this one takes 7.1 (4 heads, 16 nodes, 144 keys, head_dim 64).
+// 32-row tiles (every K/V operand used twice) need 232 registers and lose more to the coarser split: 51 and 54 us.
 #include "gsd_internal.h"
 
 namespace gsd {
 
-template <int D>
-__global__ __launch_bounds__(256) void dag_attention_f32_kernel(
-    int32_t batch, int32_t max_nodes, int32_t total_rows, int32_t num_q_heads, int32_t group, int32_t words_per_row, float scale,
-    const float *__restrict__ q, float *__restrict__ o, float *__restrict__ lse, const float *__restrict__ k,
-    const float *__restrict__ v, const int64_t *__restrict__ kv_offsets, const int32_t *__restrict__ prefix_lens,
-    const int32_t *__restrict__ node_offsets, const uint64_t *__restrict__ mask, int64_t q_ts, int64_t q_hs,
-    int64_t o_ts, int64_t o_hs, int64_t kv_ts, int64_t kv_hs) {
-    const int lane = threadIdx.x & 63;
-    const int64_t row = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);     // row = t * Hq + h
-    if (row >= total_rows) return;                                        // whole wave leaves together
-    const int32_t t = int32_t(row / num_q_heads);
-    const int32_t h = int32_t(row - int64_t(t) * num_q_heads);
-    const int32_t hk = h / group;
+namespace {
 
-    // sequence of node t: the last b with node_offsets[b] <= t
-    int b = 0;
-    while (b + 1 < batch && node_offsets[b + 1] <= t) ++b;
-    const int32_t n = min(node_offsets[b + 1] - node_offsets[b], max_nodes);
-    const int32_t P = prefix_lens[b];
-    const int64_t kv0 = kv_offsets[b];
-    const uint64_t *mrow = mask + int64_t(t) * words_per_row;
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-    float qr[D];
-    const float *qp = q + t * q_ts + h * q_hs;
-#pragma unroll
-    for (int d = 0; d < D; d += 4) {
-        const float4 x = *reinterpret_cast<const float4 *>(qp + d);
-        qr[d] = x.x * scale; qr[d + 1] = x.y * scale; qr[d + 2] = x.z * scale; qr[d + 3] = x.w * scale;
-    }
-    float acc[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) acc[d] = 0.f;
-    float m = -1e30f, l = 0.f;
+constexpr int kF32Waves = 4;
+constexpr float kF32Log2e = 1.4426950408889634f;
+constexpr float kF32Empty = -1e30f;      // running max before any visible key; finite, so that differences stay numbers
 
-    const int32_t total = P + n;
-    for (int32_t j = lane; j < total; j += 64) {
-        if (j >= P) {
-            const int32_t dj = j - P;
-            if (!((mrow[dj >> 6] >> (dj & 63)) & 1)) continue;
-        }
-        const float *kp = k + (kv0 + j) * kv_ts + hk * kv_hs;
-        const float *vp = v + (kv0 + j) * kv_ts + hk * kv_hs;
-        float s = 0.f;
-#pragma unroll
-        for (int d = 0; d < D; d += 4) {
-            const float4 x = *reinterpret_cast<const float4 *>(kp + d);
-            s = fmaf(qr[d], x.x, s); s = fmaf(qr[d + 1], x.y, s);
-            s = fmaf(qr[d + 2], x.z, s); s = fmaf(qr[d + 3], x.w, s);
-        }
-        const float m_new = fmaxf(m, s);
-        const float alpha = __expf(m - m_new);
-        const float p = __expf(s - m_new);
-        l = l * alpha + p;
-#pragma unroll
-        for (int d = 0; d < D; d += 4) {
-            const float4 x = *reinterpret_cast<const float4 *>(vp + d);
-            acc[d] = fmaf(acc[d], alpha, p * x.x); acc[d + 1] = fmaf(acc[d + 1], alpha, p * x.y);
-            acc[d + 2] = fmaf(acc[d + 2], alpha, p * x.z); acc[d + 3] = fmaf(acc[d + 3], alpha, p * x.w);
-        }
-        m = m_new;
-    }
+struct F32Params {
+    const float *q;
+    float *o;
+    float *lse;
+    const float *k;
+    const float *v;
+    const int64_t *kv_offsets;
+    const int32_t *prefix_lens;
+    const int32_t *node_offsets;
+    const uint64_t *mask;
+    int64_t q_ts, q_hs, o_ts, o_hs, kv_ts, kv_hs;
+    int32_t groups, max_nodes, num_q_heads, num_kv_heads, group, words_per_row, row_tiles;
+    float scale_log2e;
+};
 
-    // merge the 64 lane states
-    float m_all = m;
-    for (int off = 32; off > 0; off >>= 1) m_all = fmaxf(m_all, __shfl_xor(m_all, off, 64));
-    const float w = __expf(m - m_all);          // lanes that saw nothing: l == 0, acc == 0
-    l *= w;
-    for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
-    const float inv = (l > 0.f) ? 1.f / l : 0.f;
-    float *op = o + t * o_ts + h * o_hs;
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        float x = acc[d] * w;
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-        if (lane == (d & 63)) op[d] = x * inv;
-    }
-    if (lse && lane == 0) lse[row] = (l > 0.f) ? m_all + __logf(l) : -__builtin_inff();
+// max over the four 16-lane groups of a wavefront (lanes l, l^16, l^32, l^48), in every lane
+__device__ __forceinline__ float max_across_groups(float x) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float sum_across_groups(float x) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+template <int D>
+__global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(const F32Params p) {
+    constexpr int NW = kF32Waves;
+    constexpr int KV4 = D / 16;           // float4 loads of a K row fragment (4 channels per lane and load)
+    constexpr int CB = D / 16;            // 16-channel blocks of the output
+    constexpr int VV4 = CB / 4;           // float4 loads per V row and lane
+    constexpr int ROWS = 16;
+    constexpr int CHUNKS = D / 4;         // 16-byte chunks of an output row
+    __shared__ __attribute__((aligned(16))) float o_lds[NW * ROWS * D];
+    constexpr int kMaskWords = GSD_MAX_NODES_PER_SEQ / 64;
+    __shared__ uint64_t mask_lds[ROWS][kMaskWords + 1];
+    __shared__ float m_lds[NW * ROWS], l_lds[NW * ROWS];
+
+    // the row tiles of one (sequence, KV head) share K/V: they take consecutive slots of one XCD (ids are dealt
+    // round-robin to the 8 XCDs), the (sequence, KV head) groups go round the XCDs
+    const int slot = blockIdx.x >> 3;
+    const int group_id = (slot / p.row_tiles) * 8 + (blockIdx.x & 7);
+    if (group_id >= p.groups) return;
+    const int b = group_id / p.num_kv_heads, kvh = group_id - b * p.num_kv_heads;
+    const int32_t node_base = p.node_offsets[b];
+    const int32_t n = min(p.node_offsets[b + 1] - node_base, p.max_nodes);
+    const int32_t P = p.prefix_lens[b];
+    const int64_t kv_row0 = p.kv_offsets[b];
+    const int32_t G = p.group;
+    const int32_t rows_total = n * G, row0 = (slot % p.row_tiles) * ROWS;
+    if (row0 >= rows_total) return;                      // uniform for the work-group
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 15, kg = lane >> 4;
+    const int32_t keys = P + n, tiles = (keys + 15) / 16;
+    // K rows come whole (neighbouring lanes, neighbouring 16-byte chunks) into registers, go from there to a part of LDS
+    // that is this wavefront's own and are read back as operands: lane l holds row l%16, and loads that follow the
+    // operand layout touch a line per lane.  Chunk x of row r sits in slot x ^ r: the 16 rows meet in no bank.
+    // V operands are D/16 channels of a row per lane, neighbouring lanes side by side: loaded as they are.
+    constexpr int KROWS = 64 / CHUNKS;                   // K rows per load
+    const float *kv_base_k = p.k + kv_row0 * p.kv_ts + kvh * p.kv_hs, *kv_base_v = p.v + kv_row0 * p.kv_ts + kvh * p.kv_hs;
+    const int k_row = lane / CHUNKS, k_chunk = lane % CHUNKS;
+    floatx4 ks[KV4], vf[4][VV4];
+    int64_t k_off[KV4], v_off[4];                        // element offsets from the tile's first row
+    auto set_offsets = [&](int last) __attribute__((always_inline)) {     // rows past `last` repeat it
+#pragma unroll
+        for (int j = 0; j < KV4; ++j) k_off[j] = int64_t(min(j * KROWS + k_row, last)) * p.kv_ts + 4 * k_chunk;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v_off[r] = int64_t(min(4 * kg + r, last)) * p.kv_ts + 4 * col;
+    };
+    set_offsets(15);
+    auto load_k = [&](int tile) __attribute__((always_inline)) {          // past the last tile: loads that nothing waits for
+        const int t = min(tile, tiles - 1);
+        if (t * 16 + 16 > keys) set_offsets(keys - 1 - t * 16);           // uniform; no full tile comes after it
+        const float *base = kv_base_k + int64_t(t) * 16 * p.kv_ts;
+#pragma unroll
+        for (int j = 0; j < KV4; ++j) ks[j] = *reinterpret_cast<const floatx4 *>(base + k_off[j]);
+    };
+    auto load_v = [&](int tile) __attribute__((always_inline)) {          // after load_k of the same tile
+        const float *base = kv_base_v + int64_t(min(tile, tiles - 1)) * 16 * p.kv_ts;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int t = 0; t < VV4; ++t) vf[r][t] = *reinterpret_cast<const floatx4 *>(base + v_off[r] + 64 * t);
+    };
+    floatx4 *my_k = reinterpret_cast<floatx4 *>(o_lds) + wave * 16 * CHUNKS;
+    auto store_k = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < KV4; ++j) {
+            const int r = j * KROWS + k_row;
+            my_k[r * CHUNKS + (k_chunk ^ r)] = ks[j];
+        }
+    };
+
+    floatx4 qf[KV4], acc[CB];
+    float m = kF32Empty, l = 0.f;
+    const int32_t q_row = min(row0 + col, rows_total - 1), q_node = q_row / G;
+    const float *qp = p.q + (int64_t(node_base) + q_node) * p.q_ts + (kvh * G + (q_row - q_node * G)) * p.q_hs + 4 * kg;
+#pragma unroll
+    for (int t = 0; t < KV4; ++t) qf[t] = *reinterpret_cast<const floatx4 *>(qp + 16 * t);
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) acc[cb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // the words of the tile's mask rows in LDS: fetched inside the loop they would queue behind the K/V loads in flight
+    for (int x = threadIdx.x; x < ROWS * kMaskWords; x += NW * 64) {
+        const int row = x / kMaskWords, w = x - row * kMaskWords;
+        const int32_t node = min(row0 + row, rows_total - 1) / G;
+        mask_lds[row][w + 1] = w < p.words_per_row ? p.mask[(int64_t(node_base) + node) * p.words_per_row + w] : 0;
+        if (w == 0) mask_lds[row][0] = ~uint64_t(0);     // the keys before draft node 0: the end of the prefix
+    }
+    const float c = p.scale_log2e;
+    load_k(wave);
+    load_v(wave);
+    store_k();
+    __syncthreads();
+
+    for (int tile = wave; tile < tiles; tile += NW) {
+        load_k(tile + NW);
+        __builtin_amdgcn_sched_barrier(0);
+        floatx4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < KV4; ++t) {
+            const floatx4 kf = my_k[col * CHUNKS + ((4 * t + kg) ^ col)];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[e], qf[t][e], s, 0, 0, 0);
+        }
+        if (tile * 16 + 16 > P) {                        // uniform: the tile reaches into the draft nodes
+            const int32_t pos = tile * 16 + 4 * kg - P;  // draft node of this lane's first key; below 0: prefix
+            const int32_t w = (pos + 64) >> 5;           // its 32-bit word of the row in LDS, >= 1
+            const uint32_t *words = reinterpret_cast<const uint32_t *>(mask_lds[col]);
+            const uint32_t lo = words[w], hi = words[min(w + 1, 2 * kMaskWords + 1)];
+            const uint32_t bits = uint32_t(((uint64_t(hi) << 32) | lo) >> (pos & 31));
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (!((bits >> r) & 1) || pos + r >= n) s[r] = -__builtin_inff();
+        }
+        const float mx = max_across_groups(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
+        const float m_new = fmaxf(m, mx * c);
+        if (__any(m_new > m)) {                  // uniform: some row of the tile has a new maximum
+            const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+            l *= alpha;
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) acc[cb] *= alpha;
+            m = m_new;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            s[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -m));
+            l += s[r];
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+                acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][cb / 4][cb % 4], s[r], acc[cb], 0, 0, 0);
+        store_k();
+        load_v(tile + NW);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
+    __syncthreads();                                     // the K tiles and the outputs below share LDS
+
+    // merge of the eight states: (max, sum) first, then every wavefront's output scaled to the common maximum.
+    // Register i of channel block 4*x + e is channel 64*x + 16*kg + 4*i + e.
+    // Chunks are XOR-swizzled by the row, so that the 16 rows of a store do not meet in a bank.
+    const float sum = sum_across_groups(l);
+    if (kg == 0) {
+        m_lds[wave * ROWS + col] = m;
+        l_lds[wave * ROWS + col] = sum;
+    }
+    __syncthreads();
+    float top = m_lds[col];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) top = fmaxf(top, m_lds[w * ROWS + col]);
+    const float f = __builtin_amdgcn_exp2f(m - top);
+    floatx4 *out = reinterpret_cast<floatx4 *>(o_lds + (wave * ROWS + col) * D);
+#pragma unroll
+    for (int x = 0; x < VV4; ++x)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            floatx4 y;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[e] = acc[4 * x + e][i] * f;
+            out[(16 * x + 4 * kg + i) ^ col] = y;
+        }
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < ROWS * CHUNKS; idx += NW * 64) {
+        const int row = idx / CHUNKS, chunk = idx - row * CHUNKS;
+        if (row0 + row >= rows_total) break;             // rows ascend with idx
+        float top = m_lds[row];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) top = fmaxf(top, m_lds[w * ROWS + row]);
+        float sum = 0.f;
+        floatx4 y = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            sum += l_lds[w * ROWS + row] * __builtin_amdgcn_exp2f(m_lds[w * ROWS + row] - top);
+            y += reinterpret_cast<const floatx4 *>(o_lds + (w * ROWS + row) * D)[chunk ^ row];
+        }
+        y *= sum > 0.f ? 1.f / sum : 0.f;
+        const int32_t node = (row0 + row) / G, head = kvh * G + (row0 + row - node * G);
+        const int64_t t = int64_t(node_base) + node;
+        *reinterpret_cast<floatx4 *>(p.o + t * p.o_ts + head * p.o_hs + 4 * chunk) = y;
+        if (p.lse && chunk == 0)
+            p.lse[t * p.num_q_heads + head] = sum > 0.f ? (top + __log2f(sum)) * 0.6931471805599453f : -__builtin_inff();
+    }
+}
+
+}  // namespace
+
 hipError_t launch_attention_f32(const gsd_attn_desc &d, hipStream_t stream) {
-    const int64_t rows = int64_t(d.total_nodes) * d.num_q_heads;
-    const dim3 grid((unsigned)((rows + 3) / 4)), block(256);
-    const int group = d.num_q_heads / d.num_kv_heads;
-#define GSD_F32_ARGS                                                                                            \
-    d.batch, d.max_nodes, (int32_t)rows, d.num_q_heads, group, d.words_per_row, d.softmax_scale, (const float *)d.q,         \
-        (float *)d.o, d.lse, (const float *)d.k, (const float *)d.v, d.kv_offsets, d.prefix_lens,              \
-        d.node_offsets, d.mask, d.q_token_stride, d.q_head_stride, d.o_token_stride, d.o_head_stride,          \
-        d.kv_token_stride, d.kv_head_stride
-    if (d.head_dim == 64)
-        hipLaunchKernelGGL(dag_attention_f32_kernel<64>, grid, block, 0, stream, GSD_F32_ARGS);
-    else
-        hipLaunchKernelGGL(dag_attention_f32_kernel<128>, grid, block, 0, stream, GSD_F32_ARGS);
-#undef GSD_F32_ARGS
+    F32Params p;
+    p.q = (const float *)d.q; p.o = (float *)d.o; p.lse = d.lse; p.k = (const float *)d.k; p.v = (const float *)d.v;
+    p.kv_offsets = d.kv_offsets; p.prefix_lens = d.prefix_lens; p.node_offsets = d.node_offsets; p.mask = d.mask;
+    p.q_ts = d.q_token_stride; p.q_hs = d.q_head_stride; p.o_ts = d.o_token_stride; p.o_hs = d.o_head_stride;
+    p.kv_ts = d.kv_token_stride; p.kv_hs = d.kv_head_stride;
+    p.groups = d.batch * d.num_kv_heads; p.max_nodes = d.max_nodes; p.num_q_heads = d.num_q_heads;
+    p.num_kv_heads = d.num_kv_heads; p.group = d.num_q_heads / d.num_kv_heads; p.words_per_row = d.words_per_row;
+    p.scale_log2e = d.softmax_scale * kF32Log2e;
+    p.row_tiles = (d.max_nodes * p.group + 15) / 16;
+    const dim3 grid((unsigned)((p.groups + 7) / 8 * 8 * p.row_tiles)), block(kF32Waves * 64);
+    if (d.head_dim == 64) hipLaunchKernelGGL(dag_attention_f32_kernel<64>, grid, block, 0, stream, p);
+    else hipLaunchKernelGGL(dag_attention_f32_kernel<128>, grid, block, 0, stream, p);
     return hipGetLastError();
 }
 

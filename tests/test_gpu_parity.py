@@ -174,6 +174,14 @@ def test_attention_fp32_general(gpu, ref, D):
     check_attention(gpu, ref, w)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("hq,hkv", [(1, 1), (3, 1), (16, 2)])
+def test_attention_fp32_tile_edges(gpu, ref, D, hq, hkv):
+    """Rows and keys one below, at and above the 16-row tile, the 16-key run and the four wavefronts' turn of 64 keys."""
+    rng = np.random.default_rng(1000 + D + hq)
+    check_attention(gpu, ref, custom_workload(rng, [1, 15, 16, 17, 33, 2], [0, 1, 47, 48, 31, 512], hq, hkv, D, "f32"))
+
+
 @pytest.mark.parametrize("waves", [4, 8, 64])
 @pytest.mark.parametrize("splits", [1, 2, 3, 7])
 @pytest.mark.parametrize("D", [128, 64])
