@@ -11,7 +11,7 @@ LIB_PATH = os.path.join(PKG_DIR, "libgsd.so")
 BENCH_LIB_PATH = os.path.join(PKG_DIR, "libgsd_bench.so")     # measurement aid of bench.py only
 
 SOURCES = ["gsd_api.hip", "mask_build.hip", "accept_path.hip", "node_argmax.hip", "dag_attention_f32.hip",
-           "dag_attention_bf16.hip", "unmerge_tree.hip", "commit_kv.hip", "accept_stochastic.hip", "build_graph.hip"]
+           "dag_attention_bf16.hip", "dag_attention_bf16_keys.hip", "unmerge_tree.hip", "commit_kv.hip", "accept_stochastic.hip", "build_graph.hip"]
 
 # -no-hip-rt: the library carries no dependency on a particular libamdhip64; the process that loads it (the
 # Python binding: the runtime torch already runs on) supplies the HIP runtime.  Two HIP runtimes in one process

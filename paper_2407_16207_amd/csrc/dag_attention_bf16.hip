@@ -32,25 +32,16 @@
 //
 // Small problems are split along the KV axis (gsd_attn_desc.num_splits); a split writes unnormalised fp32
 // partials (O, running max, running sum) and a second kernel merges them in split order.
+#include <math.h>
+
 #include <mutex>
 #include <type_traits>
 
-#include "gsd_internal.h"
+#include "attention_bf16.h"
 
 namespace gsd {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
 constexpr int kKeysPerTile = 64;     // keys per KV tile = one mask word
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kMInit = -1e30f;     // finite stand-in for -inf: the offset stored for a partial without any visible key
 // A row's offset is not its running max: it is a guess (the true max of the first tile) that is corrected only when
 // a tile's probabilities leave a harmless range.  Per lane, the 32 probabilities of a tile add up to less than
 // kSumRaise whenever none of its shifted scores exceeds 9 (log2); a larger sum raises the offset for the tiles that
@@ -61,26 +52,6 @@ constexpr float kSumRaise = 16384.0f;
 constexpr float kSumPoison = 0x1p64f;
 constexpr float kSumTiny = 0x1p-64f;
 
-struct AttnParams {
-    const __bf16 *q;
-    __bf16 *o;
-    float *lse;
-    const __bf16 *k;
-    const __bf16 *v;
-    const int64_t *kv_offsets;
-    const int32_t *prefix_lens;
-    const int32_t *node_offsets;
-    const uint64_t *mask;
-    float *part_o;      // [splits][T][Hq][D] fp32 unnormalised
-    float *part_ml;     // [splits][T][Hq][2]  (offset in the log2 domain, sum of 2^(score - offset))
-    int64_t q_ts, q_hs, o_ts, o_hs, kv_ts, kv_hs;
-    int32_t batch, total_nodes, max_nodes, num_q_heads, num_kv_heads, group, words_per_row;
-    int32_t q_tiles;    // row tiles per (sequence, KV head)
-    int32_t splits;
-    int32_t wg_per_xcd; // ceil(batch * num_kv_heads / 8) * q_tiles * splits
-    float scale_log2e;  // softmax_scale * log2(e)
-};
-
 template <int D>
 struct Lds {
     static constexpr int kRowBytes = D * 2;                       // one K or V row, unpadded (swizzled instead)
@@ -88,68 +59,12 @@ struct Lds {
     static constexpr int kTotal = 4 * kTileBytes;                 // K and V, both double-buffered
 };
 
-// position of actual key row r (0..63) inside the LDS K tile: bits 2 and 3 of r swapped (an involution)
-__device__ __forceinline__ int k_lds_row(int r) { return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1); }
-
 // Nothing may be moved across this point by the instruction scheduler: the loop body below is laid out by hand
 // as slices of one matrix instruction, one or two LDS reads for a later slice and a few softmax operations, so
 // that the matrix pipe and the vector ALU of a wave run side by side.
 #define GSD_SLICE_END() __builtin_amdgcn_sched_barrier(0)
 
 __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
-
-// max over the two 32-lane halves of a wavefront, in every lane
-__device__ __forceinline__ float max_across_halves(float x) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
-// One 16-byte-per-lane global -> LDS copy: lane l's 16 bytes at gbase + voff land at LDS byte lds_base + 16*l.
-// Issued as inline assembly so that the compiler's wait-count pass does not serialise later LDS reads behind
-// it; completion is awaited by hand (dma_wait) before the barrier that publishes the tile.
-__device__ __forceinline__ void dma16(const void *gbase, uint32_t voff, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0"
-                 :: "s"(gbase), "v"(voff), "s"(lds_base) : "memory");
-}
-// The same with the LDS address as a scalar base plus a constant, added inside: given one scalar per destination
-// the compiler keeps them all live across the loop (sixteen at four copies per tile and wave) and spills them.
-__device__ __forceinline__ void dma16_at(const void *gbase, uint32_t voff, uint32_t lds_base, int lds_const) {
-    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0"
-                 :: "s"(gbase), "v"(voff), "s"(lds_base), "i"(lds_const) : "memory", "scc");
-}
-template <int N> __device__ __forceinline__ void dma_wait() {   // at most N vector-memory operations in flight
-    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
-}
-// A wave-uniform 64-bit value, forced into scalar registers (the copies above take their base address from there;
-// a uniform value loaded through the vector memory path would otherwise stay in vector registers).
-__device__ __forceinline__ int64_t uniform64(int64_t x) {
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(uint64_t(x)));
-    const uint32_t hi = __builtin_amdgcn_readfirstlane(uint32_t(uint64_t(x) >> 32));
-    return int64_t((uint64_t(hi) << 32) | lo);
-}
-// Work-group barrier as bare assembly: the compiler's own barrier is preceded by a wait for every outstanding LDS
-// read, which would undo the reads issued ahead of it on purpose (their results are awaited where they are used).
-__device__ __forceinline__ void wg_barrier() {
-    asm volatile("s_barrier" ::: "memory");
-}
-
-// Matrix instructions written out for the one-wave-per-SIMD variant.  With 512 registers per lane the compiler
-// selects the accumulator-register form for every matrix instruction it emits itself, and then moves every score
-// into an ordinary register before the softmax can touch it.  Written out, the score accumulators stay in ordinary
-// registers ("v") and only the output accumulators and the query fragments, which the vector ALU never reads in
-// the loop, live in accumulator registers ("a").  The compiler does not know these are matrix instructions, so
-// the two places where the vector ALU reads their results soon after them wait by hand (mfma_settle).
-__device__ __forceinline__ void mfma_v_acc(floatx16 &acc, const bf16x8 &a, const bf16x8 &b) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "a"(b));
-}
-__device__ __forceinline__ void mfma_v_init(floatx16 &acc, const bf16x8 &a, const bf16x8 &b) {   // starts a chain from zero
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=v"(acc) : "v"(a), "a"(b));
-}
-__device__ __forceinline__ void mfma_a_acc(floatx16 &acc, const bf16x8 &a, const bf16x8 &b) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-}
-// at least 16 issue cycles: longer than the 12 the vector ALU must keep away from an 8-pass matrix result
-__device__ __forceinline__ void mfma_settle() { asm volatile("s_nop 7\n\ts_nop 7" ::: "memory"); }
 
 // NW wavefronts per work-group, each owning RBW blocks of 32 query rows.
 //   <4 waves, 2 blocks>  256 rows, one work-group per CU, one wave per SIMD with the whole register file: every K/V
@@ -944,89 +859,114 @@ __global__ __launch_bounds__(NW * 64, RBW == 2 ? 1 : 8 / NW) void dag_attention_
     }
 }
 
-// Merge of the split partials, one wavefront per (node, head) row, splits taken in index order.
+// Merge of the split partials, splits taken in index order: D/4 lanes per (node, head) row, four channels each.  Bound by
+// latency, so every load of a row is independent of the others: the (offset, sum) pairs are fetched one per lane and
+// handed round by shuffles, the outputs four splits at a time.  (A wavefront per row that walked the splits, two channels
+// per lane: 8.7 us for 4096 rows and 16 splits where this one takes about 6.)
 template <int D>
 __global__ __launch_bounds__(256) void dag_attention_combine_kernel(const AttnParams p) {
-    const int lane = threadIdx.x & 63;
-    const int64_t row = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);      // t * Hq + head
+    constexpr int LPR = D / 4;                                             // lanes per row
+    constexpr int HELD = 64 / LPR;                                         // (offset, sum) pairs per lane, 64 splits at most
+    const int lane = threadIdx.x & 63, in_row = lane % LPR;
     const int64_t rows = int64_t(p.total_nodes) * p.num_q_heads;
-    if (row >= rows) return;
+    const int64_t row = int64_t(blockIdx.x) * (256 / LPR) + threadIdx.x / LPR;     // t * Hq + head
+    if (row >= rows) return;                                               // whole rows leave: shuffles stay within a row
+    float m[HELD], l[HELD], top = kMInit;
+#pragma unroll
+    for (int x = 0; x < HELD; ++x) {
+        const int s = x * LPR + in_row;
+        m[x] = kMInit;
+        l[x] = 0.f;
+        if (s < p.splits) {
+            const floatx2 ml = *reinterpret_cast<const floatx2 *>(p.part_ml + (int64_t(s) * rows + row) * 2);
+            m[x] = ml[0];
+            l[x] = ml[1];
+        }
+        top = fmaxf(top, m[x]);
+    }
+#pragma unroll
+    for (int off = LPR / 2; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off, 64));
+    float sum = 0.f;
+#pragma unroll
+    for (int x = 0; x < HELD; ++x) {
+        m[x] = __builtin_amdgcn_exp2f(m[x] - top);                         // from here on the split's factor
+        sum = fmaf(l[x], m[x], sum);
+    }
+#pragma unroll
+    for (int off = LPR / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int x = 0; x < HELD; ++x) {
+        const int here = min(LPR, p.splits - x * LPR);
+        const float *from = p.part_o + (int64_t(x) * LPR * rows + row) * D + 4 * in_row;
+#pragma unroll 4
+        for (int s = 0; s < here; ++s) {
+            const float f = __shfl(m[x], (lane & ~(LPR - 1)) + s, 64);
+            acc += *reinterpret_cast<const floatx4 *>(from + int64_t(s) * rows * D) * f;
+        }
+    }
+    const float inv = sum > 0.f ? 1.f / sum : 0.f;
     const int64_t t = row / p.num_q_heads;
     const int head = int(row - t * p.num_q_heads);
-
-    float m = kMInit;
-    for (int s = 0; s < p.splits; ++s) m = fmaxf(m, p.part_ml[(int64_t(s) * rows + row) * 2]);
-    constexpr int PER_LANE = D / 64;
-    float acc[PER_LANE];
+    bf16x4 o;
 #pragma unroll
-    for (int e = 0; e < PER_LANE; ++e) acc[e] = 0.f;
-    float l = 0.f;
-    for (int s = 0; s < p.splits; ++s) {
-        const int64_t prow = int64_t(s) * rows + row;
-        const float ms = p.part_ml[prow * 2], ls = p.part_ml[prow * 2 + 1];
-        const float w = __builtin_amdgcn_exp2f(ms - m);
-        l = fmaf(ls, w, l);
-#pragma unroll
-        for (int e = 0; e < PER_LANE; ++e) acc[e] = fmaf(p.part_o[prow * D + lane * PER_LANE + e], w, acc[e]);
-    }
-    const float inv = l > 0.f ? 1.f / l : 0.f;
-    __bf16 *op = p.o + t * p.o_ts + int64_t(head) * p.o_hs + lane * PER_LANE;
-#pragma unroll
-    for (int e = 0; e < PER_LANE; ++e) op[e] = (__bf16)(acc[e] * inv);
-    if (p.lse && lane == 0) p.lse[row] = l > 0.f ? (m + __log2f(l)) * 0.6931471805599453f : -__builtin_inff();
+    for (int e = 0; e < 4; ++e) o[e] = (__bf16)(acc[e] * inv);
+    *reinterpret_cast<bf16x4 *>(p.o + t * p.o_ts + int64_t(head) * p.o_hs + 4 * in_row) = o;
+    if (p.lse && in_row == 0) p.lse[row] = sum > 0.f ? (top + __log2f(sum)) * 0.6931471805599453f : -__builtin_inff();
 }
 
 // ---------------------------------------------------------------------------------------------- host side
 
-// Shape of a work-group: (wavefronts, 32-row blocks per wavefront).  256-row tiles (8 waves x 1 block) when a
-// (sequence, KV head) can fill them, else 128-row tiles (4 x 1).  gsd_attn_desc.wg_waves overrides: 4 -> 4 x 1,
-// 8 -> 8 x 1, 64 -> 4 x 2 (measured slower: with one wave per SIMD nothing fills a wave's issue stalls).
-struct WgShape { int waves, blocks; };
-static WgShape shape_of(const gsd_attn_desc &d) {
-    if (d.wg_waves == 4) return {4, 1};
-    if (d.wg_waves == 8) return {8, 1};
-    if (d.wg_waves == 64) return {4, 2};
+// The candidate that a small timing model likes best (microseconds, fitted on the 256-CU part): what a work-group spends
+// outside its loop plus its steps, in rounds of what the chip holds at once, but no less than the K/V bytes take; and for
+// a split the partials and the merge kernel, 2.5 us and 0.32 us per 1024 rows and split.  A step of the 8-wave kernel
+// (64 keys) takes 1.2 us alone and 1.65 us when all CUs run it (L2 and clock), of the 4-wave kernel 0.7 us and, two
+// work-groups to a CU, 1.75 us; of the keys kernel (128 keys) 1.4 us; at head_dim 64 0.8, 0.8 and 0.5 times that.
+// Splitting only pays when few work-groups would otherwise walk a long KV axis; never fewer than 4 KV tiles per split.
+AttnPlan attention_bf16_plan(const gsd_attn_desc &d) {
     const int group = d.num_q_heads / d.num_kv_heads;
-    return d.max_nodes * group >= 256 ? WgShape{8, 1} : WgShape{4, 1};
-}
-
-static int q_tiles_of(const gsd_attn_desc &d) {
-    const int group = d.num_q_heads / d.num_kv_heads;
-    const WgShape sh = shape_of(d);
-    const int rows_per_wg = sh.waves * sh.blocks * 32;
-    return (d.max_nodes * group + rows_per_wg - 1) / rows_per_wg;
-}
-
-int attention_bf16_splits(const gsd_attn_desc &d) {
+    const int rows = d.max_nodes * group;
     const int nt_max = (d.max_prefix + kKeysPerTile - 1) / kKeysPerTile + (d.max_nodes + kKeysPerTile - 1) / kKeysPerTile;
-    int splits = d.num_splits;
-    if (splits <= 0) {
-        // The split count that a small timing model likes best (microseconds, fitted to this kernel on the 256-CU
-        // part: ~10 per work-group outside its tile loop, 1.0 per tile of a 4-wave work-group and 1.65 of an 8-wave
-        // one at head_dim 128, work-groups beyond what the chip holds at once run in further rounds; the partials
-        // and the merge kernel cost 2 + S + rows/1024 * (0.9 + 0.13 S)).  Splitting only pays when few work-groups
-        // would otherwise walk a long KV axis; never fewer than 4 KV tiles per split.
-        const WgShape sh = shape_of(d);
-        const double wgs = double(q_tiles_of(d)) * d.batch * d.num_kv_heads;
-        const double resident = 256.0 * (sh.waves == 8 || sh.blocks == 2 ? 1 : 2);
-        const double t_tile = (sh.waves == 8 ? 1.65 : sh.blocks == 2 ? 2.4 : 1.0) * d.head_dim / 128.0;
-        const double rows_k = double(d.total_nodes) * d.num_q_heads / 1024.0;
-        const int cap = nt_max / 4 > 0 ? (nt_max / 4 < 64 ? nt_max / 4 : 64) : 1;
-        double best = 0;
-        for (int s = 1; s <= cap; ++s) {
-            const double rounds = double(int64_t((wgs * s + resident - 1) / resident));
-            const double t = rounds * (10.0 + double((nt_max + s - 1) / s) * t_tile) +
-                             (s > 1 ? 2.0 + s + rows_k * (0.9 + 0.13 * s) : 0.0);
-            if (s == 1 || t < best) {
-                best = t;
-                splits = s;
+    const int split_cap = nt_max / 4 > 0 ? (nt_max / 4 < 64 ? nt_max / 4 : 64) : 1;
+    const bool wide = d.head_dim == 128;
+    const float merge_us = (wide ? 0.32f : 0.16f) / 1024.0f * float(d.total_nodes) * float(d.num_q_heads);
+    const float heads = float(d.batch) * float(d.num_kv_heads);
+    const float kv_us = heads * (float(d.max_prefix) + float(d.max_nodes)) * float(d.head_dim) * (4.0f / 5.2e6f);
+    const AttnPlan shapes[] = {{4, 1, 0, 1}, {8, 1, 0, 1}, {4, 2, 0, 1}, {0, 0, 1, 1}, {0, 0, 2, 1}};
+    AttnPlan best = shapes[0];
+    float best_us = -1.0f;
+    for (const AttnPlan &shape : shapes) {
+        const int forced = shape.row_groups ? 0 : shape.blocks == 2 ? 64 : shape.waves;       // as wg_waves names it
+        if (d.wg_waves != 0 ? forced != d.wg_waves : forced == 64) continue;
+        const float wgs = heads * float((rows + shape.rows_per_wg() - 1) / shape.rows_per_wg());
+        const bool keys = shape.row_groups != 0, small = shape.waves == 4 && shape.blocks == 1;
+        const int resident = small || (shape.row_groups == 1 && d.head_dim == 64) ? 512 : 256;
+        const int steps = keys ? (d.max_prefix + d.max_nodes + 127) / 128 : nt_max;
+        const float tile = wide ? 1.0f : keys ? 0.5f : 0.8f;
+        for (int s = 1; s <= split_cap; s += s < 6 ? 1 : s < 24 ? 2 : 8) {
+            if (d.num_splits > 0) {
+                s = d.num_splits < nt_max ? d.num_splits : nt_max;
+                if (s > 64) s = 64;
+            } else if (s > 1 && wgs * s > 2 * resident) {
+                break;
             }
+            const float all = wgs * s, fill = all / resident, rounds = ceilf(fill);
+            const float each = float((steps + s - 1) / s) * tile;
+            float us;
+            if (keys) us = rounds * (6.0f + each * 1.4f);
+            else if (small) us = (fill > 1.0f ? 0.5f * (rounds + fill) : 1.0f) * (7.0f + each * (all > 256 ? 1.75f : 0.7f));
+            else us = rounds * (7.0f + each * (all >= 256 ? 1.65f : 1.2f));
+            us = us < 7.0f + kv_us ? 7.0f + kv_us : us;
+            if (s > 1) us += 2.5f + merge_us * s;
+            if (best_us < 0.0f || us < best_us) {
+                best_us = us;
+                best = shape;
+                best.splits = s;
+            }
+            if (d.num_splits > 0) break;
         }
     }
-    if (splits > nt_max) splits = nt_max;
-    if (splits < 1) splits = 1;
-    if (splits > 64) splits = 64;
-    return splits;
+    return best;
 }
 
 size_t attention_bf16_workspace(const gsd_attn_desc &d, int splits) {
@@ -1060,7 +1000,8 @@ hipError_t attention_static_scratch(void **ptr) {
     return hipSuccess;
 }
 
-hipError_t launch_attention_bf16(const gsd_attn_desc &d, int splits, hipStream_t stream) {
+hipError_t launch_attention_bf16(const gsd_attn_desc &d, const AttnPlan &plan, hipStream_t stream) {
+    const int splits = plan.splits;
     AttnParams p;
     p.q = (const __bf16 *)d.q; p.o = (__bf16 *)d.o; p.lse = d.lse;
     p.k = (const __bf16 *)d.k; p.v = (const __bf16 *)d.v;
@@ -1071,27 +1012,32 @@ hipError_t launch_attention_bf16(const gsd_attn_desc &d, int splits, hipStream_t
     p.kv_ts = d.kv_token_stride; p.kv_hs = d.kv_head_stride;
     p.batch = d.batch; p.total_nodes = d.total_nodes; p.max_nodes = d.max_nodes; p.num_q_heads = d.num_q_heads;
     p.num_kv_heads = d.num_kv_heads; p.group = d.num_q_heads / d.num_kv_heads; p.words_per_row = d.words_per_row;
-    p.q_tiles = q_tiles_of(d);
+    p.q_tiles = (d.max_nodes * p.group + plan.rows_per_wg() - 1) / plan.rows_per_wg();
     p.splits = splits;
     p.wg_per_xcd = (d.batch * d.num_kv_heads + 7) / 8 * p.q_tiles * splits;
     p.scale_log2e = d.softmax_scale * kLog2e;
 
-    const WgShape sh = shape_of(d);
-    const dim3 grid(p.wg_per_xcd * 8), block(sh.waves * 64);
-    if (d.head_dim == 128) {
-        if (sh.blocks == 2) hipLaunchKernelGGL((dag_attention_bf16_kernel<128, 4, 2>), grid, block, 0, stream, p);
-        else if (sh.waves == 8) hipLaunchKernelGGL((dag_attention_bf16_kernel<128, 8, 1>), grid, block, 0, stream, p);
-        else hipLaunchKernelGGL((dag_attention_bf16_kernel<128, 4, 1>), grid, block, 0, stream, p);
+    hipError_t err;
+    if (plan.row_groups) {
+        err = launch_attention_bf16_keys(p, d.head_dim, plan.row_groups, stream);
     } else {
-        if (sh.blocks == 2) hipLaunchKernelGGL((dag_attention_bf16_kernel<64, 4, 2>), grid, block, 0, stream, p);
-        else if (sh.waves == 8) hipLaunchKernelGGL((dag_attention_bf16_kernel<64, 8, 1>), grid, block, 0, stream, p);
-        else hipLaunchKernelGGL((dag_attention_bf16_kernel<64, 4, 1>), grid, block, 0, stream, p);
+        const dim3 grid(p.wg_per_xcd * 8), block(plan.waves * 64);
+        if (d.head_dim == 128) {
+            if (plan.blocks == 2) hipLaunchKernelGGL((dag_attention_bf16_kernel<128, 4, 2>), grid, block, 0, stream, p);
+            else if (plan.waves == 8) hipLaunchKernelGGL((dag_attention_bf16_kernel<128, 8, 1>), grid, block, 0, stream, p);
+            else hipLaunchKernelGGL((dag_attention_bf16_kernel<128, 4, 1>), grid, block, 0, stream, p);
+        } else {
+            if (plan.blocks == 2) hipLaunchKernelGGL((dag_attention_bf16_kernel<64, 4, 2>), grid, block, 0, stream, p);
+            else if (plan.waves == 8) hipLaunchKernelGGL((dag_attention_bf16_kernel<64, 8, 1>), grid, block, 0, stream, p);
+            else hipLaunchKernelGGL((dag_attention_bf16_kernel<64, 4, 1>), grid, block, 0, stream, p);
+        }
+        err = hipGetLastError();
     }
-    hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     if (splits > 1) {
         const int64_t rows = int64_t(d.total_nodes) * d.num_q_heads;
-        const dim3 cgrid((unsigned)((rows + 3) / 4));
+        const int rows_per_block = 256 / (d.head_dim / 4);
+        const dim3 cgrid((unsigned)((rows + rows_per_block - 1) / rows_per_block));
         if (d.head_dim == 128)
             hipLaunchKernelGGL(dag_attention_combine_kernel<128>, cgrid, dim3(256), 0, stream, p);
         else

@@ -83,13 +83,13 @@ int gsd_build_mask(int32_t batch, int32_t max_nodes, int32_t words_per_row, cons
 
 int gsd_dag_attention_splits(const gsd_attn_desc *desc) {
     if (check_attn_desc(desc) != GSD_OK) return -1;
-    return desc->dtype == GSD_BF16 ? gsd::attention_bf16_splits(*desc) : 1;
+    return desc->dtype == GSD_BF16 ? gsd::attention_bf16_plan(*desc).splits : 1;
 }
 
 size_t gsd_dag_attention_workspace(const gsd_attn_desc *desc) {
     if (check_attn_desc(desc) != GSD_OK) return (size_t)-1;
     if (desc->dtype != GSD_BF16) return 0;
-    return gsd::attention_bf16_workspace(*desc, gsd::attention_bf16_splits(*desc));
+    return gsd::attention_bf16_workspace(*desc, gsd::attention_bf16_plan(*desc).splits);
 }
 
 }  // extern "C"
@@ -136,13 +136,13 @@ int gsd_dag_attention(const gsd_attn_desc *desc, void *hip_stream) {
     if (d.dtype == GSD_F32) {
         err = gsd::launch_attention_f32(d, stream);
     } else {
-        const int splits = gsd::attention_bf16_splits(d);
-        const size_t need = gsd::attention_bf16_workspace(d, splits);
+        const gsd::AttnPlan plan = gsd::attention_bf16_plan(d);
+        const size_t need = gsd::attention_bf16_workspace(d, plan.splits);
         if (need > 0 && (!d.workspace || d.workspace_bytes < need))
-            return fail(GSD_ERR_WORKSPACE, "workspace of %zu bytes needed for %d KV splits, %zu given", need, splits,
+            return fail(GSD_ERR_WORKSPACE, "workspace of %zu bytes needed for %d KV splits, %zu given", need, plan.splits,
                         d.workspace ? d.workspace_bytes : size_t(0));
         if (need > 0 && !aligned16(d.workspace)) return fail(GSD_ERR_INVALID_ARG, "workspace must be 16-byte aligned");
-        err = gsd::launch_attention_bf16(d, splits, stream);
+        err = gsd::launch_attention_bf16(d, plan, stream);
     }
     return err == hipSuccess ? GSD_OK : hip_fail(err, "gsd_dag_attention launch");
 }
@@ -158,11 +158,11 @@ int gsd_dag_attention_static(const gsd_attn_desc *desc, void *hip_stream) {
     if (d.dtype == GSD_F32) {
         err = gsd::launch_attention_f32(d, stream);
     } else {
-        const int splits = gsd::attention_bf16_splits(d);
-        const size_t need = gsd::attention_bf16_workspace(d, splits);
+        const gsd::AttnPlan plan = gsd::attention_bf16_plan(d);
+        const size_t need = gsd::attention_bf16_workspace(d, plan.splits);
         if (need > GSD_STATIC_SCRATCH_BYTES)
             return fail(GSD_ERR_WORKSPACE, "%zu bytes of split partials (%d KV splits) exceed the static scratch of %zu",
-                        need, splits, size_t(GSD_STATIC_SCRATCH_BYTES));
+                        need, plan.splits, size_t(GSD_STATIC_SCRATCH_BYTES));
         d.workspace = nullptr;
         d.workspace_bytes = 0;
         if (need > 0) {
@@ -172,7 +172,7 @@ int gsd_dag_attention_static(const gsd_attn_desc *desc, void *hip_stream) {
             d.workspace = ptr;
             d.workspace_bytes = GSD_STATIC_SCRATCH_BYTES;
         }
-        err = gsd::launch_attention_bf16(d, splits, stream);
+        err = gsd::launch_attention_bf16(d, plan, stream);
     }
     return err == hipSuccess ? GSD_OK : hip_fail(err, "gsd_dag_attention_static launch");
 }

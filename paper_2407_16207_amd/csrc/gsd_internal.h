@@ -23,10 +23,17 @@ hipError_t launch_accept(int32_t batch, int32_t max_nodes, const int32_t *node_o
 
 hipError_t launch_attention_f32(const gsd_attn_desc &d, hipStream_t stream);
 
-// bf16 MFMA path.  `splits` >= 1 as chosen by attention_bf16_splits(); partials (if splits > 1) go to workspace.
-int attention_bf16_splits(const gsd_attn_desc &d);
+// bf16 MFMA path: which kernel, work-group shape and split count a descriptor gets.  Partials (if splits > 1) go to
+// workspace.
+struct AttnPlan {
+    int waves, blocks;     // dag_attention_bf16_kernel: wavefronts, 32-row blocks per wavefront
+    int row_groups;        // or, if not 0, dag_attention_bf16_keys_kernel with that many row groups
+    int splits;
+    int rows_per_wg() const { return row_groups ? row_groups * 32 : waves * blocks * 32; }
+};
+AttnPlan attention_bf16_plan(const gsd_attn_desc &d);
 size_t attention_bf16_workspace(const gsd_attn_desc &d, int splits);
-hipError_t launch_attention_bf16(const gsd_attn_desc &d, int splits, hipStream_t stream);
+hipError_t launch_attention_bf16(const gsd_attn_desc &d, const AttnPlan &plan, hipStream_t stream);
 // device address, on the current device, of the library's static scratch array of GSD_STATIC_SCRATCH_BYTES
 hipError_t attention_static_scratch(void **ptr);
 

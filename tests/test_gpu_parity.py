@@ -193,6 +193,16 @@ def test_attention_bf16_small_all_rows(gpu, ref, D, splits, waves):
     check_attention(gpu, ref, w, num_splits=splits, wg_waves=waves)
 
 
+@pytest.mark.parametrize("hq,hkv,D", [(2, 2, 128), (2, 2, 64), (6, 2, 128), (6, 2, 64), (16, 2, 128)])
+@pytest.mark.parametrize("splits", [0, 3])
+def test_attention_bf16_few_rows(gpu, ref, hq, hkv, D, splits):
+    """Shapes the library gives to the kernel whose wavefronts deal out the keys: rows and keys one below, at and above its
+    32-row groups, 32-key tiles and 128-key steps, more splits than steps, an empty prefix."""
+    rng = np.random.default_rng(700 + hq + D + splits)
+    check_attention(gpu, ref, custom_workload(rng, [1, 5, 10, 11, 21, 32, 33], [0, 1, 31, 117, 107, 96, 300], hq, hkv, D, "bf16"),
+                    num_splits=splits)
+
+
 def test_attention_bf16_mha_and_odd_group(gpu, ref):
     rng = np.random.default_rng(5)
     check_attention(gpu, ref, custom_workload(rng, [70, 3], [129, 5], 3, 3, 128, "bf16"))     # MHA
