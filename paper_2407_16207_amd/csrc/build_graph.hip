@@ -24,8 +24,11 @@
 // An edge from a later layer into an earlier one breaks the generation order as a topological order: the fill kernel
 // renumbers the graph by level (longest distance from the root, by relaxation), nodes of one level in generation
 // order (a counting sort: ballots within a wave, one scan over the per-wave counts).
-// Two launches: the first only counts nodes and edges per sequence, the second repeats the construction and writes
-// the packed graph behind the sequences before it (the library keeps no scratch memory).
+// The sequences' graphs are packed one behind the other, so a work-group needs the sizes of all sequences before its own:
+// each publishes its two counts in the output array `counts` as soon as it has them and waits for the others' only where
+// it starts to write, by which time they are there.  A small launch before it marks the counts as missing (the library
+// keeps no scratch memory).  Counting in a first kernel and constructing again in a second one took 16 + 31 us for eight
+// trees of 512 nodes, this one 32 us.
 #include "gsd_internal.h"
 
 namespace gsd {
@@ -329,72 +332,30 @@ __device__ __forceinline__ int stable_rank(GraphLds &s, int32_t *table, int key,
     return valid ? table[key * kWaves + wave] + place : -1;     // (the caller meets at a barrier before the table is used again)
 }
 
-__global__ __launch_bounds__(kGraphThreads) void graph_count_kernel(
-    int32_t max_nodes, const int32_t *__restrict__ node_offsets, const int32_t *__restrict__ tree_parent,
-    const int32_t *__restrict__ tokens, const float *__restrict__ draft_prob, int tau, float theta_prob, float theta_sib,
-    int32_t *__restrict__ counts /* [B][2]: nodes, edges */, int32_t *__restrict__ error_flag) {
-    __shared__ GraphLds s;
-    const int b = blockIdx.x;
-    const int64_t base = node_offsets[b];
-    int n = node_offsets[b + 1] - node_offsets[b];
-    bool bad = false;
-    if (n > max_nodes) {
-        n = max_nodes;
-        bad = true;
-    }
-    if (n < 0) n = 0;
-    construct(s, n, base, tree_parent, tokens, draft_prob, tau, theta_prob, theta_sib);
-    decide_merges(s, n);
-    const int i = threadIdx.x;
-    const bool ex = i < n && (s.flags[i] & kFlagExists);
-    const int nodes = block_scan(s, s.scan, ex ? 1 : 0);
-    const int total_nodes = s.scan[kGraphThreads - 1];
-    __syncthreads();
-    const int edges = block_scan(s, s.scan, ex ? 1 + (s.par[i] >= 0 ? s.merge_cnt[s.par[i]] : 0) : 0);
-    const int total_edges = s.scan[kGraphThreads - 1];
-    (void)nodes;
-    (void)edges;
-    if (i == 0) {
-        counts[2 * b] = total_nodes;
-        counts[2 * b + 1] = total_edges;
-        if ((bad || s.bad) && error_flag) atomicOr(error_flag, 1);
-    }
+constexpr int32_t kCountMissing = -1;          // in `counts`: this sequence has not got that far
+
+__global__ __launch_bounds__(256) void graph_clear_kernel(int64_t total, int32_t *__restrict__ counts) {
+    const int64_t x = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (x < total) counts[x] = kCountMissing;
 }
 
-__global__ __launch_bounds__(kGraphThreads) void graph_fill_kernel(
+// The wait for the earlier sequences ends: a work-group publishes its counts without waiting for anybody, and only
+// work-groups with smaller ids, which the chip starts first, are waited for.  It is bounded on top of that (a work-group
+// whose wait ran out reports malformed input and writes nothing).
+__global__ __launch_bounds__(kGraphThreads) void build_graph_kernel(
     int32_t batch, int32_t max_nodes, const int32_t *__restrict__ node_offsets, const int32_t *__restrict__ tree_parent,
     const int32_t *__restrict__ tokens, const float *__restrict__ draft_prob, int tau, float theta_prob, float theta_sib,
-    const int32_t *__restrict__ counts, int32_t *__restrict__ graph_node_offsets, int32_t *__restrict__ parent_offsets,
+    int32_t *counts /* [B][2]: nodes, edges */, int32_t *__restrict__ graph_node_offsets, int32_t *__restrict__ parent_offsets,
     int32_t *__restrict__ parent_idx, int64_t edge_capacity, int32_t *__restrict__ origin,
     int32_t *__restrict__ flags_out, int32_t *__restrict__ error_flag) {
     __shared__ GraphLds s;
     __shared__ int32_t red[2][kGraphThreads / 64];
     const int b = blockIdx.x;
     const int i = threadIdx.x;
-    // packed position of this sequence: sums over the sequences before it
-    int nb = 0, eb = 0;
-    for (int x = i; x < b; x += kGraphThreads) {
-        nb += counts[2 * x];
-        eb += counts[2 * x + 1];
-    }
-    for (int d = 32; d > 0; d >>= 1) {
-        nb += __shfl_xor(nb, d);
-        eb += __shfl_xor(eb, d);
-    }
-    if ((i & 63) == 0) {
-        red[0][i >> 6] = nb;
-        red[1][i >> 6] = eb;
-    }
-    __syncthreads();
-    int node_base = 0, edge_base = 0;
-    for (int w = 0; w < kGraphThreads / 64; ++w) {
-        node_base += red[0][w];
-        edge_base += red[1][w];
-    }
-
     const int64_t base = node_offsets[b];
     int n = node_offsets[b + 1] - node_offsets[b];
-    if (n > max_nodes) n = max_nodes;
+    const bool too_many = n > max_nodes;
+    if (too_many) n = max_nodes;
     if (n < 0) n = 0;
     construct(s, n, base, tree_parent, tokens, draft_prob, tau, theta_prob, theta_sib);
     decide_merges(s, n);
@@ -402,6 +363,18 @@ __global__ __launch_bounds__(kGraphThreads) void graph_fill_kernel(
     const bool merger = ex && (s.flags[i] & kFlagMerged);
     const int my_par = i < n ? s.par[i] : -2;
     const int my_first = merger ? s.merged_to[i] : -1;
+    const int my_edges = ex ? 1 + (my_par >= 0 ? s.merge_cnt[my_par] : 0) : 0;
+    {
+        int sum_nodes = ex ? 1 : 0, sum_edges = my_edges;
+        for (int d = 32; d > 0; d >>= 1) {
+            sum_nodes += __shfl_xor(sum_nodes, d);
+            sum_edges += __shfl_xor(sum_edges, d);
+        }
+        if ((i & 63) == 0) {
+            red[0][i >> 6] = sum_nodes;
+            red[1][i >> 6] = sum_edges;
+        }
+    }
     // Storage that construct() and decide_merges() are done with is used again from here on:
     int32_t *level = s.tok;                 // longest distance from the root, in edges below the root's children
     int32_t *group_level = s.first_ex;      // per node f: the largest level among f and the nodes merged into it
@@ -409,6 +382,17 @@ __global__ __launch_bounds__(kGraphThreads) void graph_fill_kernel(
     int32_t *list_off = reinterpret_cast<int32_t *>(s.sib_max);     // per f: where its mergers' new ids start in `list`
     int32_t *list = s.cls;                  // new ids of the mergers of every f, ascending within an f
     __syncthreads();
+    int total_nodes = 0, total_edges = 0;
+#pragma unroll
+    for (int w = 0; w < kGraphThreads / 64; ++w) {
+        total_nodes += red[0][w];
+        total_edges += red[1][w];
+    }
+    if (i == 0) {
+        __hip_atomic_store(&counts[2 * int64_t(b)], total_nodes, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&counts[2 * int64_t(b) + 1], total_edges, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((too_many || s.bad) && error_flag) atomicOr(error_flag, 1);
+    }
     level[i] = ex ? s.depth[i] - 1 : -1;
     group_level[i] = -1;
     __syncthreads();
@@ -431,8 +415,8 @@ __global__ __launch_bounds__(kGraphThreads) void graph_fill_kernel(
     // new id = rank by (level, id) among the existing nodes
     int32_t *table = reinterpret_cast<int32_t *>(s.pool);            // the ancestor rows are not needed any more
     int32_t *node_of = table + 8 * GSD_MAX_NODES_PER_SEQ;           // node with a given new id
-    int total_nodes = 0;
-    const int my_new = stable_rank(s, table, ex ? level[i] : 0, ex, total_nodes);
+    int ranked = 0;
+    const int my_new = stable_rank(s, table, ex ? level[i] : 0, ex, ranked);
     new_id[i] = my_new;
     if (ex) node_of[my_new] = i;
     __syncthreads();
@@ -446,14 +430,48 @@ __global__ __launch_bounds__(kGraphThreads) void graph_fill_kernel(
     if (v_merger) list[place] = i;
     __syncthreads();
     // edges, in the order of the new ids
-    const int my_edges = ex ? 1 + (my_par >= 0 ? s.merge_cnt[my_par] : 0) : 0;
     int32_t *by_rank = s.depth;             // depth is not read any more
     by_rank[i] = 0;
     __syncthreads();
     if (ex) by_rank[my_new] = my_edges;
     __syncthreads();
     (void)block_scan(s, s.scan, by_rank[i]);
-    const int total_edges = s.scan[kGraphThreads - 1];
+    // packed position of this sequence: sums over the sequences before it
+    constexpr int kPollLimit = 1 << 22;
+    int nb = 0, eb = 0, lost = 0;
+    for (int x = i; x < b; x += kGraphThreads) {
+        int32_t cn = kCountMissing, ce = kCountMissing;
+        for (int poll = 0; poll < kPollLimit; ++poll) {
+            cn = __hip_atomic_load(&counts[2 * int64_t(x)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            ce = __hip_atomic_load(&counts[2 * int64_t(x) + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (cn != kCountMissing && ce != kCountMissing) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        if (cn == kCountMissing || ce == kCountMissing) {
+            lost = 1;
+            break;
+        }
+        nb += cn;
+        eb += ce;
+    }
+    for (int d = 32; d > 0; d >>= 1) {
+        nb += __shfl_xor(nb, d);
+        eb += __shfl_xor(eb, d);
+    }
+    if ((i & 63) == 0) {                    // (the counts of this sequence were read from here several barriers ago)
+        red[0][i >> 6] = nb;
+        red[1][i >> 6] = eb;
+    }
+    if (__syncthreads_or(lost)) {
+        if (i == 0 && error_flag) atomicOr(error_flag, 1);
+        return;
+    }
+    int node_base = 0, edge_base = 0;
+#pragma unroll
+    for (int w = 0; w < kGraphThreads / 64; ++w) {
+        node_base += red[0][w];
+        edge_base += red[1][w];
+    }
     if (ex) {
         const int g = node_base + my_new;
         origin[g] = i;
@@ -492,11 +510,11 @@ hipError_t launch_build_graph(int32_t batch, int32_t max_nodes, const int32_t *n
                               float theta_sib, int32_t *counts, int32_t *graph_node_offsets, int32_t *parent_offsets,
                               int32_t *parent_idx, int64_t edge_capacity, int32_t *origin, int32_t *flags,
                               int32_t *error_flag, hipStream_t stream) {
-    hipLaunchKernelGGL(graph_count_kernel, dim3(batch), dim3(kGraphThreads), 0, stream, max_nodes, node_offsets,
-                       tree_parent, tokens, draft_prob, tau, theta_prob, theta_sib, counts, error_flag);
+    const int64_t total = 2 * int64_t(batch);
+    hipLaunchKernelGGL(graph_clear_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, total, counts);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(graph_fill_kernel, dim3(batch), dim3(kGraphThreads), 0, stream, batch, max_nodes, node_offsets,
+    hipLaunchKernelGGL(build_graph_kernel, dim3(batch), dim3(kGraphThreads), 0, stream, batch, max_nodes, node_offsets,
                        tree_parent, tokens, draft_prob, tau, theta_prob, theta_sib, counts, graph_node_offsets,
                        parent_offsets, parent_idx, edge_capacity, origin, flags, error_flag);
     return hipGetLastError();

@@ -526,6 +526,15 @@ def test_build_token_graph_many_sequences(gpu):
     assert len(r[0]) == len(sizes) + 1 and int(((r[4] & 4) != 0).sum()) > 1000
 
 
+@pytest.mark.parametrize("sizes", [[0], [0, 1, 0, 512, 0, 3], [1] * 64 + [0] * 513 + [65]])
+def test_build_token_graph_empty_sequences(gpu, sizes):
+    """An empty sequence's counts are zeros, not missing: the sequences behind it go on."""
+    rng = np.random.default_rng(41)
+    node_offsets, par, tok, q = token_trees(rng, [x for x in sizes if x] or [1], 3, 5)
+    node_offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    compare_graph_with_oracle(gpu, node_offsets, par, tok, q, 2, 0.0, 0.0)
+
+
 def test_build_token_graph_flags_bad_input_and_small_capacity(gpu):
     import paper_2407_16207_amd as gsd
     par = np.array([-1, 0, 3, 0, -5, 1], dtype=np.int32)          # node 2 points forward, node 4 below -1
