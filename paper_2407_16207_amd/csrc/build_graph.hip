@@ -47,8 +47,9 @@ struct GraphLds {
     int32_t cls[GSD_MAX_NODES_PER_SEQ];        // class of the node's tau-gram (an earlier-or-equal node id), -1 if none
     int32_t first_ex[GSD_MAX_NODES_PER_SEQ];   // per class: smallest existing node seen so far
     int32_t merge_cnt[GSD_MAX_NODES_PER_SEQ];  // nodes merged into this one (merge edges actually drawn)
-    // 32 KB used three times over: the key table of the tau-gram classes, then (merge decisions) per node the set of
-    // redundant nodes it is the first occurrence for, word-major, then the counting tables of the renumbering
+    // 32 KB used four times over: the key table of the tau-gram classes, then (merge decisions) per node the set of
+    // redundant nodes it is the first occurrence for, word-major, then the counting table of the renumbering, then the
+    // sets of mergers
     uint64_t pool[GSD_MAX_NODES_PER_SEQ * 8];
     int32_t wave_tot[16];
     int32_t bad;
@@ -379,8 +380,7 @@ __global__ __launch_bounds__(kGraphThreads) void build_graph_kernel(
     int32_t *level = s.tok;                 // longest distance from the root, in edges below the root's children
     int32_t *group_level = s.first_ex;      // per node f: the largest level among f and the nodes merged into it
     int32_t *new_id = reinterpret_cast<int32_t *>(s.q);
-    int32_t *list_off = reinterpret_cast<int32_t *>(s.sib_max);     // per f: where its mergers' new ids start in `list`
-    int32_t *list = s.cls;                  // new ids of the mergers of every f, ascending within an f
+    constexpr int kSetWords = GSD_MAX_NODES_PER_SEQ / 32;           // words of a set of nodes
     __syncthreads();
     int total_nodes = 0, total_edges = 0;
 #pragma unroll
@@ -414,21 +414,17 @@ __global__ __launch_bounds__(kGraphThreads) void build_graph_kernel(
     }
     // new id = rank by (level, id) among the existing nodes
     int32_t *table = reinterpret_cast<int32_t *>(s.pool);            // the ancestor rows are not needed any more
-    int32_t *node_of = table + 8 * GSD_MAX_NODES_PER_SEQ;           // node with a given new id
     int ranked = 0;
     const int my_new = stable_rank(s, table, ex ? level[i] : 0, ex, ranked);
     new_id[i] = my_new;
-    if (ex) node_of[my_new] = i;
     __syncthreads();
-    // the mergers of every first occurrence, sorted by new id: with the threads standing in the order of the new ids,
-    // a merger's place in the list of all mergers is its rank by (first occurrence, new id)
-    const int node_r = i < total_nodes ? node_of[i] : -1;         // this thread stands for the node with new id i
-    const bool v_merger = node_r >= 0 && (s.flags[node_r] & kFlagMerged);
-    int total_mergers = 0;
-    const int place = stable_rank(s, table, v_merger ? s.merged_to[node_r] : 0, v_merger, total_mergers);
-    list_off[i] = table[i * (kGraphThreads / 64)];
-    if (v_merger) list[place] = i;
+    // The mergers of every first occurrence as a set of new ids, word-major: read in order, the set of a node's tree
+    // parent, with that parent itself added, is the node's list of parents.
+    uint32_t *mergers = reinterpret_cast<uint32_t *>(s.pool);       // [16][GSD_MAX_NODES_PER_SEQ], the table's place
+#pragma unroll
+    for (int w = 0; w < kSetWords; ++w) mergers[w * GSD_MAX_NODES_PER_SEQ + i] = 0;
     __syncthreads();
+    if (merger) atomicOr(&mergers[(my_new >> 5) * GSD_MAX_NODES_PER_SEQ + my_first], 1u << (my_new & 31));
     // edges, in the order of the new ids
     int32_t *by_rank = s.depth;             // depth is not read any more
     by_rank[i] = 0;
@@ -485,14 +481,16 @@ __global__ __launch_bounds__(kGraphThreads) void build_graph_kernel(
         };
         if (my_par < 0) {
             put(-1);
-        } else {                                // the tree parent's new id merged into the sorted ids of its mergers
+        } else {
             const int pid = new_id[my_par];
-            const int k = s.merge_cnt[my_par];
-            const int32_t *m = list + list_off[my_par];
-            int x = 0;
-            for (; x < k && m[x] < pid; ++x) put(m[x]);
-            put(pid);
-            for (; x < k; ++x) put(m[x]);
+#pragma unroll
+            for (int w = 0; w < kSetWords; ++w) {
+                uint32_t set = mergers[w * GSD_MAX_NODES_PER_SEQ + my_par] | (w == (pid >> 5) ? 1u << (pid & 31) : 0u);
+                while (set != 0) {
+                    put(32 * w + __ffs(set) - 1);
+                    set &= set - 1;
+                }
+            }
         }
         if (over && error_flag) atomicOr(error_flag, 2);
     }
