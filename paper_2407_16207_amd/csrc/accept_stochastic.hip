@@ -1,19 +1,23 @@
 // Non-deterministic verification (paper Section 3: the i-th drafted token is accepted with probability
 // min(1, p/q), the first rejection discards the rest of the hypothesis and the LLM regenerates that token;
-// Section 6.4: the setting on token graphs).  Three kernels:
+// Section 6.4: the setting on token graphs).  Two kernels:
 //
 //   softmax_stats_kernel    one pass over a logits row: running (max, sum of exp(x - max)) per lane, merged across
 //                           the work-group: the normaliser of the LLM's distribution after every node.  HBM-bound,
 //                           same traffic as the argmax pass of deterministic verification.
-//   accept_stochastic_kernel one work-group per sequence: every edge r -> i is tested once,
+//   accept_and_resample_kernel one work-group per sequence, in two phases that share everything but the vocabulary rows:
+//     accept_phase            every edge r -> i is tested once,
 //                               accept_u[i] * draft_prob[i] < p_r(token_i)      (<=> u < min(1, p/q) for u < 1)
 //                           with p_r(token_i) = exp(logit - max_r) / sum_r gathered from the row of r, then the same
 //                           relaxation, end-node choice and back-walk as the deterministic kernel.
-//   resample_kernel         one work-group per sequence: the regenerated token, drawn by inverse CDF from
-//                           max(p - q, 0) at the end of the accepted path (from p if that node has no children or the
-//                           residual is empty).  Every thread owns a contiguous slice of the vocabulary, slice sums
-//                           are scanned in thread order, the owning thread walks its slice: one fixed summation order.
-//                           (resample_held_kernel: the same with the slices kept in registers, where they fit.)
+//     resample_phase          the regenerated token, drawn by inverse CDF from max(p - q, 0) at the end of the accepted
+//                           path (from p if that node has no children or the residual is empty).  Every thread owns a
+//                           contiguous slice of the vocabulary, slice sums are scanned in thread order, the owning
+//                           thread walks its slice: one fixed summation order.
+//                           (resample_held_phase: the same with the slices kept in registers, where they fit.)
+// Both phases are chains of dependent round trips on one CU per sequence.  As two kernels (7.0 + 11.7 us on 8 sequences
+// of 256 nodes, 32000 tokens) the second waited for a launch and fetched end node, offsets and parents again: together
+// 16.7 us.
 #include "gsd_internal.h"
 
 namespace gsd {
@@ -136,14 +140,21 @@ hipError_t launch_softmax_stats(int64_t rows, int32_t vocab, int dtype, const vo
     return hipGetLastError();
 }
 
-constexpr int kStochThreads = 512;
+constexpr int kStochThreads = 1024;            // one per node in the first phase, one per vocabulary slice in the second
 
-__global__ __launch_bounds__(kStochThreads) void accept_stochastic_kernel(const gsd_stochastic_desc d) {
-    __shared__ int32_t L[GSD_MAX_NODES_PER_SEQ];
-    __shared__ int32_t path_s[GSD_MAX_NODES_PER_SEQ];
-    __shared__ int32_t back_s[GSD_MAX_NODES_PER_SEQ];
-    __shared__ uint32_t wave_best[kStochThreads / 64];
-    __shared__ int32_t len_s;
+struct AcceptLds {
+    int32_t L[GSD_MAX_NODES_PER_SEQ];
+    int32_t path[GSD_MAX_NODES_PER_SEQ];
+    int32_t back[GSD_MAX_NODES_PER_SEQ];
+    uint32_t wave_best[kStochThreads / 64];
+    int32_t len, end;
+};
+
+// Writes accept_len, accept_path and end_node of the calling work-group's sequence.  Returns the end node (-1: the root)
+// and, in `child`, whether one of the calling thread's nodes is a child of it.
+__device__ __forceinline__ int accept_phase(AcceptLds &s, const gsd_stochastic_desc &d, bool &child) {
+    int32_t *L = s.L, *path_s = s.path, *back_s = s.back;
+    uint32_t *wave_best = s.wave_best;
     static_assert(kStochThreads >= GSD_MAX_NODES_PER_SEQ, "one thread per node");
 
     const int b = blockIdx.x;
@@ -163,6 +174,9 @@ __global__ __launch_bounds__(kStochThreads) void accept_stochastic_kernel(const 
 #pragma unroll
     for (int x = 0; x < kRegParents; ++x) par[x] = -2;
     int32_t e_lo = 0, e_hi = 0;    // this node's slice of parent_idx
+    int32_t r[kRegParents];        // its first entries as they stand there, the last one repeated
+#pragma unroll
+    for (int x = 0; x < kRegParents; ++x) r[x] = -2;
     int32_t tok = 0;
     bool tok_ok = false;           // a token outside the vocabulary is never accepted
     float coin = 0.f;              // accept_u * draft_prob: the edge passes iff coin < p_r(tok)
@@ -182,7 +196,6 @@ __global__ __launch_bounds__(kStochThreads) void accept_stochastic_kernel(const 
         tok_ok = tok >= 0 && tok < d.vocab;
         if (!tok_ok) tok = 0;                                  // keeps the gathers below in bounds
         if (e_hi > e_lo) {
-            int r[kRegParents];
 #pragma unroll
             for (int x = 0; x < kRegParents; ++x) r[x] = d.parent_idx[min(e_lo + x, e_hi - 1)];
 #pragma unroll
@@ -259,7 +272,8 @@ __global__ __launch_bounds__(kStochThreads) void accept_stochastic_kernel(const 
         for (int w = 0; w < kStochThreads / 64; ++w) k = wave_best[w] > k ? wave_best[w] : k;
         const int32_t len = int32_t(k / 1024u);
         int32_t v = (len > 0) ? int32_t(1023u - (k % 1024u)) : -1;
-        len_s = len;
+        s.len = len;
+        s.end = v;
         d.accept_len[b] = len;
         d.end_node[b] = v;
         for (int pos = len - 1; pos >= 0 && v >= 0 && v < n; --pos) {   // L drops by one per step: the root's child sits at pos 0
@@ -268,37 +282,31 @@ __global__ __launch_bounds__(kStochThreads) void accept_stochastic_kernel(const 
         }
     }
     __syncthreads();
-    const int32_t len = len_s;
+    const int32_t len = s.len, end = s.end;
     int32_t *out = d.accept_path + int64_t(b) * d.max_nodes;
     for (int x = threadIdx.x; x < d.max_nodes; x += kStochThreads) out[x] = (x < len) ? path_s[x] : -1;
+    child = false;
+    if (active && e_hi > e_lo) {
+#pragma unroll
+        for (int x = 0; x < kRegParents; ++x) child |= r[x] == end;
+        for (int e = e_lo + kRegParents; e < e_hi; ++e) child |= d.parent_idx[e] == end;
+    }
+    return end;
 }
 
-constexpr int kResampleThreads = 1024;
+constexpr int kResampleThreads = kStochThreads;
 
-__global__ __launch_bounds__(kResampleThreads) void resample_kernel(const gsd_stochastic_desc d) {
+__device__ __forceinline__ void resample_phase(const gsd_stochastic_desc &d, int end, bool child) {
     __shared__ float red_m[kResampleThreads / 64], red_s[kResampleThreads / 64];
     __shared__ float part[kResampleThreads];
     __shared__ float stat[4];
-    __shared__ int has_child_s, pick_s;
+    __shared__ int pick_s;
 
     const int b = blockIdx.x;
     const int64_t base = d.node_offsets[b];
-    int n = d.node_offsets[b + 1] - d.node_offsets[b];
-    if (n > d.max_nodes) n = d.max_nodes;
-    if (n < 0) n = 0;
-    const int end = d.end_node[b];
     const int V = d.vocab;
-
-    // does the end node (or the root) have children ?
-    if (threadIdx.x == 0) {
-        has_child_s = 0;
-        pick_s = -1;
-    }
-    __syncthreads();
-    const int32_t e0 = d.parent_offsets[base], e1 = d.parent_offsets[base + n];
-    int mine = 0;
-    for (int e = e0 + threadIdx.x; e < e1; e += kResampleThreads) mine |= (d.parent_idx[e] == end);
-    if (mine) has_child_s = 1;
+    if (threadIdx.x == 0) pick_s = -1;
+    const bool use_residual = __syncthreads_or(child) != 0;      // does the end node (or the root) have children ?
 
     const void *p_row = end < 0 ? d.root_logits : d.logits;
     const void *q_row = end < 0 ? d.root_draft_logits : d.draft_logits;
@@ -326,7 +334,6 @@ __global__ __launch_bounds__(kResampleThreads) void resample_kernel(const gsd_st
     }
     __syncthreads();
     const float q_max = stat[0], q_sum = stat[1];
-    const bool use_residual = has_child_s != 0;
 
     // contiguous slice of the vocabulary per thread
     const int per = (V + kResampleThreads - 1) / kResampleThreads;
@@ -447,7 +454,7 @@ __global__ __launch_bounds__(kResampleThreads) void resample_kernel(const gsd_st
 constexpr int kHeld = 32;
 
 template <bool BF16>
-__global__ __launch_bounds__(kResampleThreads) void resample_held_kernel(const gsd_stochastic_desc d) {
+__device__ __forceinline__ void resample_held_phase(const gsd_stochastic_desc &d, int end, bool child) {
     constexpr int ELT = BF16 ? 2 : 4;
     constexpr int PER_VEC = 16 / ELT;
     constexpr int KV = kHeld / PER_VEC;
@@ -459,10 +466,6 @@ __global__ __launch_bounds__(kResampleThreads) void resample_held_kernel(const g
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int b = blockIdx.x;
     const int64_t base = d.node_offsets[b];
-    int n = d.node_offsets[b + 1] - d.node_offsets[b];
-    if (n > d.max_nodes) n = d.max_nodes;
-    if (n < 0) n = 0;
-    const int end = d.end_node[b];
     const int V = d.vocab;
     if (t == 0) pick_s = -1;
 
@@ -481,10 +484,6 @@ __global__ __launch_bounds__(kResampleThreads) void resample_held_kernel(const g
     }
     const float p_max = end < 0 ? d.row_max[d.total_nodes + b] : d.row_max[base + end];
     const float p_sum = end < 0 ? d.row_sumexp[d.total_nodes + b] : d.row_sumexp[base + end];
-    // does the end node (or the root) have children ?
-    const int32_t e0 = d.parent_offsets[base], e1 = d.parent_offsets[base + n];
-    int mine = 0;
-    for (int e = e0 + t; e < e1; e += kResampleThreads) mine |= (d.parent_idx[e] == end);
 
     auto value = [&](const u32x4 v, int e) -> float {
         if (BF16) return (e & 1) ? __uint_as_float(v[e >> 1] & 0xffff0000u) : __uint_as_float(v[e >> 1] << 16);
@@ -514,7 +513,7 @@ __global__ __launch_bounds__(kResampleThreads) void resample_held_kernel(const g
         red_m[wave] = m;
         red_s[wave] = sum;
     }
-    const bool use_residual = __syncthreads_or(mine) != 0;
+    const bool use_residual = __syncthreads_or(child) != 0;       // does the end node (or the root) have children ?
     float q_max = red_m[0], q_sum = red_s[0];
     for (int w = 1; w < kWaves; ++w) merge_state(q_max, q_sum, red_m[w], red_s[w]);
 
@@ -526,13 +525,17 @@ __global__ __launch_bounds__(kResampleThreads) void resample_held_kernel(const g
     // the cumulative weight before this thread's slice and up to its end: the slice in ascending token order, the
     // wave in lane order, the waves in their order
     float before = 0.f, upto = 0.f, total = 0.f;
+    float held[kHeld];                                            // the slice's weights: the owner walks them
     auto scan = [&](bool residual, int turn) {
         float local = 0.f;
 #pragma unroll
         for (int j = 0; j < KV; ++j)
-            if (j < nvec) {
 #pragma unroll
-                for (int e = 0; e < PER_VEC; ++e) local += weight_of(value(raw_p[j], e), value(raw_q[j], e), residual);
+            for (int e = 0; e < PER_VEC; ++e) {
+                float &w = held[j * PER_VEC + e];
+                w = 0.f;
+                if (j < nvec) w = weight_of(value(raw_p[j], e), value(raw_q[j], e), residual);
+                local += w;
             }
         float incl = local;
 #pragma unroll
@@ -568,7 +571,7 @@ __global__ __launch_bounds__(kResampleThreads) void resample_held_kernel(const g
             if (j < nvec) {
 #pragma unroll
                 for (int e = 0; e < PER_VEC; ++e) {
-                    const float w = weight_of(value(raw_p[j], e), value(raw_q[j], e), residual);
+                    const float w = held[j * PER_VEC + e];
                     run += w;
                     if (w > 0.f) last = x0 + j * PER_VEC + e;
                     if (pick < 0 && run > target) pick = x0 + j * PER_VEC + e;
@@ -584,7 +587,7 @@ __global__ __launch_bounds__(kResampleThreads) void resample_held_kernel(const g
             if (j < nvec) {
 #pragma unroll
                 for (int e = 0; e < PER_VEC; ++e)
-                    if (weight_of(value(raw_p[j], e), value(raw_q[j], e), residual) > 0.f) last = x0 + j * PER_VEC + e;
+                    if (held[j * PER_VEC + e] > 0.f) last = x0 + j * PER_VEC + e;
             }
         for (int off = 32; off > 0; off >>= 1) last = max(last, __shfl_xor(last, off, 64));
         __shared__ int wave_last[kWaves];
@@ -600,27 +603,36 @@ __global__ __launch_bounds__(kResampleThreads) void resample_held_kernel(const g
     if (t == 0) d.bonus_token[b] = pick_s;
 }
 
+enum class Resample { general, held_f32, held_bf16 };
+
+template <Resample KIND>
+__global__ __launch_bounds__(kStochThreads) void accept_and_resample_kernel(const gsd_stochastic_desc d) {
+    __shared__ AcceptLds s;
+    bool child = false;
+    const int end = __builtin_amdgcn_readfirstlane(accept_phase(s, d, child));
+    if constexpr (KIND == Resample::general) resample_phase(d, end, child);
+    else resample_held_phase<KIND == Resample::held_bf16>(d, end, child);
+}
+
 hipError_t launch_accept_stochastic(const gsd_stochastic_desc &d, hipStream_t stream) {
     // the node rows and, behind them, the root rows: one launch
     hipError_t err = launch_softmax_stats(d.total_nodes, d.vocab, d.dtype, d.logits, d.row_stride, d.row_max,
                                           d.row_sumexp, stream, d.batch, d.root_logits);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(accept_stochastic_kernel, dim3(d.batch), dim3(kStochThreads), 0, stream, d);
-    err = hipGetLastError();
-    if (err != hipSuccess) return err;
-    // slices that fit registers: see resample_held_kernel
+    // slices that fit registers: see resample_held_phase
     const int elt = d.dtype == GSD_BF16 ? 2 : 4;
     const int per = (d.vocab + kResampleThreads - 1) / kResampleThreads;
     auto aligned = [&](const void *ptr) { return reinterpret_cast<uintptr_t>(ptr) % 16 == 0; };
     const bool held = per <= kHeld && (per * elt) % 16 == 0 && (int64_t(d.vocab) * elt) % 16 == 0 &&
                       (d.row_stride * elt) % 16 == 0 && aligned(d.logits) && aligned(d.root_logits) &&
                       aligned(d.draft_logits) && aligned(d.root_draft_logits);
+    const dim3 grid(d.batch), block(kStochThreads);
     if (held && d.dtype == GSD_BF16)
-        hipLaunchKernelGGL(resample_held_kernel<true>, dim3(d.batch), dim3(kResampleThreads), 0, stream, d);
+        hipLaunchKernelGGL(accept_and_resample_kernel<Resample::held_bf16>, grid, block, 0, stream, d);
     else if (held)
-        hipLaunchKernelGGL(resample_held_kernel<false>, dim3(d.batch), dim3(kResampleThreads), 0, stream, d);
+        hipLaunchKernelGGL(accept_and_resample_kernel<Resample::held_f32>, grid, block, 0, stream, d);
     else
-        hipLaunchKernelGGL(resample_kernel, dim3(d.batch), dim3(kResampleThreads), 0, stream, d);
+        hipLaunchKernelGGL(accept_and_resample_kernel<Resample::general>, grid, block, 0, stream, d);
     return hipGetLastError();
 }
 
