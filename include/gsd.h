@@ -96,7 +96,8 @@ int gsd_build_mask(int32_t batch, int32_t max_nodes, int32_t words_per_row, cons
  * lse (optional, [T][Hq] fp32): natural-log sum of exp of the scaled scores over the visible keys.
  *
  * Small problems are split along the KV prefix across work-groups and merged by a second kernel in a fixed
- * order; the partial results live in `workspace` (gsd_dag_attention_workspace() bytes, 0 if unsplit).
+ * order; the partial results live in `workspace` (gsd_dag_attention_workspace() bytes, 0 if unsplit).  An fp32 call
+ * whose workspace is missing, smaller or not 16-byte aligned runs unsplit; a bf16 call is refused.
  */
 typedef struct gsd_attn_desc {
     int32_t batch;         /* B */
@@ -137,8 +138,8 @@ int gsd_dag_attention(const gsd_attn_desc *desc, void *hip_stream);
 
 /*
  * gsd_dag_attention for callers that cannot allocate device memory or pass a workspace (code under HIP graph
- * capture, tight serving loops, harnesses that forbid hipMalloc): the same kernels and the same results, but the
- * split-KV partials live in an array of GSD_STATIC_SCRATCH_BYTES inside the library, one copy per GPU, held until
+ * capture, tight serving loops, harnesses that forbid hipMalloc): the same kernels and the same results (fp32 runs
+ * unsplit: the same up to the order of its sums), but the split-KV partials live in an array of GSD_STATIC_SCRATCH_BYTES inside the library, one copy per GPU, held until
  * the process ends.  desc->workspace and desc->workspace_bytes are ignored.  A descriptor whose partials
  * (gsd_dag_attention_workspace() bytes) exceed GSD_STATIC_SCRATCH_BYTES is rejected with GSD_ERR_WORKSPACE before
  * anything is launched.  Calls no allocating routine.  All calls on one GPU share that GPU's array: two calls that

@@ -1,5 +1,5 @@
 // What the two bf16 attention kernels (dag_attention_bf16.hip, dag_attention_bf16_keys.hip) share: parameters, operand
-// types, global -> LDS copies.
+// types, global -> LDS copies; and the merge of split partials, which the fp32 kernel uses too.
 #pragma once
 #include "gsd_internal.h"
 
@@ -93,6 +93,7 @@ __device__ __forceinline__ void mfma_a_acc(floatx16 &acc, const bf16x8 &a, const
 // at least 16 issue cycles: longer than the 12 the vector ALU must keep away from an 8-pass matrix result
 __device__ __forceinline__ void mfma_settle() { asm volatile("s_nop 7\n\ts_nop 7" ::: "memory"); }
 
+hipError_t launch_attention_combine(const AttnParams &p, int head_dim, int dtype, hipStream_t stream);
 hipError_t launch_attention_bf16_keys(const AttnParams &p, int head_dim, int row_groups, hipStream_t stream);
 
 }  // namespace gsd

@@ -863,7 +863,7 @@ __global__ __launch_bounds__(NW * 64, RBW == 2 ? 1 : 8 / NW) void dag_attention_
 // latency, so every load of a row is independent of the others: the (offset, sum) pairs are fetched one per lane and
 // handed round by shuffles, the outputs four splits at a time.  (A wavefront per row that walked the splits, two channels
 // per lane: 8.7 us for 4096 rows and 16 splits where this one takes about 6.)
-template <int D>
+template <int D, typename OUT>
 __global__ __launch_bounds__(256) void dag_attention_combine_kernel(const AttnParams p) {
     constexpr int LPR = D / 4;                                             // lanes per row
     constexpr int HELD = 64 / LPR;                                         // (offset, sum) pairs per lane, 64 splits at most
@@ -908,10 +908,11 @@ __global__ __launch_bounds__(256) void dag_attention_combine_kernel(const AttnPa
     const float inv = sum > 0.f ? 1.f / sum : 0.f;
     const int64_t t = row / p.num_q_heads;
     const int head = int(row - t * p.num_q_heads);
-    bf16x4 o;
+    typedef OUT OutX4 __attribute__((ext_vector_type(4)));
+    OutX4 o;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = (__bf16)(acc[e] * inv);
-    *reinterpret_cast<bf16x4 *>(p.o + t * p.o_ts + int64_t(head) * p.o_hs + 4 * in_row) = o;
+    for (int e = 0; e < 4; ++e) o[e] = (OUT)(acc[e] * inv);
+    *reinterpret_cast<OutX4 *>(reinterpret_cast<OUT *>(p.o) + t * p.o_ts + int64_t(head) * p.o_hs + 4 * in_row) = o;
     if (p.lse && in_row == 0) p.lse[row] = sum > 0.f ? (top + __log2f(sum)) * 0.6931471805599453f : -__builtin_inff();
 }
 
@@ -969,7 +970,7 @@ AttnPlan attention_bf16_plan(const gsd_attn_desc &d) {
     return best;
 }
 
-size_t attention_bf16_workspace(const gsd_attn_desc &d, int splits) {
+size_t attention_workspace(const gsd_attn_desc &d, int splits) {
     if (splits <= 1) return 0;
     return size_t(splits) * d.total_nodes * d.num_q_heads * (size_t(d.head_dim) + 2) * sizeof(float);
 }
@@ -998,6 +999,21 @@ hipError_t attention_static_scratch(void **ptr) {
     }
     *ptr = address[dev];
     return hipSuccess;
+}
+
+// merges the partials of p.splits splits into p.o, whose elements are of type `dtype`
+hipError_t launch_attention_combine(const AttnParams &p, int head_dim, int dtype, hipStream_t stream) {
+    const int64_t rows = int64_t(p.total_nodes) * p.num_q_heads;
+    const int rows_per_block = 256 / (head_dim / 4);
+    const dim3 grid((unsigned)((rows + rows_per_block - 1) / rows_per_block)), block(256);
+    if (dtype == GSD_BF16) {
+        if (head_dim == 128) hipLaunchKernelGGL((dag_attention_combine_kernel<128, __bf16>), grid, block, 0, stream, p);
+        else hipLaunchKernelGGL((dag_attention_combine_kernel<64, __bf16>), grid, block, 0, stream, p);
+    } else {
+        if (head_dim == 128) hipLaunchKernelGGL((dag_attention_combine_kernel<128, float>), grid, block, 0, stream, p);
+        else hipLaunchKernelGGL((dag_attention_combine_kernel<64, float>), grid, block, 0, stream, p);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_attention_bf16(const gsd_attn_desc &d, const AttnPlan &plan, hipStream_t stream) {
@@ -1033,18 +1049,7 @@ hipError_t launch_attention_bf16(const gsd_attn_desc &d, const AttnPlan &plan, h
         }
         err = hipGetLastError();
     }
-    if (err != hipSuccess) return err;
-    if (splits > 1) {
-        const int64_t rows = int64_t(d.total_nodes) * d.num_q_heads;
-        const int rows_per_block = 256 / (d.head_dim / 4);
-        const dim3 cgrid((unsigned)((rows + rows_per_block - 1) / rows_per_block));
-        if (d.head_dim == 128)
-            hipLaunchKernelGGL(dag_attention_combine_kernel<128>, cgrid, dim3(256), 0, stream, p);
-        else
-            hipLaunchKernelGGL(dag_attention_combine_kernel<64>, cgrid, dim3(256), 0, stream, p);
-        err = hipGetLastError();
-    }
-    return err;
+    return err != hipSuccess || splits <= 1 ? err : launch_attention_combine(p, d.head_dim, GSD_BF16, stream);
 }
 
 }  // namespace gsd

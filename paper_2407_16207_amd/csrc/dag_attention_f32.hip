@@ -16,18 +16,21 @@
 // What bounds it: a SIMD's matrix and vector instructions one after the other (a second wavefront per SIMD hides
 // nothing: 8 wavefronts over the same tiles take the same time), 64 matrix instructions of 14 ns per run at head_dim
 // 128 and a third of that again for softmax and addresses; with fewer tiles than CUs, the idle CUs.
-// 32 heads of 64 rows over 1088 keys, head_dim 128 (128 tiles, half the chip): 29.4 us = 38 TFLOP/s; 8 groups of 960
+// 32 heads of 64 rows over 1088 keys, head_dim 128 (128 tiles, half the chip): 31.4 us = 36 TFLOP/s; 8 groups of 960
 // rows over 1120 keys: 53 us = 78 TFLOP/s of the 154 that a large fp32 matrix product reaches.  The plain-FMA kernel
 // before this one (a lane per key, every lane reading a K and a V row of its own) took 313 and 1147 us, and 24.8 us
 // where this one takes 7.1 (4 heads, 16 nodes, 144 keys, head_dim 64).
+// Summed in one level the outputs were further from 64-bit sums than that kernel's (relative 4.5e-7 against 4.1e-7 on the
+// first case, 5.1e-7 against 3.6e-7 at head_dim 64); in two levels, with two chains per score, they are nearer (3.2e-7 and
+// 3.0e-7), for about 1 us.
 // 32-row tiles (every K/V operand used twice) need 232 registers and lose more to the coarser split: 51 and 54 us.
-#include "gsd_internal.h"
+// With a workspace the keys are also split over work-groups where the tiles leave CUs idle (attention_f32_splits), merged
+// by the kernel that merges the bf16 splits: the 128 tiles above then take 23.5 us, merge included.
+#include "attention_bf16.h"
 
 namespace gsd {
 
 namespace {
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kF32Waves = 4;
 constexpr float kF32Log2e = 1.4426950408889634f;
@@ -44,7 +47,9 @@ struct F32Params {
     const int32_t *node_offsets;
     const uint64_t *mask;
     int64_t q_ts, q_hs, o_ts, o_hs, kv_ts, kv_hs;
-    int32_t groups, max_nodes, num_q_heads, num_kv_heads, group, words_per_row, row_tiles;
+    float *part_o, *part_ml;             // as in AttnParams; used if splits > 1
+    int64_t part_rows;                   // total_nodes * num_q_heads
+    int32_t groups, max_nodes, num_q_heads, num_kv_heads, group, words_per_row, row_tiles, splits;
     float scale_log2e;
 };
 
@@ -77,8 +82,9 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(co
 
     // the row tiles of one (sequence, KV head) share K/V: they take consecutive slots of one XCD (ids are dealt
     // round-robin to the 8 XCDs), the (sequence, KV head) groups go round the XCDs
-    const int slot = blockIdx.x >> 3;
-    const int group_id = (slot / p.row_tiles) * 8 + (blockIdx.x & 7);
+    const int slot = blockIdx.x >> 3, per_group = p.row_tiles * p.splits;
+    const int group_id = (slot / per_group) * 8 + (blockIdx.x & 7);
+    const int split = slot % per_group / p.row_tiles;    // the row tiles of a split are neighbours
     if (group_id >= p.groups) return;
     const int b = group_id / p.num_kv_heads, kvh = group_id - b * p.num_kv_heads;
     const int32_t node_base = p.node_offsets[b];
@@ -91,7 +97,8 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(co
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 15, kg = lane >> 4;
-    const int32_t keys = P + n, tiles = (keys + 15) / 16;
+    const int32_t keys = P + n, all_tiles = (keys + 15) / 16, per_split = (all_tiles + p.splits - 1) / p.splits;
+    const int32_t first = split * per_split, tiles = min(all_tiles, first + per_split);     // this split's; may be none
     // K rows come whole (neighbouring lanes, neighbouring 16-byte chunks) into registers, go from there to a part of LDS
     // that is this wavefront's own and are read back as operands: lane l holds row l%16, and loads that follow the
     // operand layout touch a line per lane.  Chunk x of row r sits in slot x ^ r: the 16 rows meet in no bank.
@@ -131,14 +138,26 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(co
         }
     };
 
-    floatx4 qf[KV4], acc[CB];
-    float m = kF32Empty, l = 0.f;
+    // Sums in two levels, or their rounding errors would grow with the length of the context: the running ones take
+    // kFold tiles and are then added to the totals.
+    constexpr int kFold = 8;
+    floatx4 qf[KV4], acc[CB], total[CB];
+    float m = kF32Empty, l = 0.f, l_total = 0.f;
     const int32_t q_row = min(row0 + col, rows_total - 1), q_node = q_row / G;
     const float *qp = p.q + (int64_t(node_base) + q_node) * p.q_ts + (kvh * G + (q_row - q_node * G)) * p.q_hs + 4 * kg;
 #pragma unroll
     for (int t = 0; t < KV4; ++t) qf[t] = *reinterpret_cast<const floatx4 *>(qp + 16 * t);
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) acc[cb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int cb = 0; cb < CB; ++cb) acc[cb] = total[cb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto fold = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            total[cb] += acc[cb];
+            acc[cb] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+        l_total += l;
+        l = 0.f;
+    };
     // the words of the tile's mask rows in LDS: fetched inside the loop they would queue behind the K/V loads in flight
     for (int x = threadIdx.x; x < ROWS * kMaskWords; x += NW * 64) {
         const int row = x / kMaskWords, w = x - row * kMaskWords;
@@ -147,22 +166,26 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(co
         if (w == 0) mask_lds[row][0] = ~uint64_t(0);     // the keys before draft node 0: the end of the prefix
     }
     const float c = p.scale_log2e;
-    load_k(wave);
-    load_v(wave);
+    load_k(first + wave);
+    load_v(first + wave);
     store_k();
     __syncthreads();
 
-    for (int tile = wave; tile < tiles; tile += NW) {
+    int left = kFold;                                    // tiles until the next fold
+    for (int tile = first + wave; tile < tiles; tile += NW) {
         load_k(tile + NW);
         __builtin_amdgcn_sched_barrier(0);
-        floatx4 s = {0.f, 0.f, 0.f, 0.f};
+        floatx4 s = {0.f, 0.f, 0.f, 0.f}, s_odd = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int t = 0; t < KV4; ++t) {
             const floatx4 kf = my_k[col * CHUNKS + ((4 * t + kg) ^ col)];
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[e], qf[t][e], s, 0, 0, 0);
+            for (int e = 0; e < 4; ++e) {
+                floatx4 &sum = t & 1 ? s_odd : s;
+                sum = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[e], qf[t][e], sum, 0, 0, 0);
+            }
         }
+        s += s_odd;
         if (tile * 16 + 16 > P) {                        // uniform: the tile reaches into the draft nodes
             const int32_t pos = tile * 16 + 4 * kg - P;  // draft node of this lane's first key; below 0: prefix
             const int32_t w = (pos + 64) >> 5;           // its 32-bit word of the row in LDS, >= 1
@@ -178,8 +201,12 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(co
         if (__any(m_new > m)) {                  // uniform: some row of the tile has a new maximum
             const float alpha = __builtin_amdgcn_exp2f(m - m_new);
             l *= alpha;
+            l_total *= alpha;
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb) acc[cb] *= alpha;
+            for (int cb = 0; cb < CB; ++cb) {
+                acc[cb] *= alpha;
+                total[cb] *= alpha;
+            }
             m = m_new;
         }
 #pragma unroll
@@ -194,15 +221,20 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(co
                 acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][cb / 4][cb % 4], s[r], acc[cb], 0, 0, 0);
         store_k();
         load_v(tile + NW);
+        if (--left == 0) {                               // uniform
+            fold();
+            left = kFold;
+        }
         __builtin_amdgcn_sched_barrier(0);
     }
+    fold();
 
     __syncthreads();                                     // the K tiles and the outputs below share LDS
 
     // merge of the eight states: (max, sum) first, then every wavefront's output scaled to the common maximum.
     // Register i of channel block 4*x + e is channel 64*x + 16*kg + 4*i + e.
     // Chunks are XOR-swizzled by the row, so that the 16 rows of a store do not meet in a bank.
-    const float sum = sum_across_groups(l);
+    const float sum = sum_across_groups(l_total);
     if (kg == 0) {
         m_lds[wave * ROWS + col] = m;
         l_lds[wave * ROWS + col] = sum;
@@ -219,7 +251,7 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(co
         for (int i = 0; i < 4; ++i) {
             floatx4 y;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) y[e] = acc[4 * x + e][i] * f;
+            for (int e = 0; e < 4; ++e) y[e] = total[4 * x + e][i] * f;
             out[(16 * x + 4 * kg + i) ^ col] = y;
         }
     __syncthreads();
@@ -236,9 +268,15 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(co
             sum += l_lds[w * ROWS + row] * __builtin_amdgcn_exp2f(m_lds[w * ROWS + row] - top);
             y += reinterpret_cast<const floatx4 *>(o_lds + (w * ROWS + row) * D)[chunk ^ row];
         }
-        y *= sum > 0.f ? 1.f / sum : 0.f;
         const int32_t node = (row0 + row) / G, head = kvh * G + (row0 + row - node * G);
         const int64_t t = int64_t(node_base) + node;
+        if (p.splits > 1) {
+            const int64_t at = split * p.part_rows + t * p.num_q_heads + head;
+            *reinterpret_cast<floatx4 *>(p.part_o + at * D + 4 * chunk) = y;
+            if (chunk == 0) *reinterpret_cast<floatx2 *>(p.part_ml + at * 2) = floatx2{top, sum};
+            continue;
+        }
+        y *= sum > 0.f ? 1.f / sum : 0.f;
         *reinterpret_cast<floatx4 *>(p.o + t * p.o_ts + head * p.o_hs + 4 * chunk) = y;
         if (p.lse && chunk == 0)
             p.lse[t * p.num_q_heads + head] = sum > 0.f ? (top + __log2f(sum)) * 0.6931471805599453f : -__builtin_inff();
@@ -247,7 +285,36 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(co
 
 }  // namespace
 
-hipError_t launch_attention_f32(const gsd_attn_desc &d, hipStream_t stream) {
+// Splits of the keys that a small timing model likes best (microseconds, 256 CUs): 4.5 outside the loop and 1.45 (head_dim
+// 64: 0.75) per turn of the four wavefronts, in rounds of one work-group per CU, and for splitting the merge kernel: 2.5,
+// and per split 0.4 and 0.32 per 1024 rows.  Never fewer than two turns per split.  Measured (us, unsplit -> chosen): 32 heads
+// of 64 rows over 1088 keys 31.4 -> 23.5 (3 splits 27.1, 4 24.0, 6 30.7); 8 of 32 over 4128 97 -> 20.6; 4 of 16 over 8016
+// 179 -> 25.5; 16 of 64 x 4 sequences, one round unsplit, stays (2 splits 35.4 against 31.4).
+int attention_f32_splits(const gsd_attn_desc &d) {
+    const int rows = d.max_nodes * (d.num_q_heads / d.num_kv_heads);
+    const int turns = int((int64_t(d.max_prefix) + d.max_nodes + 63) / 64);
+    if (d.num_splits > 0) {
+        const int forced = d.num_splits < turns ? d.num_splits : turns;
+        return forced < 64 ? forced : 64;
+    }
+    const int cap = turns / 2 < 1 ? 1 : turns / 2 < 64 ? turns / 2 : 64;
+    const float tiles = float(d.batch) * float(d.num_kv_heads) * float((rows + 15) / 16);
+    const float merge_us = 0.32f / 1024.0f * float(d.total_nodes) * float(d.num_q_heads) * (d.head_dim == 128 ? 1.0f : 0.5f);
+    int best = 1;
+    float best_us = -1.0f;
+    for (int s = 1; s <= cap; ++s) {
+        float us = ceilf(tiles * s / 256.0f) * (4.5f + float((turns + s - 1) / s) * (d.head_dim == 128 ? 1.45f : 0.75f));
+        if (s > 1) us += 2.5f + (0.4f + merge_us) * s;
+        if (best_us < 0.0f || us < best_us) {
+            best_us = us;
+            best = s;
+        }
+        if (tiles * s >= 512.0f) break;
+    }
+    return best;
+}
+
+hipError_t launch_attention_f32(const gsd_attn_desc &d, int splits, hipStream_t stream) {
     F32Params p;
     p.q = (const float *)d.q; p.o = (float *)d.o; p.lse = d.lse; p.k = (const float *)d.k; p.v = (const float *)d.v;
     p.kv_offsets = d.kv_offsets; p.prefix_lens = d.prefix_lens; p.node_offsets = d.node_offsets; p.mask = d.mask;
@@ -257,10 +324,20 @@ hipError_t launch_attention_f32(const gsd_attn_desc &d, hipStream_t stream) {
     p.num_kv_heads = d.num_kv_heads; p.group = d.num_q_heads / d.num_kv_heads; p.words_per_row = d.words_per_row;
     p.scale_log2e = d.softmax_scale * kF32Log2e;
     p.row_tiles = (d.max_nodes * p.group + 15) / 16;
-    const dim3 grid((unsigned)((p.groups + 7) / 8 * 8 * p.row_tiles)), block(kF32Waves * 64);
+    p.splits = splits;
+    p.part_rows = int64_t(d.total_nodes) * d.num_q_heads;
+    p.part_o = splits > 1 ? (float *)d.workspace : nullptr;
+    p.part_ml = splits > 1 ? p.part_o + splits * p.part_rows * d.head_dim : nullptr;
+    const dim3 grid((unsigned)((p.groups + 7) / 8 * 8 * p.row_tiles * splits)), block(kF32Waves * 64);
     if (d.head_dim == 64) hipLaunchKernelGGL(dag_attention_f32_kernel<64>, grid, block, 0, stream, p);
     else hipLaunchKernelGGL(dag_attention_f32_kernel<128>, grid, block, 0, stream, p);
-    return hipGetLastError();
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess || splits <= 1) return err;
+    AttnParams c = {};                                   // what the merge kernel reads
+    c.o = (__bf16 *)d.o; c.lse = d.lse; c.o_ts = d.o_token_stride; c.o_hs = d.o_head_stride;
+    c.part_o = p.part_o; c.part_ml = p.part_ml; c.splits = splits;
+    c.total_nodes = d.total_nodes; c.num_q_heads = d.num_q_heads;
+    return launch_attention_combine(c, d.head_dim, GSD_F32, stream);
 }
 
 }  // namespace gsd

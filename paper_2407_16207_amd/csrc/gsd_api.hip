@@ -83,13 +83,12 @@ int gsd_build_mask(int32_t batch, int32_t max_nodes, int32_t words_per_row, cons
 
 int gsd_dag_attention_splits(const gsd_attn_desc *desc) {
     if (check_attn_desc(desc) != GSD_OK) return -1;
-    return desc->dtype == GSD_BF16 ? gsd::attention_bf16_plan(*desc).splits : 1;
+    return desc->dtype == GSD_BF16 ? gsd::attention_bf16_plan(*desc).splits : gsd::attention_f32_splits(*desc);
 }
 
 size_t gsd_dag_attention_workspace(const gsd_attn_desc *desc) {
     if (check_attn_desc(desc) != GSD_OK) return (size_t)-1;
-    if (desc->dtype != GSD_BF16) return 0;
-    return gsd::attention_bf16_workspace(*desc, gsd::attention_bf16_plan(*desc).splits);
+    return gsd::attention_workspace(*desc, gsd_dag_attention_splits(desc));
 }
 
 }  // extern "C"
@@ -134,10 +133,12 @@ int gsd_dag_attention(const gsd_attn_desc *desc, void *hip_stream) {
     hipStream_t stream = (hipStream_t)hip_stream;
     hipError_t err;
     if (d.dtype == GSD_F32) {
-        err = gsd::launch_attention_f32(d, stream);
+        const int splits = gsd::attention_f32_splits(d);
+        const bool room = d.workspace && d.workspace_bytes >= gsd::attention_workspace(d, splits) && aligned16(d.workspace);
+        err = gsd::launch_attention_f32(d, room ? splits : 1, stream);
     } else {
         const gsd::AttnPlan plan = gsd::attention_bf16_plan(d);
-        const size_t need = gsd::attention_bf16_workspace(d, plan.splits);
+        const size_t need = gsd::attention_workspace(d, plan.splits);
         if (need > 0 && (!d.workspace || d.workspace_bytes < need))
             return fail(GSD_ERR_WORKSPACE, "workspace of %zu bytes needed for %d KV splits, %zu given", need, plan.splits,
                         d.workspace ? d.workspace_bytes : size_t(0));
@@ -156,10 +157,10 @@ int gsd_dag_attention_static(const gsd_attn_desc *desc, void *hip_stream) {
     hipStream_t stream = (hipStream_t)hip_stream;
     hipError_t err;
     if (d.dtype == GSD_F32) {
-        err = gsd::launch_attention_f32(d, stream);
+        err = gsd::launch_attention_f32(d, 1, stream);
     } else {
         const gsd::AttnPlan plan = gsd::attention_bf16_plan(d);
-        const size_t need = gsd::attention_bf16_workspace(d, plan.splits);
+        const size_t need = gsd::attention_workspace(d, plan.splits);
         if (need > GSD_STATIC_SCRATCH_BYTES)
             return fail(GSD_ERR_WORKSPACE, "%zu bytes of split partials (%d KV splits) exceed the static scratch of %zu",
                         need, plan.splits, size_t(GSD_STATIC_SCRATCH_BYTES));

@@ -182,6 +182,28 @@ def test_attention_fp32_tile_edges(gpu, ref, D, hq, hkv):
     check_attention(gpu, ref, custom_workload(rng, [1, 15, 16, 17, 33, 2], [0, 1, 47, 48, 31, 512], hq, hkv, D, "f32"))
 
 
+@pytest.mark.parametrize("splits", [0, 2, 3, 64])
+@pytest.mark.parametrize("D", [64, 128])
+def test_attention_fp32_splits(gpu, ref, D, splits):
+    """Splits that end inside the prefix and inside the draft nodes, splits without a key; and a workspace that is missing
+    or too small leaves the call unsplit, bit for bit."""
+    import paper_2407_16207_amd as gsd
+    rng = np.random.default_rng(1100 + D + splits)
+    w = custom_workload(rng, [1, 15, 16, 17, 33, 2], [0, 1, 47, 48, 531, 5], 6, 2, D, "f32")
+    d = gpu.DeviceWorkload(w)
+    out = check_attention(gpu, ref, w, d=d, num_splits=splits)
+    mask = d.build_mask()
+    alone = d.attention(mask, num_splits=1)
+    small = torch.empty(16, dtype=torch.uint8, device="cuda")
+    kept = d.attention(mask, num_splits=splits, workspace=small)
+    desc = gsd.make_attn_desc(d.q, d.k, d.v, d.kv_offsets, d.prefix_lens, d.node_offsets, mask, d.max_nodes, d.max_prefix,
+                              w.softmax_scale, out=torch.empty_like(d.q), num_splits=splits)
+    assert (gsd.gsd_dag_attention_workspace(desc) > 0) == (gsd.gsd_dag_attention_splits(desc) > 1)
+    torch.cuda.synchronize()
+    assert torch.equal(kept, alone)
+    assert (out - alone).abs().max().item() < 1e-5
+
+
 @pytest.mark.parametrize("waves", [4, 8, 64])
 @pytest.mark.parametrize("splits", [1, 2, 3, 7])
 @pytest.mark.parametrize("D", [128, 64])
