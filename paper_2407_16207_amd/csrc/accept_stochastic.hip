@@ -296,154 +296,209 @@ __device__ __forceinline__ int accept_phase(AcceptLds &s, const gsd_stochastic_d
 
 constexpr int kResampleThreads = kStochThreads;
 
+// The draw for any vocabulary, type and alignment.  A thread's slice is contiguous in memory, so lanes that fetched their
+// own slices one element after the other would touch 64 lines with every load; instead neighbouring lanes fetch
+// neighbouring elements, all slices a segment of kSegBytes at a time, into LDS, where a slice starts an odd number of
+// words after the one before it (no bank conflicts when every lane then reads its own).  The slice that holds the target
+// is weighed by the whole work-group and walked by one thread.  Bound by the chain of these phases on one CU.
+// 8 sequences of 128 nodes, whole call: 32003 bf16 tokens 66.4 -> 43.7 us; 4 sequences, 64000 tokens: 108 -> 61.7;
+// 2 sequences, 64001 fp32 tokens: 98.5 -> 62.7, against a kernel that fetched slices lane by lane.
+template <bool BF16>
 __device__ __forceinline__ void resample_phase(const gsd_stochastic_desc &d, int end, bool child) {
-    __shared__ float red_m[kResampleThreads / 64], red_s[kResampleThreads / 64];
-    __shared__ float part[kResampleThreads];
-    __shared__ float stat[4];
-    __shared__ int pick_s;
+    constexpr int ELT = BF16 ? 2 : 4;
+    constexpr int kSegBytes = 64, kSeg = kSegBytes / ELT;         // elements of a slice that are in LDS at a time
+    constexpr int kStride = kSegBytes / 4 + 1;                    // words from one slice's segment to the next
+    constexpr int kWaves = kResampleThreads / 64;
+    __shared__ uint32_t seg_p[kResampleThreads * kStride], seg_q[kResampleThreads * kStride];
+    __shared__ float part[2][kResampleThreads];
+    __shared__ float red_m[kWaves], red_s[kWaves], stat[2];
+    __shared__ int owner_s, pick_s;
 
+    const int t = threadIdx.x;
     const int b = blockIdx.x;
     const int64_t base = d.node_offsets[b];
     const int V = d.vocab;
-    if (threadIdx.x == 0) pick_s = -1;
-    const bool use_residual = __syncthreads_or(child) != 0;      // does the end node (or the root) have children ?
-
-    const void *p_row = end < 0 ? d.root_logits : d.logits;
-    const void *q_row = end < 0 ? d.root_draft_logits : d.draft_logits;
+    if (t == 0) {
+        owner_s = 0x7fffffff;
+        pick_s = -1;
+    }
     const int64_t row_off = (end < 0 ? int64_t(b) : base + end) * d.row_stride;
+    const char *p_row = reinterpret_cast<const char *>(end < 0 ? d.root_logits : d.logits) + row_off * ELT;
+    const char *q_row = reinterpret_cast<const char *>(end < 0 ? d.root_draft_logits : d.draft_logits) + row_off * ELT;
     const float p_max = end < 0 ? d.row_max[d.total_nodes + b] : d.row_max[base + end];
     const float p_sum = end < 0 ? d.row_sumexp[d.total_nodes + b] : d.row_sumexp[base + end];
+    auto raw = [&](const char *row, int x) -> uint32_t {
+        if (BF16) return reinterpret_cast<const uint16_t *>(row)[x];
+        return reinterpret_cast<const uint32_t *>(row)[x];
+    };
+    auto value = [&](uint32_t v) -> float { return __uint_as_float(BF16 ? v << 16 : v); };
 
     // the draft row's own (max, sum)
     float m = -__builtin_inff(), s = 0.f;
-    for (int x = threadIdx.x; x < V; x += kResampleThreads) merge_state(m, s, load_logit(q_row, row_off + x, d.dtype), 1.f);
+    constexpr int kBatch = 16;
+    for (int x0 = t; x0 < V; x0 += kResampleThreads * kBatch) {
+        uint32_t v[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            if (x0 - t + u * kResampleThreads >= V) break;        // uniform
+            v[u] = raw(q_row, min(x0 + u * kResampleThreads, V - 1));
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            if (x0 + u * kResampleThreads >= V) break;
+            const float x = value(v[u]);
+            if (fabsf(x) < __builtin_inff()) {                    // merge_state(m, s, x, 1) with the one exponential that
+                const float e = __expf(x > m ? m - x : x - m);    // is not exp(0)
+                s = x > m ? fmaf(s, e, 1.f) : s + e;
+                m = fmaxf(m, x);
+            } else {
+                merge_state(m, s, x, 1.f);
+            }
+        }
+    }
     for (int off = 32; off > 0; off >>= 1) {
         const float m2 = __shfl_xor(m, off, 64), s2 = __shfl_xor(s, off, 64);
         merge_state(m, s, m2, s2);
     }
-    if ((threadIdx.x & 63) == 0) {
-        red_m[threadIdx.x >> 6] = m;
-        red_s[threadIdx.x >> 6] = s;
+    if ((t & 63) == 0) {
+        red_m[t >> 6] = m;
+        red_s[t >> 6] = s;
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
+    const bool use_residual = __syncthreads_or(child) != 0;       // does the end node (or the root) have children ?
+    if (t == 0) {
         float M = red_m[0], S = red_s[0];
-        for (int w = 1; w < kResampleThreads / 64; ++w) merge_state(M, S, red_m[w], red_s[w]);
+        for (int w = 1; w < kWaves; ++w) merge_state(M, S, red_m[w], red_s[w]);
         stat[0] = M;
         stat[1] = S;
     }
     __syncthreads();
     const float q_max = stat[0], q_sum = stat[1];
-
-    // contiguous slice of the vocabulary per thread
-    const int per = (V + kResampleThreads - 1) / kResampleThreads;
-    const int x0 = threadIdx.x * per, x1 = min(V, x0 + per);
-    auto weight = [&](int x, bool residual) -> float {
-        const float p = __expf(load_logit(p_row, row_off + x, d.dtype) - p_max) / p_sum;
+    auto weight = [&](uint32_t vp, uint32_t vq, bool residual) -> float {
+        const float p = __expf(value(vp) - p_max) / p_sum;
         if (!residual) return p;
-        const float q = __expf(load_logit(q_row, row_off + x, d.dtype) - q_max) / q_sum;
+        const float q = __expf(value(vq) - q_max) / q_sum;
         return fmaxf(p - q, 0.f);
     };
-    // The weights of this thread's slice, in ascending token order, handed to f(x, w) until f returns true.  A slice
-    // is contiguous in memory, so when it starts on a 16-byte boundary it is fetched 16 bytes at a time (one load
-    // per 8 bf16 / 4 fp32 values instead of one per value: the lanes of a wave are a slice apart, so every load
-    // instruction touches 64 cache lines whatever its width); same values, same order either way.
-    const int elt = d.dtype == GSD_BF16 ? 2 : 4;
-    const int per_vec = 16 / elt;
-    const bool vec_ok = (per * elt) % 16 == 0 &&
-                        (reinterpret_cast<uintptr_t>(p_row) + uintptr_t(row_off) * elt) % 16 == 0 &&
-                        (reinterpret_cast<uintptr_t>(q_row) + uintptr_t(row_off) * elt) % 16 == 0;
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    auto unpack = [&](const u32x4 v, float (&out)[8]) {
-        if (d.dtype == GSD_BF16) {
+
+    const int per = (V + kResampleThreads - 1) / kResampleThreads;
+    const int x0 = t * per;
+    // weight of this thread's slice, in ascending token order
+    auto slice_sum = [&](bool residual) -> float {
+        float local = 0.f;
+        for (int g0 = 0; g0 < per; g0 += kSeg) {
+            const int width = min(kSeg, per - g0);                // elements per slice in this turn
+            int lg = 0;                                           // 2^lg >= width lanes fetch a slice's segment
+            while ((1 << lg) < width) ++lg;
+            const int e = t & ((1 << lg) - 1), first = t >> lg, step = kResampleThreads >> lg, rounds = 1 << lg;
+            __syncthreads();                                      // the segment before this one has been read
+            constexpr int kFetch = 8;
+            for (int r0 = 0; r0 < rounds; r0 += kFetch) {
+                uint32_t vp[kFetch], vq[kFetch];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                out[2 * j] = __uint_as_float(v[j] << 16);
-                out[2 * j + 1] = __uint_as_float(v[j] & 0xffff0000u);
+                for (int u = 0; u < kFetch; ++u) {
+                    const int slice = min(first + (r0 + u) * step, kResampleThreads - 1);
+                    const int x = min(slice * per + g0 + e, V - 1);
+                    vp[u] = raw(p_row, x);
+                    vq[u] = raw(q_row, x);
+                }
+#pragma unroll
+                for (int u = 0; u < kFetch; ++u) {
+                    const int slice = first + (r0 + u) * step;
+                    if (slice < kResampleThreads && e < width) {
+                        if (BF16) {
+                            reinterpret_cast<uint16_t *>(seg_p)[slice * 2 * kStride + e] = uint16_t(vp[u]);
+                            reinterpret_cast<uint16_t *>(seg_q)[slice * 2 * kStride + e] = uint16_t(vq[u]);
+                        } else {
+                            seg_p[slice * kStride + e] = vp[u];
+                            seg_q[slice * kStride + e] = vq[u];
+                        }
+                    }
+                }
             }
-        } else {
+            __syncthreads();
+            constexpr int kPerWord = 4 / ELT;
+#pragma unroll 4
+            for (int w = 0; w < kSegBytes / 4; ++w) {
+                if (w * kPerWord >= width) break;                 // uniform
+                const uint32_t wp = seg_p[t * kStride + w], wq = seg_q[t * kStride + w];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) out[j] = __uint_as_float(v[j]);
-        }
-    };
-    auto for_each_weight = [&](bool residual, auto &&f) {
-        int x = x0;
-        if (vec_ok) {
-            for (; x + per_vec <= x1; x += per_vec) {
-                float lp[8], lq[8];
-                unpack(*reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(p_row) + (row_off + x) * elt), lp);
-                if (residual)
-                    unpack(*reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(q_row) + (row_off + x) * elt), lq);
-                for (int j = 0; j < per_vec; ++j) {
-                    const float pp = __expf(lp[j] - p_max) / p_sum;
-                    const float w = residual ? fmaxf(pp - __expf(lq[j] - q_max) / q_sum, 0.f) : pp;
-                    if (f(x + j, w)) return;
+                for (int h = 0; h < kPerWord; ++h) {
+                    const int i = g0 + w * kPerWord + h;
+                    const uint32_t vp = BF16 ? (h ? wp >> 16 : wp & 0xffffu) : wp;
+                    const uint32_t vq = BF16 ? (h ? wq >> 16 : wq & 0xffffu) : wq;
+                    if (i < per && x0 + i < V) local += weight(vp, vq, residual);
                 }
             }
         }
-        for (; x < x1; ++x)
-            if (f(x, weight(x, residual))) return;
+        return local;
     };
-    // total weight (thread-ordered scan in LDS, fixed order), falling back to p when the residual is empty
-    auto scan = [&](bool residual) -> float {
-        float local = 0.f;
-        for_each_weight(residual, [&](int, float w) {
-            local += w;
-            return false;
-        });
+    // inclusive scan of the slices' weights, one fixed order; the buffers take turns, so a step needs one barrier
+    float before = 0.f, upto = 0.f, total = 0.f;
+    auto scan = [&](bool residual) {
+        upto = slice_sum(residual);
+        int at = 0;
+        part[at][t] = upto;
         __syncthreads();
-        part[threadIdx.x] = local;
-        __syncthreads();
-        for (int dd = 1; dd < kResampleThreads; dd <<= 1) {      // inclusive scan
-            const float add = int(threadIdx.x) >= dd ? part[threadIdx.x - dd] : 0.f;
-            __syncthreads();
-            part[threadIdx.x] += add;
+        for (int dd = 1; dd < kResampleThreads; dd <<= 1) {
+            if (t >= dd) upto += part[at][t - dd];
+            at ^= 1;
+            part[at][t] = upto;
             __syncthreads();
         }
-        return part[kResampleThreads - 1];
+        before = t > 0 ? part[at][t - 1] : 0.f;
+        total = part[at][kResampleThreads - 1];
     };
     bool residual = use_residual;
-    float total = scan(residual);
-    if (residual && !(total > 0.f)) {
+    scan(residual);
+    if (residual && !(total > 0.f)) {                             // empty residual: draw from p
+        __syncthreads();
         residual = false;
-        total = scan(false);
+        scan(false);
     }
     const float target = d.resample_u[b] * total;
-    const float before = threadIdx.x > 0 ? part[threadIdx.x - 1] : 0.f;
-    const float upto = part[threadIdx.x];
-    // the owner of the target walks its slice; the smallest token whose cumulative weight exceeds the target
-    if (before <= target && target < upto) {
+    // the owner of the target: the smallest token whose cumulative weight exceeds the target is in its slice
+    const bool mine = before <= target && target < upto;
+    if (mine) atomicMin(&owner_s, t);
+    __syncthreads();
+    const int owner = owner_s;
+    if (owner < kResampleThreads) {                               // uniform
         float run = before;
-        int pick = -1;
-        for_each_weight(residual, [&](int x, float w) {
-            run += w;
-            if (run > target) {
-                pick = x;
-                return true;
-            }
-            return false;
-        });
-        if (pick < 0) {                                     // rounding inside the slice: its last token with weight
-            for (int x = x1 - 1; x >= x0; --x)
-                if (weight(x, residual) > 0.f) {
-                    pick = x;
-                    break;
+        int pick = -1, last = -1;
+        float *weights = reinterpret_cast<float *>(seg_p);
+        for (int c0 = 0; c0 < per; c0 += kResampleThreads) {
+            const int i = c0 + t, x = owner * per + i;
+            const bool in = i < per && x < V;
+            if (in) weights[t] = weight(raw(p_row, x), raw(q_row, x), residual);
+            __syncthreads();
+            if (t == owner) {
+                const int count = min(min(per - c0, kResampleThreads), V - (x0 + c0));
+#pragma unroll 8
+                for (int k = 0; k < count; ++k) {
+                    const float w = weights[k];
+                    run += w;
+                    if (w > 0.f) last = x0 + c0 + k;
+                    if (pick < 0 && run > target) pick = x0 + c0 + k;
                 }
-        }
-        pick_s = pick;
-    }
-    __syncthreads();
-    if (pick_s < 0 && threadIdx.x == 0) {                    // target == total by rounding: the last token with weight
-        int pick = 0;
-        for (int x = V - 1; x >= 0; --x)
-            if (weight(x, residual) > 0.f) {
-                pick = x;
-                break;
             }
-        pick_s = pick;
+            __syncthreads();
+        }
+        if (t == owner) pick_s = pick >= 0 ? pick : last;         // rounding inside the slice: its last token with weight
     }
     __syncthreads();
-    if (threadIdx.x == 0) d.bonus_token[b] = pick_s;
+    if (pick_s < 0) {                                             // target == total by rounding: the last token with weight
+        int last = -1;
+        for (int x = t; x < V; x += kResampleThreads)
+            if (weight(raw(p_row, x), raw(q_row, x), residual) > 0.f) last = x;
+        for (int off = 32; off > 0; off >>= 1) last = max(last, __shfl_xor(last, off, 64));
+        if ((t & 63) == 0) red_m[t >> 6] = __int_as_float(last);
+        __syncthreads();
+        if (t == 0) {
+            int best = 0;
+            for (int w = 0; w < kWaves; ++w) best = max(best, __float_as_int(red_m[w]));
+            pick_s = best;
+        }
+    }
+    if (t == 0) d.bonus_token[b] = pick_s;
 }
 
 // The same draw for rows whose per-thread slice fits registers (the launcher checks: the slice is a whole number of
@@ -603,15 +658,17 @@ __device__ __forceinline__ void resample_held_phase(const gsd_stochastic_desc &d
     if (t == 0) d.bonus_token[b] = pick_s;
 }
 
-enum class Resample { general, held_f32, held_bf16 };
+enum class Resample { general_f32, general_bf16, held_f32, held_bf16 };
 
 template <Resample KIND>
 __global__ __launch_bounds__(kStochThreads) void accept_and_resample_kernel(const gsd_stochastic_desc d) {
     __shared__ AcceptLds s;
     bool child = false;
     const int end = __builtin_amdgcn_readfirstlane(accept_phase(s, d, child));
-    if constexpr (KIND == Resample::general) resample_phase(d, end, child);
-    else resample_held_phase<KIND == Resample::held_bf16>(d, end, child);
+    if constexpr (KIND == Resample::general_f32 || KIND == Resample::general_bf16)
+        resample_phase<KIND == Resample::general_bf16>(d, end, child);
+    else
+        resample_held_phase<KIND == Resample::held_bf16>(d, end, child);
 }
 
 hipError_t launch_accept_stochastic(const gsd_stochastic_desc &d, hipStream_t stream) {
@@ -631,8 +688,10 @@ hipError_t launch_accept_stochastic(const gsd_stochastic_desc &d, hipStream_t st
         hipLaunchKernelGGL(accept_and_resample_kernel<Resample::held_bf16>, grid, block, 0, stream, d);
     else if (held)
         hipLaunchKernelGGL(accept_and_resample_kernel<Resample::held_f32>, grid, block, 0, stream, d);
+    else if (d.dtype == GSD_BF16)
+        hipLaunchKernelGGL(accept_and_resample_kernel<Resample::general_bf16>, grid, block, 0, stream, d);
     else
-        hipLaunchKernelGGL(accept_and_resample_kernel<Resample::general>, grid, block, 0, stream, d);
+        hipLaunchKernelGGL(accept_and_resample_kernel<Resample::general_f32>, grid, block, 0, stream, d);
     return hipGetLastError();
 }
 

@@ -288,6 +288,35 @@ def test_softmax_stats_and_stochastic_acceptance(gpu, dtype, vocab, sizes):
     assert exact >= len(cdfs) - 1
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("vocab", [1, 2, 1023, 1024, 1025, 2049, 16385, 32767, 33001, 66001])
+def test_stochastic_draw_any_vocabulary(gpu, dtype, vocab):
+    """Slices of 1 to 65 tokens, at and around the segments that pass through LDS; rows that start on odd elements; draws from
+    p (no child below the path's end) and from the residual (empty for the vocabulary of one token)."""
+    import paper_2407_16207_amd as gsd
+    rng = np.random.default_rng(vocab)
+    node_offsets, poff, pidx = [np.array(x, dtype=np.int32) for x in ([0, 2, 3, 5], [0, 1, 2, 3, 4, 5], [-1, 0, -1, -1, 0])]
+    total, batch = 5, 3
+    lp = torch.from_numpy(rng.standard_normal((total + batch, vocab + 1)).astype(np.float32) * 2)
+    lq = torch.from_numpy(rng.standard_normal((total + batch, vocab + 1)).astype(np.float32) * 2)
+    lp, lq = (x.to(torch.bfloat16 if dtype == "bf16" else torch.float32) for x in (lp, lq))
+    p, q = (torch.softmax(x[:, 1:].double(), 1).numpy() for x in (lp, lq))
+    accept_u = np.array([0, 0, 0, 1, 1], dtype=np.float32)        # two whole paths, one that ends at once
+    resample_u = np.array([0.0, 0.37, 0.9999], dtype=np.float32)
+    draft_prob = np.array([0.5, 0.5, 0.5, 1e6, 1e6], dtype=np.float32)
+    dp, dq = lp.cuda()[:, 1:], lq.cuda()[:, 1:]
+    ln, path, end, bonus, _, _ = gsd.gsd_accept_stochastic(
+        gpu.to_dev(node_offsets), gpu.to_dev(poff), gpu.to_dev(pidx), gpu.to_dev(np.zeros(total, dtype=np.int32)), dp[:total],
+        dp[total:], dq[:total], dq[total:], gpu.to_dev(draft_prob), gpu.to_dev(accept_u), gpu.to_dev(resample_u), 2)
+    torch.cuda.synchronize()
+    assert ln.cpu().tolist() == [2, 1, 0] and end.cpu().tolist() == [1, 0, -1]
+    # fp32 sums of terms <= 1 that add up to 1, at most 65 + 10 additions deep, and normalisers within 2e-6
+    for b, row, residual in ((0, 1, False), (1, 2, False), (2, total + 2, True)):
+        cdf = np.cumsum(np.maximum(p[row] - q[row], 0) if residual else p[row])
+        x, target = int(bonus[b]), float(resample_u[b]) * cdf[-1]
+        assert p[row][x] > 0 and (cdf[x - 1] if x else 0.0) - 2e-5 <= target <= cdf[x] + 2e-5
+
+
 def test_stochastic_acceptance_many_parents(gpu):
     """Nodes with more parents than the kernel keeps in registers (4): accepted paths stay exact."""
     import paper_2407_16207_amd as gsd
