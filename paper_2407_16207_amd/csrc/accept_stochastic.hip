@@ -73,10 +73,13 @@ __global__ __launch_bounds__(THREADS) void softmax_stats_kernel(int32_t vocab, c
         if (BF16) return __uint_as_float(uint32_t(reinterpret_cast<const uint16_t *>(row_ptr)[i]) << 16);
         return reinterpret_cast<const float *>(row_ptr)[i];
     };
-    if (int(threadIdx.x) < head) {
-        const float x = scalar_at(threadIdx.x);
-        add_batch(&x, 1);
-    }
+    // the elements before the first and behind the last 16-byte boundary are fetched ahead of the body and looked at after
+    // it was issued: waited for at once they would cost a row two more round trips to memory
+    const bool has_head = int(threadIdx.x) < head, has_tail = tail_start + int(threadIdx.x) < vocab;
+    float head_x = 0.f, tail_x = 0.f;
+    if (has_head) head_x = scalar_at(threadIdx.x);
+    if (has_tail) tail_x = scalar_at(tail_start + threadIdx.x);
+    bool head_due = has_head;
     const u32x4 *vec = reinterpret_cast<const u32x4 *>(row_ptr + size_t(head) * ELT);
     // kBatch loads are issued before the first of them is looked at (one load per lane in flight streams at the pace of
     // memory latency, not bandwidth); a slot past the end of the row reads the last chunk again and is ignored
@@ -85,6 +88,8 @@ __global__ __launch_bounds__(THREADS) void softmax_stats_kernel(int32_t vocab, c
         u32x4 w[kBatch];
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) w[u] = __builtin_nontemporal_load(vec + min(c0 + u * THREADS, nvec - 1));
+        if (head_due) add_batch(&head_x, 1);
+        head_due = false;
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
             if (c0 + u * THREADS >= nvec) break;
@@ -102,17 +107,14 @@ __global__ __launch_bounds__(THREADS) void softmax_stats_kernel(int32_t vocab, c
             add_batch(x, PER_VEC);
         }
     }
-    {
-        const int i = tail_start + threadIdx.x;
-        if (i < vocab) {
-            const float x = scalar_at(i);
-            add_batch(&x, 1);
-        }
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        const float m2 = __shfl_xor(m, off, 64), s2 = __shfl_xor(s, off, 64);
-        merge_state(m, s, m2, s2);
-    }
+    if (head_due) add_batch(&head_x, 1);                 // a row too short to give this lane a chunk
+    if (has_tail) add_batch(&tail_x, 1);
+    merge_state(m, s, lane_xor<32>(m), lane_xor<32>(s));
+    merge_state(m, s, lane_xor<16>(m), lane_xor<16>(s));
+    merge_state(m, s, lane_xor<8>(m), lane_xor<8>(s));
+    merge_state(m, s, lane_xor<4>(m), lane_xor<4>(s));
+    merge_state(m, s, lane_xor<2>(m), lane_xor<2>(s));
+    merge_state(m, s, lane_xor<1>(m), lane_xor<1>(s));
     __shared__ float sm[THREADS / 64], ss[THREADS / 64];
     if ((threadIdx.x & 63) == 0) {
         sm[threadIdx.x >> 6] = m;

@@ -7,6 +7,37 @@
 
 namespace gsd {
 
+// The value of lane (l ^ MASK), without the LDS round trip of a shuffle.
+template <int MASK>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x) {
+    static_assert(MASK == 1 || MASK == 2 || MASK == 4 || MASK == 8 || MASK == 16 || MASK == 32, "one bit of the lane id");
+    constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kQuadXor3 = 0x1B, kRowRor8 = 0x128, kHalfMirror = 0x141;
+    if constexpr (MASK == 1) return __builtin_amdgcn_update_dpp(x, x, kQuadXor1, 0xf, 0xf, false);
+    if constexpr (MASK == 2) return __builtin_amdgcn_update_dpp(x, x, kQuadXor2, 0xf, 0xf, false);
+    if constexpr (MASK == 4) {                           // l ^ 7 (mirror of 8), then ^ 3 (mirror of 4)
+        const uint32_t y = __builtin_amdgcn_update_dpp(x, x, kHalfMirror, 0xf, 0xf, false);
+        return __builtin_amdgcn_update_dpp(y, y, kQuadXor3, 0xf, 0xf, false);
+    }
+    if constexpr (MASK == 8) return __builtin_amdgcn_update_dpp(x, x, kRowRor8, 0xf, 0xf, false);
+    // both results of a swap of x with itself: the other half's value in the first for the upper half, in the second for
+    // the lower one
+    const bool upper = __lane_id() & MASK;
+    if constexpr (MASK == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return upper ? r[0] : r[1];
+    }
+    if constexpr (MASK == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return upper ? r[0] : r[1];
+    }
+}
+template <int MASK> __device__ __forceinline__ float lane_xor(float x) {
+    return __uint_as_float(lane_xor<MASK>(__float_as_uint(x)));
+}
+template <int MASK> __device__ __forceinline__ int32_t lane_xor(int32_t x) {
+    return int32_t(lane_xor<MASK>(uint32_t(x)));
+}
+
 // Host-side launchers; every argument has been validated by the API layer.
 hipError_t launch_build_mask(int32_t batch, int32_t max_nodes, int32_t words_per_row, const int32_t *node_offsets,
                              const int32_t *parent_offsets, const int32_t *parent_idx, uint64_t *mask,

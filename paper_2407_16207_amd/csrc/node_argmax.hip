@@ -74,11 +74,17 @@ __global__ __launch_bounds__(THREADS) void node_argmax_kernel(int32_t vocab, con
         sm_s = sm_s * __expf(sm_m - mm) + add;
         sm_m = mm;
     };
-    if (int(threadIdx.x) < head) {
-        const float x = scalar_at(threadIdx.x);
-        consider(best, x, threadIdx.x);
+    // The elements before the first and behind the last 16-byte boundary, fetched ahead of the body and looked at after it
+    // was issued: waited for at once they would cost a row two more round trips to memory.
+    const bool has_head = int(threadIdx.x) < head, has_tail = tail_start + int(threadIdx.x) < vocab;
+    float head_x = 0.f, tail_x = 0.f;
+    if (has_head) head_x = scalar_at(threadIdx.x);
+    if (has_tail) tail_x = scalar_at(tail_start + threadIdx.x);
+    bool head_due = has_head;
+    auto take = [&](float x, int32_t i) {
+        consider(best, x, i);
         if (STATS) add_batch(&x, 1, fmaxf(x, -__builtin_inff()));
-    }
+    };
 
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     const u32x4 *vec = reinterpret_cast<const u32x4 *>(row_ptr + size_t(head) * ELT);
@@ -112,6 +118,8 @@ __global__ __launch_bounds__(THREADS) void node_argmax_kernel(int32_t vocab, con
             const int c = min(c0 + u * THREADS, nvec - 1);
             w[u] = NT ? __builtin_nontemporal_load(vec + c) : vec[c];
         }
+        if (head_due) take(head_x, threadIdx.x);
+        head_due = false;
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
             const int c = c0 + u * THREADS;
@@ -137,28 +145,22 @@ __global__ __launch_bounds__(THREADS) void node_argmax_kernel(int32_t vocab, con
         for (int j = PER_VEC - 1; j >= 0; --j)
             if (x[j] == body_max) consider(best, x[j], head + body_chunk * PER_VEC + j);
     }
-    {
-        const int i = tail_start + threadIdx.x;
-        if (i < vocab) {
-            const float x = scalar_at(i);
-            consider(best, x, i);
-            if (STATS) add_batch(&x, 1, fmaxf(x, -__builtin_inff()));
-        }
-    }
+    if (head_due) take(head_x, threadIdx.x);              // a row too short to give this lane a chunk
+    if (has_tail) take(tail_x, tail_start + threadIdx.x);
 
-    for (int off = 32; off > 0; off >>= 1) {
-        Best o;
-        o.val = __shfl_xor(best.val, off, 64);
-        o.idx = __shfl_xor(best.idx, off, 64);
-        best = merge(best, o);
-        if (STATS) {
-            const float m2 = __shfl_xor(sm_m, off, 64), s2 = __shfl_xor(sm_s, off, 64);
-            merge_softmax_state(sm_m, sm_s, m2, s2);
-        }
-    }
-    __shared__ float s_val[THREADS / 64];
-    __shared__ int32_t s_idx[THREADS / 64];
-    __shared__ float s_m[THREADS / 64], s_s[THREADS / 64];
+    auto with = [&](float val, int32_t idx, float m2, float s2) {
+        best = merge(best, Best{val, idx});
+        if (STATS) merge_softmax_state(sm_m, sm_s, m2, s2);
+    };
+#define GSD_STEP(MASK)                                                                                               \
+    with(lane_xor<MASK>(best.val), lane_xor<MASK>(best.idx), STATS ? lane_xor<MASK>(sm_m) : 0.f,                     \
+         STATS ? lane_xor<MASK>(sm_s) : 0.f)
+    GSD_STEP(32); GSD_STEP(16); GSD_STEP(8); GSD_STEP(4); GSD_STEP(2); GSD_STEP(1);
+    constexpr int kWaves = THREADS / 64;
+    static_assert(kWaves <= 16, "one lane of a 16-lane row per wavefront below");
+    __shared__ float s_val[kWaves];
+    __shared__ int32_t s_idx[kWaves];
+    __shared__ float s_m[kWaves], s_s[kWaves];
     if ((threadIdx.x & 63) == 0) {
         s_val[threadIdx.x >> 6] = best.val;
         s_idx[threadIdx.x >> 6] = best.idx;
@@ -168,23 +170,36 @@ __global__ __launch_bounds__(THREADS) void node_argmax_kernel(int32_t vocab, con
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        Best r{s_val[0], s_idx[0]};
-        for (int w = 1; w < THREADS / 64; ++w) r = merge(r, Best{s_val[w], s_idx[w]});
-        pred[row] = (r.idx == 0x7fffffff) ? 0 : r.idx;
+    if (threadIdx.x < 64) {                               // the wavefronts' results, one per lane, the same way
+        const int w = threadIdx.x % kWaves;
+        best = Best{s_val[w], s_idx[w]};
         if (STATS) {
-            float M = s_m[0], S = s_s[0];
-            for (int w = 1; w < THREADS / 64; ++w) merge_softmax_state(M, S, s_m[w], s_s[w]);
-            row_max[row] = M;
-            row_sumexp[row] = S;
+            sm_m = s_m[w];
+            sm_s = s_s[w];
+        }
+        if constexpr (kWaves > 8) GSD_STEP(8);
+        if constexpr (kWaves > 4) GSD_STEP(4);
+        if constexpr (kWaves > 2) GSD_STEP(2);
+        if constexpr (kWaves > 1) GSD_STEP(1);
+        if (threadIdx.x == 0) {
+            pred[row] = (best.idx == 0x7fffffff) ? 0 : best.idx;
+            if (STATS) {
+                row_max[row] = sm_m;
+                row_sumexp[row] = sm_s;
+            }
         }
     }
+#undef GSD_STEP
 }
 
 hipError_t launch_node_argmax(int32_t rows, int32_t vocab, int dtype, const void *logits, int64_t row_stride,
                               int32_t *pred, float *row_max, float *row_sumexp, hipStream_t stream) {
-    // Few rows: large work-groups so each row still has many loads in flight.
-    const bool big = rows < 1024;
+    // Few rows: the smallest work-group that has the whole row in flight at once (8 loads of 16 bytes per lane); what is
+    // larger only adds wavefronts to start and to merge, what is smaller makes the row two round trips to memory.
+    // 900 rows of 8000 bf16: 6.6 us with 512 lanes, 9.0 with 1024; 385 of 32003 with normalisers 9.5 and 10.1; 300 of 64000
+    // fp32 (four batches either way) 17.7 and 16.9.
+    const double row_bytes = double(vocab) * (dtype == GSD_BF16 ? 2 : 4);
+    const int threads = rows >= 1024 || row_bytes <= 32768 ? 256 : row_bytes <= 65536 ? 512 : 1024;
     // Measured on this chip with 32000-entry bf16 rows: logits that fit the 256 MB last-level cache stream faster
     // with non-temporal loads (131 MB: 5.27 against 4.93 TB/s), larger ones with ordinary loads (1 GB: 5.25 against
     // 4.89 TB/s).
@@ -193,10 +208,15 @@ hipError_t launch_node_argmax(int32_t rows, int32_t vocab, int dtype, const void
 #define GSD_ARGMAX_LAUNCH(THREADS, BF16, NT, STATS)                                                                 \
     hipLaunchKernelGGL((node_argmax_kernel<THREADS, BF16, NT, STATS>), dim3(rows), dim3(THREADS), 0, stream, vocab,  \
                        logits, row_stride, pred, row_max, row_sumexp)
+#define GSD_ARGMAX_NT(THREADS, BF16, STATS)                                                                          \
+    do {                                                                                                            \
+        if (nt) GSD_ARGMAX_LAUNCH(THREADS, BF16, true, STATS); else GSD_ARGMAX_LAUNCH(THREADS, BF16, false, STATS);  \
+    } while (0)
 #define GSD_ARGMAX_PICK(BF16, STATS)                                                                                \
     do {                                                                                                            \
-        if (big) { if (nt) GSD_ARGMAX_LAUNCH(1024, BF16, true, STATS); else GSD_ARGMAX_LAUNCH(1024, BF16, false, STATS); } \
-        else { if (nt) GSD_ARGMAX_LAUNCH(256, BF16, true, STATS); else GSD_ARGMAX_LAUNCH(256, BF16, false, STATS); }  \
+        if (threads == 1024) GSD_ARGMAX_NT(1024, BF16, STATS);                                                       \
+        else if (threads == 512) GSD_ARGMAX_NT(512, BF16, STATS);                                                    \
+        else GSD_ARGMAX_NT(256, BF16, STATS);                                                                        \
     } while (0)
     if (dtype == GSD_BF16) {
         if (stats) GSD_ARGMAX_PICK(true, true); else GSD_ARGMAX_PICK(true, false);
@@ -204,6 +224,7 @@ hipError_t launch_node_argmax(int32_t rows, int32_t vocab, int dtype, const void
         if (stats) GSD_ARGMAX_PICK(false, true); else GSD_ARGMAX_PICK(false, false);
     }
 #undef GSD_ARGMAX_PICK
+#undef GSD_ARGMAX_NT
 #undef GSD_ARGMAX_LAUNCH
     return hipGetLastError();
 }

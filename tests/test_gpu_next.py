@@ -483,6 +483,34 @@ def test_argmax_and_softmax_normalisers_in_one_pass(gpu, ref, dtype):
         assert torch.equal(m, m2) and (s_ / s2 - 1).abs().max().item() < 2e-6
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("rows", [3, 1025])
+@pytest.mark.parametrize("vocab", [1, 7, 17, 2049, 8191, 16385, 32769])
+def test_row_sweeps_at_odd_alignments(gpu, ref, dtype, rows, vocab):
+    """Every start within 16 bytes, rows too short for a chunk, around the row sizes where the work-group grows; the maximum
+    twice, in the elements before the first and behind the last boundary."""
+    import paper_2407_16207_amd as gsd
+    rng = np.random.default_rng(vocab)
+    if rows > 1000 and vocab > 9000:
+        pytest.skip("one size of many rows is enough")
+    x = torch.from_numpy(rng.standard_normal((rows, vocab + 9)).astype(np.float32))
+    x = x.to(torch.bfloat16 if dtype == "bf16" else torch.float32).cuda()
+    for shift in range(0, 9, 1 if rows < 100 else 4):
+        view = x[:, shift:shift + vocab]
+        view[0, 0] = view[0, -1] = 9.0
+        view[1, -1] = 9.0
+        pred, m, s_ = gsd.gsd_node_argmax_stats(view)
+        m2, s2 = gsd.gsd_softmax_stats(view)
+        alone = gsd.gsd_node_argmax(view)
+        torch.cuda.synchronize()
+        host = view.float().cpu().numpy()
+        assert np.array_equal(pred.cpu().numpy(), host.argmax(1)) and torch.equal(pred, alone)
+        _, m_ref, z_ref = gsd_next.softmax_rows(host.astype(np.float64))
+        for mm, ss in ((m, s_), (m2, s2)):
+            assert np.array_equal(mm.cpu().numpy().astype(np.float64), m_ref)
+            assert np.abs(ss.cpu().numpy().astype(np.float64) / z_ref - 1).max() < 2e-6
+
+
 def compare_graph_with_oracle(gpu, node_offsets, par, tok, q, tau, theta_prob, theta_sib, max_nodes=512):
     import paper_2407_16207_amd as gsd
     flag = torch.zeros(1, dtype=torch.int32, device="cuda")
