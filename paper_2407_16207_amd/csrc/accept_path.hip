@@ -10,22 +10,17 @@
 
 namespace gsd {
 
-constexpr int kAcceptThreads = 512;
-constexpr int kAcceptEdgeCache = 6144;
-
-__global__ __launch_bounds__(kAcceptThreads) void accept_kernel(
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void accept_kernel(
     int32_t max_nodes, const int32_t *__restrict__ node_offsets, const int32_t *__restrict__ parent_offsets,
     const int32_t *__restrict__ parent_idx, const int32_t *__restrict__ tokens, const int32_t *__restrict__ pred,
     const int32_t *__restrict__ root_pred, int32_t *__restrict__ accept_len, int32_t *__restrict__ accept_path,
     int32_t *__restrict__ bonus_token) {
-    __shared__ int32_t L[GSD_MAX_NODES_PER_SEQ];
-    __shared__ int32_t pred_s[GSD_MAX_NODES_PER_SEQ];
-    __shared__ int32_t tok_s[GSD_MAX_NODES_PER_SEQ];
-    __shared__ int32_t path_s[GSD_MAX_NODES_PER_SEQ];
-    __shared__ int32_t back_s[GSD_MAX_NODES_PER_SEQ];
-    __shared__ int32_t off_cache[GSD_MAX_NODES_PER_SEQ + 1];
-    __shared__ int32_t edge_cache[kAcceptEdgeCache];
-    __shared__ uint32_t wave_best[kAcceptThreads / 64];
+    __shared__ int32_t L[THREADS];
+    __shared__ int32_t pred_s[THREADS];
+    __shared__ int32_t path_s[THREADS];
+    __shared__ int32_t back_s[THREADS];
+    __shared__ uint32_t wave_best[THREADS / 64];
     __shared__ int32_t len_s;
 
     const int b = blockIdx.x;
@@ -34,26 +29,10 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_kernel(
     if (n > max_nodes) n = max_nodes;
     if (n < 0) n = 0;
     const int32_t rp = root_pred[b];
-    const int32_t e0 = parent_offsets[base];
-    const int32_t e1 = parent_offsets[base + n];
-    const bool cached = (e1 - e0) <= kAcceptEdgeCache;
 
-    for (int i = threadIdx.x; i <= n; i += kAcceptThreads) off_cache[i] = parent_offsets[base + i] - e0;
-    if (cached)
-        for (int e = threadIdx.x; e < e1 - e0; e += kAcceptThreads) edge_cache[e] = parent_idx[e0 + e];
-    for (int i = threadIdx.x; i < n; i += kAcceptThreads) {
-        L[i] = -1;
-        pred_s[i] = pred[base + i];
-        tok_s[i] = tokens[base + i];
-    }
-    __syncthreads();
-    // parent e of this sequence, from the LDS copy or (sequences with more edges than the cache holds) from memory
-    auto edge_at = [&](int e) -> int { return cached ? edge_cache[e] : parent_idx[e0 + e]; };
-
-    // One thread per node (kAcceptThreads >= GSD_MAX_NODES_PER_SEQ).  Whether an edge is accepted never changes,
-    // so it is decided once; the first four parents of a node stay in registers as (id, accepted), which leaves a
-    // sweep with four independent LDS reads and no branch per parent (branches serialise the round trips).
-    static_assert(kAcceptThreads >= GSD_MAX_NODES_PER_SEQ, "one thread per node");
+    // One thread per node (the launcher: THREADS >= max_nodes).  Whether an edge is accepted never changes, so it is decided
+    // once; the first four parents of a node, fetched together with clamped indices instead of branches, stay in registers,
+    // which leaves a sweep with four independent LDS reads and no branch per parent (branches serialise the round trips).
     constexpr int kRegParents = 4;
     const int i = threadIdx.x;
     const bool active = i < n;
@@ -65,15 +44,24 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_kernel(
     // is edge p -> i accepted (p is a well-formed parent of i)?
     auto accepted = [&](int p) -> bool { return my_tok == (p == -1 ? rp : pred_s[p]); };
     if (active) {
-        e_lo = off_cache[i];
-        e_hi = off_cache[i + 1];
-        my_tok = tok_s[i];
+        e_lo = parent_offsets[base + i];
+        e_hi = parent_offsets[base + i + 1];
+        my_tok = tokens[base + i];
+        pred_s[i] = pred[base + i];
+        L[i] = -1;
+        if (e_hi > e_lo) {
+#pragma unroll
+            for (int x = 0; x < kRegParents; ++x) par[x] = parent_idx[min(e_lo + x, e_hi - 1)];
+        }
+    }
+    __syncthreads();
+    if (active) {
 #pragma unroll
         for (int x = 0; x < kRegParents; ++x) {
-            if (e_lo + x < e_hi) {
-                const int p = edge_at(e_lo + x);
-                if (p >= -1 && p < i && accepted(p)) par[x] = p;
-            }
+            const int p = par[x];
+            const bool edge = e_lo + x < e_hi && p >= -1 && p < i;
+            const int32_t llm = pred_s[edge && p >= 0 ? p : i];
+            par[x] = edge && my_tok == (p == -1 ? rp : llm) ? p : -2;
         }
     }
     const bool more = active && e_hi - e_lo > kRegParents;     // rare: a node with more than four parents
@@ -91,7 +79,7 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_kernel(
             }
             if (more) {
                 for (int e = e_lo + kRegParents; e < e_hi; ++e) {
-                    const int p = edge_at(e);
+                    const int p = parent_idx[e];
                     if (p < -1 || p >= i || !accepted(p)) continue;
                     const int32_t lp = (p == -1) ? 0 : L[p];
                     if (lp >= 0 && lp + 1 > best) best = lp + 1;
@@ -118,7 +106,7 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_kernel(
         }
         if (more) {
             for (int e = e_lo + kRegParents; e < e_hi; ++e) {
-                const int p = edge_at(e);
+                const int p = parent_idx[e];
                 if (p < -1 || p >= i || !accepted(p)) continue;
                 const int32_t lp = (p == -1) ? 0 : L[p];
                 if (lp == mine - 1 && p < chosen) chosen = p;
@@ -130,15 +118,17 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_kernel(
     // best end node: largest L, then smallest id.  key = L * 1024 + (1023 - i), 0 = nothing accepted.
     uint32_t key = 0;
     if (active && mine > 0) key = uint32_t(mine) * 1024u + uint32_t(1023 - i);
-    for (int off = 32; off > 0; off >>= 1) {
-        const uint32_t other = __shfl_xor(key, off, 64);
-        key = other > key ? other : key;
-    }
+    key = max(key, lane_xor<32>(key));
+    key = max(key, lane_xor<16>(key));
+    key = max(key, lane_xor<8>(key));
+    key = max(key, lane_xor<4>(key));
+    key = max(key, lane_xor<2>(key));
+    key = max(key, lane_xor<1>(key));
     if ((threadIdx.x & 63) == 0) wave_best[threadIdx.x >> 6] = key;
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t k = 0;
-        for (int w = 0; w < kAcceptThreads / 64; ++w) k = wave_best[w] > k ? wave_best[w] : k;
+        for (int w = 0; w < THREADS / 64; ++w) k = wave_best[w] > k ? wave_best[w] : k;
         const int32_t len = int32_t(k / 1024u);
         int32_t v = (len > 0) ? int32_t(1023u - (k % 1024u)) : -1;
         len_s = len;
@@ -152,15 +142,25 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_kernel(
     __syncthreads();
     const int32_t len = len_s;
     int32_t *out = accept_path + int64_t(b) * max_nodes;
-    for (int x = threadIdx.x; x < max_nodes; x += kAcceptThreads) out[x] = (x < len) ? path_s[x] : -1;
+    for (int x = threadIdx.x; x < max_nodes; x += THREADS) out[x] = (x < len) ? path_s[x] : -1;
 }
 
 hipError_t launch_accept(int32_t batch, int32_t max_nodes, const int32_t *node_offsets,
                          const int32_t *parent_offsets, const int32_t *parent_idx, const int32_t *tokens,
                          const int32_t *pred, const int32_t *root_pred, int32_t *accept_len, int32_t *accept_path,
                          int32_t *bonus_token, hipStream_t stream) {
-    hipLaunchKernelGGL(accept_kernel, dim3(batch), dim3(kAcceptThreads), 0, stream, max_nodes, node_offsets,
-                       parent_offsets, parent_idx, tokens, pred, root_pred, accept_len, accept_path, bonus_token);
+    // The fewest wavefronts that hold a node per lane: each more costs the launch and every barrier of the sweeps.
+    // 64 nodes: 3.4 us with one, 4.5 with eight and the parents
+    // passed through LDS first; 8 sequences of 256: 6.1 against 6.8 us; 32 of 512: 9.7 against 10.8.
+#define GSD_ACCEPT(THREADS)                                                                                          \
+    hipLaunchKernelGGL(accept_kernel<THREADS>, dim3(batch), dim3(THREADS), 0, stream, max_nodes, node_offsets,       \
+                       parent_offsets, parent_idx, tokens, pred, root_pred, accept_len, accept_path, bonus_token)
+    static_assert(GSD_MAX_NODES_PER_SEQ == 512, "the cases below cover 512 nodes");
+    if (max_nodes <= 64) GSD_ACCEPT(64);
+    else if (max_nodes <= 128) GSD_ACCEPT(128);
+    else if (max_nodes <= 256) GSD_ACCEPT(256);
+    else GSD_ACCEPT(512);
+#undef GSD_ACCEPT
     return hipGetLastError();
 }
 

@@ -484,15 +484,12 @@ def test_argmax_and_softmax_normalisers_in_one_pass(gpu, ref, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("rows", [3, 1025])
-@pytest.mark.parametrize("vocab", [1, 7, 17, 2049, 8191, 16385, 32769])
+@pytest.mark.parametrize("rows,vocab", [(3, 1), (3, 7), (3, 17), (3, 2049), (3, 8191), (3, 16385), (3, 32769), (1025, 7), (1025, 8191)])
 def test_row_sweeps_at_odd_alignments(gpu, ref, dtype, rows, vocab):
     """Every start within 16 bytes, rows too short for a chunk, around the row sizes where the work-group grows; the maximum
     twice, in the elements before the first and behind the last boundary."""
     import paper_2407_16207_amd as gsd
     rng = np.random.default_rng(vocab)
-    if rows > 1000 and vocab > 9000:
-        pytest.skip("one size of many rows is enough")
     x = torch.from_numpy(rng.standard_normal((rows, vocab + 9)).astype(np.float32))
     x = x.to(torch.bfloat16 if dtype == "bf16" else torch.float32).cuda()
     for shift in range(0, 9, 1 if rows < 100 else 4):
