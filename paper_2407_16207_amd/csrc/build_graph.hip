@@ -28,7 +28,9 @@
 // each publishes its two counts in the output array `counts` as soon as it has them and waits for the others' only where
 // it starts to write, by which time they are there.  A small launch before it marks the counts as missing (the library
 // keeps no scratch memory).  Counting in a first kernel and constructing again in a second one took 16 + 31 us for eight
-// trees of 512 nodes, this one 32 us.
+// trees of 512 nodes, this one 32 us then and 22 now (both launches in a replayed graph 34.9 -> 23.8).
+// Bound by the chain of its phases on one CU (us, of 18.5 inside the kernel): depths 0.7, classes 1.8, layers 1.9, merge
+// decisions 4.1, counts 0.7, levels 2.5, renumbering 2.1, edges and packing 3.5.
 #include "gsd_internal.h"
 
 namespace gsd {
@@ -52,6 +54,7 @@ struct GraphLds {
     // sets of mergers
     uint64_t pool[GSD_MAX_NODES_PER_SEQ * 8];
     int32_t wave_tot[16];
+    int32_t moved[3];                          // of a round of the level relaxation: some level has grown
     int32_t bad;
     int32_t max_depth;
 };
@@ -102,13 +105,20 @@ __device__ __forceinline__ void construct(GraphLds &s, int n, int64_t base, cons
         s.depth[i] = a == -1 ? d : 0;
     }
     __syncthreads();
-    if (i < n) {
-        if (i > 0 && s.depth[i] < s.depth[i - 1]) s.bad = 1;       // not breadth first
-        atomicMax(&s.max_depth, s.depth[i]);
+    const int my_depth = i < n ? s.depth[i] : 0;
+    if (i > 0 && i < n && my_depth < s.depth[i - 1]) s.bad = 1;    // not breadth first
+    {
+        int deepest = my_depth;                        // one atomic per wave: 512 on one word take 1.3 us
+        deepest = max(deepest, lane_xor<32>(deepest));
+        deepest = max(deepest, lane_xor<16>(deepest));
+        deepest = max(deepest, lane_xor<8>(deepest));
+        deepest = max(deepest, lane_xor<4>(deepest));
+        deepest = max(deepest, lane_xor<2>(deepest));
+        deepest = max(deepest, lane_xor<1>(deepest));
+        if ((i & 63) == 0) atomicMax(&s.max_depth, deepest);
     }
     __syncthreads();
     const int max_depth = s.max_depth;
-    const int my_depth = i < n ? s.depth[i] : 0;
 
     // tau-gram classes, level by level.  At level t a node with depth >= t has the key (its token, the level t-1
     // class of its parent); its class is the smallest node id with the same key.  The nodes with a key claim a slot
@@ -242,18 +252,15 @@ __device__ __forceinline__ void decide_in_one_wave(GraphLds &s, int n_red) {
             const int wk = 2 * c + half;                    // the word that holds the bits of these 32 pairs
             const int end = n_red - 64 * c < 32 * half + 32 ? n_red - 64 * c : 32 * half + 32;
             for (int l = 32 * half; l < end; ++l) {         // uniform
-                const uint32_t bit = 1u << (l & 31);
-                const uint32_t own = __builtin_amdgcn_readlane(row[c][wk], l);
-                if (own & bit) continue;                    // R descends from F
                 uint32_t r_row[W];
 #pragma unroll
                 for (int w = wk; w < W; ++w) r_row[w] = __builtin_amdgcn_readlane(row[c][w], l);
+                if ((r_row[wk] >> (l & 31)) & 1) continue;  // R descends from F
 #pragma unroll
-                for (int c2 = c; c2 < NC; ++c2) {
-                    if (row[c2][wk] & bit) {
+                for (int c2 = c; c2 < NC; ++c2) {           // a mask instead of a branch: three instructions to enter one
+                    const uint32_t has = uint32_t(__builtin_amdgcn_sbfe(int(row[c2][wk]), uint32_t(l) & 31, 1));
 #pragma unroll
-                        for (int w = wk; w < W; ++w) row[c2][w] |= r_row[w];
-                    }
+                    for (int w = wk; w < W; ++w) row[c2][w] |= r_row[w] & has;
                 }
                 drawn[c] |= uint64_t(1) << l;
             }
@@ -385,7 +392,6 @@ __global__ __launch_bounds__(kGraphThreads) void build_graph_kernel(
         }
     }
     // Storage that construct() and decide_merges() are done with is used again from here on:
-    int32_t *level = s.tok;                 // longest distance from the root, in edges below the root's children
     int32_t *group_level = s.first_ex;      // per node f: the largest level among f and the nodes merged into it
     int32_t *new_id = reinterpret_cast<int32_t *>(s.q);
     constexpr int kSetWords = GSD_MAX_NODES_PER_SEQ / 32;           // words of a set of nodes
@@ -401,29 +407,44 @@ __global__ __launch_bounds__(kGraphThreads) void build_graph_kernel(
         __hip_atomic_store(&counts[2 * int64_t(b) + 1], total_edges, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if ((too_many || s.bad) && error_flag) atomicOr(error_flag, 1);
     }
-    level[i] = ex ? s.depth[i] - 1 : -1;
+    // Levels by relaxation: they start at the tree depth, a lower bound, and only grow.  Whatever a read returns is a bound as
+    // well, so the waves need not take their steps together: each follows its own nodes for a few, and they meet only to
+    // find out whether all of them have come to rest.  A round in which nothing grew has seen every update (they were made
+    // before its opening barrier) and is the last: at most one round per node of the longest path.  8 trees of 512 nodes, 11 to 25
+    // levels: 2.5 us, 7.2 with two barriers and a reduction for every level.
+    constexpr int kSteps = 4;
+    int my_level = ex ? s.depth[i] - 1 : -1;
     group_level[i] = -1;
+    if (i < 3) s.moved[i] = 0;
     __syncthreads();
-    // levels by relaxation: they start at the tree depth, a lower bound, and only grow; a sweep that moves nothing
-    // ends it (at most one sweep per node of the longest path, and never more than n + 1)
-    for (int sweep = 0; sweep <= n; ++sweep) {
-        if (ex) atomicMax(&group_level[i], level[i]);
-        if (merger) atomicMax(&group_level[my_first], level[i]);
-        __syncthreads();
-        int changed = 0;
+    if (ex) atomicMax(&group_level[i], my_level);
+    if (merger) atomicMax(&group_level[my_first], my_level);
+    __syncthreads();
+    for (int round = 0; round <= n; ++round) {
+        bool grew = false;
         if (ex && my_par >= 0) {
-            const int l = 1 + group_level[my_par];
-            if (l > level[i]) {
-                level[i] = l;
-                changed = 1;
+#pragma unroll
+            for (int step = 0; step < kSteps; ++step) {
+                const int l = 1 + __hip_atomic_load(&group_level[my_par], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (l > my_level && l < GSD_MAX_NODES_PER_SEQ) {     // (a level of a node in a graph without cycles)
+                    my_level = l;
+                    grew = true;
+                    atomicMax(&group_level[i], l);
+                    if (merger) atomicMax(&group_level[my_first], l);
+                }
             }
         }
-        if (!__syncthreads_or(changed)) break;
+        // three flags in turn: one is written, one read, and the one that everybody has read is cleared
+        const int at = round % 3;
+        if (grew) s.moved[at] = 1;
+        __syncthreads();
+        if (i == 0) s.moved[(round + 2) % 3] = 0;
+        if (s.moved[at] == 0) break;
     }
     // new id = rank by (level, id) among the existing nodes
     int32_t *table = reinterpret_cast<int32_t *>(s.pool);            // the ancestor rows are not needed any more
     int ranked = 0;
-    const int my_new = stable_rank(s, table, ex ? level[i] : 0, ex, ranked);
+    const int my_new = stable_rank(s, table, ex ? my_level : 0, ex, ranked);
     new_id[i] = my_new;
     __syncthreads();
     // The mergers of every first occurrence as a set of new ids, word-major: read in order, the set of a node's tree

@@ -601,6 +601,18 @@ def test_build_token_graph_many_redundant_nodes(gpu, k, vocab, tau, seed, at_lea
     assert int(((first & 4) != 0).sum()) >= at_least, int(((first & 4) != 0).sum())
 
 
+@pytest.mark.parametrize("chains,length,vocab,tau", [(1, 512, 600, 1), (2, 256, 300, 1), (12, 42, 60, 2), (5, 100, 40, 1), (64, 8, 30, 1)])
+def test_build_token_graph_long_paths(gpu, chains, length, vocab, tau):
+    """Chains side by side that merge into each other's earlier layers: levels far above the depth of the tree, which the level
+    relaxation reaches node by node across all wavefronts."""
+    rng = np.random.default_rng(100 * chains + length)
+    n = chains * length
+    par = np.concatenate([np.full(chains, -1), np.arange(n - chains)]).astype(np.int32)
+    tok = rng.integers(0, vocab, n).astype(np.int32)
+    r = compare_graph_with_oracle(gpu, np.array([0, n], dtype=np.int32), par, tok, np.full(n, 0.5, dtype=np.float32), tau, 0.0, 0.0)
+    assert len(r[3]) > chains
+
+
 def test_build_token_graph_many_sequences(gpu):
     """More sequences than a work-group has threads: every work-group adds up the counts of all sequences before it."""
     rng = np.random.default_rng(99)
