@@ -17,7 +17,9 @@
 //                           (resample_held_phase: the same with the slices kept in registers, where they fit.)
 // Both phases are chains of dependent round trips on one CU per sequence.  As two kernels (7.0 + 11.7 us on 8 sequences
 // of 256 nodes, 32000 tokens) the second waited for a launch and fetched end node, offsets and parents again: together
-// 16.7 us.  With more sequences than CUs they are two kernels all the same (accept_stochastic_kernel, resample_kernel).
+// 16.7 us, now 14.6.  What is left is mostly the vector work of one CU: exponentials of 32000 draft logits 2.2 us, weights 3.5.  With more sequences than CUs they are two kernels all the same (accept_stochastic_kernel, resample_kernel).
+#include <type_traits>
+
 #include "gsd_internal.h"
 
 namespace gsd {
@@ -149,6 +151,7 @@ struct AcceptLds {
     int32_t path[GSD_MAX_NODES_PER_SEQ];
     int32_t back[GSD_MAX_NODES_PER_SEQ];
     uint32_t wave_best[kStochThreads / 64];
+    int32_t grew[3];                   // of a round of the relaxation: some L has grown
     int32_t len, end;
 };
 
@@ -210,36 +213,52 @@ __device__ __forceinline__ int accept_phase(AcceptLds &s, const gsd_stochastic_d
         }
         L[i] = -1;
     }
+    if (i < 3) s.grew[i] = 0;
     const bool more = active && e_hi - e_lo > kRegParents;     // rare: a node with more than four parents
     auto passes = [&](int r) -> bool { return r >= -1 && r < i && tok_ok && coin < prob_after(r); };
     __syncthreads();
 
+    // L[i] = 1 + max L[parent] by relaxation.  Values only grow and whatever is read is the length of a path that exists, so the
+    // waves follow their own nodes for a few steps and then meet to find out whether all have come to rest (256 nodes: 1.35 us,
+    // 2.3 when every step was a sweep with a barrier and a reduction).
+    // Further parents are tested anew in every step: a wave that has some takes one step at a time.
+    const int steps = __any(more) ? 1 : 4;
     int32_t mine = -1;             // L[i]
-    for (int sweep = 0; sweep <= n; ++sweep) {
-        int changed = 0;
+    for (int round = 0; round <= n; ++round) {
+        bool grew = false;
         if (active) {
-            int32_t best = mine;
+#pragma unroll 1
+            for (int step = 0; step < steps; ++step) {
+                int32_t best = mine;
 #pragma unroll
-            for (int x = 0; x < kRegParents; ++x) {
-                const int32_t l = L[par[x] >= 0 ? par[x] : i];
-                const int32_t lr = par[x] >= 0 ? l : (par[x] == -1 ? 0 : -1);
-                if (lr >= 0 && lr + 1 > best) best = lr + 1;
-            }
-            if (more) {
-                for (int e = e_lo + kRegParents; e < e_hi; ++e) {
-                    const int r = d.parent_idx[e];
-                    if (!passes(r)) continue;
-                    const int32_t lr = (r == -1) ? 0 : L[r];
+                for (int x = 0; x < kRegParents; ++x) {
+                    const int32_t l = __hip_atomic_load(&L[par[x] >= 0 ? par[x] : i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    const int32_t lr = par[x] >= 0 ? l : (par[x] == -1 ? 0 : -1);
                     if (lr >= 0 && lr + 1 > best) best = lr + 1;
                 }
-            }
-            if (best != mine) {
-                mine = best;
-                L[i] = best;
-                changed = 1;
+                if (more) {
+                    for (int e = e_lo + kRegParents; e < e_hi; ++e) {
+                        const int r = d.parent_idx[e];
+                        if (!passes(r)) continue;
+                        const int32_t lr = r == -1 ? 0 : __hip_atomic_load(&L[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        if (lr >= 0 && lr + 1 > best) best = lr + 1;
+                    }
+                }
+                const bool up = best != mine;
+                if (up) {
+                    mine = best;
+                    grew = true;
+                    __hip_atomic_store(&L[i], best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+                if (!__any(up)) break;
             }
         }
-        if (!__syncthreads_or(changed)) break;
+        // three flags in turn: one is written, one read, and the one that everybody has read is cleared
+        const int at = round % 3;
+        if (grew) s.grew[at] = 1;
+        __syncthreads();
+        if (i == 0) s.grew[(round + 2) % 3] = 0;
+        if (s.grew[at] == 0) break;
     }
 
     // back pointer of every accepted node: the smallest-id passing parent that ends a path one node shorter
@@ -264,10 +283,12 @@ __device__ __forceinline__ int accept_phase(AcceptLds &s, const gsd_stochastic_d
 
     uint32_t key = 0;                                    // largest L, then smallest id
     if (active && mine > 0) key = uint32_t(mine) * 1024u + uint32_t(1023 - i);
-    for (int off = 32; off > 0; off >>= 1) {
-        const uint32_t other = __shfl_xor(key, off, 64);
-        key = other > key ? other : key;
-    }
+    key = max(key, lane_xor<32>(key));
+    key = max(key, lane_xor<16>(key));
+    key = max(key, lane_xor<8>(key));
+    key = max(key, lane_xor<4>(key));
+    key = max(key, lane_xor<2>(key));
+    key = max(key, lane_xor<1>(key));
     if ((threadIdx.x & 63) == 0) wave_best[threadIdx.x >> 6] = key;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -298,6 +319,57 @@ __device__ __forceinline__ int accept_phase(AcceptLds &s, const gsd_stochastic_d
 }
 
 constexpr int kResampleThreads = kStochThreads;
+constexpr int kResampleWaves = kResampleThreads / 64;
+
+__device__ __forceinline__ void merge_lanes(float &m, float &s) {      // of a wave, in every lane
+    merge_state(m, s, lane_xor<32>(m), lane_xor<32>(s));
+    merge_state(m, s, lane_xor<16>(m), lane_xor<16>(s));
+    merge_state(m, s, lane_xor<8>(m), lane_xor<8>(s));
+    merge_state(m, s, lane_xor<4>(m), lane_xor<4>(s));
+    merge_state(m, s, lane_xor<2>(m), lane_xor<2>(s));
+    merge_state(m, s, lane_xor<1>(m), lane_xor<1>(s));
+}
+
+// The states of the work-group's 16 waves merged in their order, by one wave, a state per lane: the running maxima and both
+// factors of every merge at once, which leaves one multiply-add per state in the chain.
+__device__ __forceinline__ void merge_waves(const float *red_m, const float *red_s, float &m, float &s) {
+    static_assert(kResampleWaves == 16, "a row of 16 lanes");
+    const int w = threadIdx.x & 15;
+    const float empty = -__builtin_inff(), mw = red_m[w];
+    auto from_below = [&](float x, auto shift) -> float {              // lane w - shift of the row; none: empty
+        return __uint_as_float(__builtin_amdgcn_update_dpp(__float_as_uint(empty), __float_as_uint(x), 0x110 + decltype(shift)::value, 0xf, 0xf, false));
+    };
+    float top = mw;
+    top = fmaxf(top, from_below(top, std::integral_constant<int, 1>{}));
+    top = fmaxf(top, from_below(top, std::integral_constant<int, 2>{}));
+    top = fmaxf(top, from_below(top, std::integral_constant<int, 4>{}));
+    top = fmaxf(top, from_below(top, std::integral_constant<int, 8>{}));
+    const float below = from_below(top, std::integral_constant<int, 1>{});
+    const bool none = top == empty;                                    // all states up to this one are empty
+    const uint32_t keep = __float_as_uint(none ? 0.f : __expf(below - top));
+    const uint32_t add = __float_as_uint(red_s[w] * (none ? 0.f : __expf(mw - top)));
+    s = red_s[0];
+#pragma unroll
+    for (int x = 1; x < kResampleWaves; ++x)
+        s = __builtin_fmaf(s, __uint_as_float(__builtin_amdgcn_readlane(keep, x)), __uint_as_float(__builtin_amdgcn_readlane(add, x)));
+    m = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(top), 15));
+}
+
+// x / d, correctly rounded, for many x and one d from [1, 2^31): two corrections of x * (1/d).  The first leaves a quotient
+// within an ulp, from which, with a correctly rounded reciprocal, the second rounds correctly (Markstein 1990); remainders are
+// exact and quotients normal down to x = 2^-94, below which it is left to the compiler's division (5 instructions instead of 11 and a
+// reciprocal each).
+struct Divisor {
+    float d, inverse;
+    __device__ __forceinline__ explicit Divisor(float by) : d(by), inverse(1.f / by) {}
+    __device__ __forceinline__ float operator()(float x) const {
+        float q = x * inverse;
+        q = __builtin_fmaf(__builtin_fmaf(-q, d, x), inverse, q);
+        q = __builtin_fmaf(__builtin_fmaf(-q, d, x), inverse, q);
+        if (__builtin_expect(__any(__float_as_uint(x) - 1u < __float_as_uint(0x1p-94f) - 1u), 0)) q = x / d;
+        return q;
+    }
+};
 
 // The draw for any vocabulary, type and alignment.  A thread's slice is contiguous in memory, so lanes that fetched their
 // own slices one element after the other would touch 64 lines with every load; instead neighbouring lanes fetch
@@ -305,13 +377,14 @@ constexpr int kResampleThreads = kStochThreads;
 // words after the one before it (no bank conflicts when every lane then reads its own).  The slice that holds the target
 // is weighed by the whole work-group and walked by one thread.  Bound by the chain of these phases on one CU.
 // 8 sequences of 128 nodes, whole call: 32003 bf16 tokens 66.4 -> 43.7 us; 4 sequences, 64000 tokens: 108 -> 61.7;
-// 2 sequences, 64001 fp32 tokens: 98.5 -> 62.7, against a kernel that fetched slices lane by lane.
+// 2 sequences, 64001 fp32 tokens: 98.5 -> 62.7, against a kernel that fetched slices lane by lane.  With the scan and the
+// divisions below: 8 of 64 nodes, 32003 tokens 34.4 -> 31.6, 4 of 64, 64000 tokens 53.4 -> 48.3.
 template <bool BF16, int SEG_BYTES>
 __device__ __forceinline__ void resample_phase(const gsd_stochastic_desc &d, int end, bool child) {
     constexpr int ELT = BF16 ? 2 : 4;
     constexpr int kSeg = SEG_BYTES / ELT;                         // elements of a slice that are in LDS at a time
     constexpr int kStride = SEG_BYTES / 4 + 1;                    // words from one slice's segment to the next
-    constexpr int kWaves = kResampleThreads / 64;
+    constexpr int kWaves = kResampleWaves;
     __shared__ uint32_t seg_p[kResampleThreads * kStride], seg_q[kResampleThreads * kStride];
     __shared__ float part[2][kResampleThreads];
     __shared__ float red_m[kWaves], red_s[kWaves], stat[2];
@@ -359,27 +432,27 @@ __device__ __forceinline__ void resample_phase(const gsd_stochastic_desc &d, int
             }
         }
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        const float m2 = __shfl_xor(m, off, 64), s2 = __shfl_xor(s, off, 64);
-        merge_state(m, s, m2, s2);
-    }
+    merge_lanes(m, s);
     if ((t & 63) == 0) {
         red_m[t >> 6] = m;
         red_s[t >> 6] = s;
     }
     const bool use_residual = __syncthreads_or(child) != 0;       // does the end node (or the root) have children ?
-    if (t == 0) {
-        float M = red_m[0], S = red_s[0];
-        for (int w = 1; w < kWaves; ++w) merge_state(M, S, red_m[w], red_s[w]);
-        stat[0] = M;
-        stat[1] = S;
+    if (t < 64) {
+        float M, S;
+        merge_waves(red_m, red_s, M, S);
+        if (t == 0) {
+            stat[0] = M;
+            stat[1] = S;
+        }
     }
     __syncthreads();
-    const float q_max = stat[0], q_sum = stat[1];
+    const float q_max = stat[0];
+    const Divisor by_p(p_sum), by_q(stat[1]);
     auto weight = [&](uint32_t vp, uint32_t vq, bool residual) -> float {
-        const float p = __expf(value(vp) - p_max) / p_sum;
+        const float p = by_p(__expf(value(vp) - p_max));
         if (!residual) return p;
-        const float q = __expf(value(vq) - q_max) / q_sum;
+        const float q = by_q(__expf(value(vq) - q_max));
         return fmaxf(p - q, 0.f);
     };
 
@@ -437,21 +510,38 @@ __device__ __forceinline__ void resample_phase(const gsd_stochastic_desc &d, int
         }
         return local;
     };
-    // inclusive scan of the slices' weights, one fixed order; the buffers take turns, so a step needs one barrier
+    // Inclusive scan of the slices' weights in one fixed order, that of ten doubling steps: value t takes in value t - 1, then
+    // t - 2, t - 4, ... t - 512, each as the step before left it.  The steps up to 32 reach into the wave before at most, so a
+    // wave takes them on its own, with that wave's values in a second register; the others stay in the lane, sixteen
+    // values from LDS.  Three barriers instead of eleven, 2.9 instead of 5.4 us.
     float before = 0.f, upto = 0.f, total = 0.f;
+    const int lane = t & 63, wave = t >> 6;
     auto scan = [&](bool residual) {
-        upto = slice_sum(residual);
-        int at = 0;
-        part[at][t] = upto;
+        float a = slice_sum(residual);
+        part[0][t] = a;
         __syncthreads();
-        for (int dd = 1; dd < kResampleThreads; dd <<= 1) {
-            if (t >= dd) upto += part[at][t - dd];
-            at ^= 1;
-            part[at][t] = upto;
-            __syncthreads();
+        float prev = wave > 0 ? part[0][t - 64] : 0.f;           // (lanes below a step's reach are not needed after it)
+#pragma unroll
+        for (int dd = 1; dd < 64; dd <<= 1) {
+            const int src = (lane - dd) & 63;
+            const float from_a = __shfl(a, src, 64), from_prev = __shfl(prev, src, 64);
+            if (t >= dd) a += lane >= dd ? from_a : from_prev;
+            prev += lane >= dd ? from_prev : 0.f;
         }
-        before = t > 0 ? part[at][t - 1] : 0.f;
-        total = part[at][kResampleThreads - 1];
+        part[1][t] = a;
+        __syncthreads();
+        float x[kWaves];
+#pragma unroll
+        for (int j = 0; j < kWaves; ++j) x[j] = j <= wave ? part[1][t - (j <= wave ? 64 * j : 0)] : 0.f;
+#pragma unroll
+        for (int step = 1; step < kWaves; step <<= 1)            // x[j] stands for wave - j
+#pragma unroll
+            for (int j = 0; j + step < kWaves; j += 2 * step) x[j] += x[j + step];
+        upto = x[0];
+        part[0][t] = upto;
+        __syncthreads();
+        before = t > 0 ? part[0][t - 1] : 0.f;
+        total = part[0][kResampleThreads - 1];
     };
     bool residual = use_residual;
     scan(residual);
@@ -518,9 +608,9 @@ __device__ __forceinline__ void resample_held_phase(const gsd_stochastic_desc &d
     constexpr int ELT = BF16 ? 2 : 4;
     constexpr int PER_VEC = 16 / ELT;
     constexpr int KV = kHeld / PER_VEC;
-    constexpr int kWaves = kResampleThreads / 64;
+    constexpr int kWaves = kResampleWaves;
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    __shared__ float red_m[kWaves], red_s[kWaves], wave_sum[2][kWaves];
+    __shared__ float red_m[kWaves], red_s[kWaves], stat[2], wave_sum[2][kWaves];
     __shared__ int pick_s;
 
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -565,17 +655,22 @@ __device__ __forceinline__ void resample_held_phase(const gsd_stochastic_desc &d
                 for (int e = 0; e < PER_VEC; ++e) sum += __expf(value(raw_q[j], e) - m);
             }
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        const float m2 = __shfl_xor(m, off, 64), s2 = __shfl_xor(sum, off, 64);
-        merge_state(m, sum, m2, s2);
-    }
+    merge_lanes(m, sum);
     if (lane == 0) {
         red_m[wave] = m;
         red_s[wave] = sum;
     }
     const bool use_residual = __syncthreads_or(child) != 0;       // does the end node (or the root) have children ?
-    float q_max = red_m[0], q_sum = red_s[0];
-    for (int w = 1; w < kWaves; ++w) merge_state(q_max, q_sum, red_m[w], red_s[w]);
+    if (wave == 0) {
+        float M, S;
+        merge_waves(red_m, red_s, M, S);
+        if (lane == 0) {
+            stat[0] = M;
+            stat[1] = S;
+        }
+    }
+    __syncthreads();
+    const float q_max = stat[0], q_sum = stat[1];
 
     const float p_scale = 1.f / p_sum, q_scale = 1.f / q_sum;     // one division per row instead of one per token
     auto weight_of = [&](float lp, float lq, bool residual) -> float {
@@ -691,8 +786,10 @@ __global__ __launch_bounds__(kAcceptOnlyThreads) void accept_stochastic_kernel(c
     accept_phase<kAcceptOnlyThreads>(s, d, child);
 }
 
+// (The general draw has to leave room for a second work-group: at 7 wavefronts to a SIMD 512 sequences over 1000 tokens take
+// 22.8 us a call instead of 19.5.)
 template <Resample KIND>
-__global__ __launch_bounds__(kResampleThreads) void resample_kernel(const gsd_stochastic_desc d) {
+__global__ __launch_bounds__(kResampleThreads, KIND == Resample::general_f32 || KIND == Resample::general_bf16 ? 8 : 4) void resample_kernel(const gsd_stochastic_desc d) {
     const int64_t base = d.node_offsets[blockIdx.x];
     const int n = max(0, min(d.node_offsets[blockIdx.x + 1] - int32_t(base), d.max_nodes));
     const int end = __builtin_amdgcn_readfirstlane(d.end_node[blockIdx.x]);

@@ -318,6 +318,35 @@ def test_stochastic_draw_any_vocabulary(gpu, dtype, vocab):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("vocab", [3, 1003, 2049, 8192])
+def test_stochastic_draw_with_far_apart_logits(gpu, dtype, vocab):
+    """Logits up to 400 apart, rows with -inf on most tokens: exponentials below 2^-94, where the draw's own division hands over
+    to the compiler's, exact zeros, and slices without any weight."""
+    import paper_2407_16207_amd as gsd
+    rng = np.random.default_rng(vocab)
+    batch = 6
+    spread = (rng.random((2 * batch, vocab)) * -400).astype(np.float32)
+    spread[rng.random(spread.shape) < np.array([0.0, 0.9] * batch)[:, None]] = -np.inf
+    spread[np.arange(2 * batch), rng.integers(0, vocab, 2 * batch)] = 0.0
+    lp = torch.from_numpy(spread).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    lq = torch.from_numpy(np.roll(spread, 1, axis=0)).to(lp.dtype)
+    node_offsets = np.arange(batch + 1, dtype=np.int32)           # a node per sequence, a child of the root that is refused
+    resample_u = np.linspace(0, 0.999, batch).astype(np.float32)
+    dp, dq = lp.cuda(), lq.cuda()
+    ln, _, end, bonus, _, _ = gsd.gsd_accept_stochastic(
+        gpu.to_dev(node_offsets), gpu.to_dev(node_offsets), gpu.to_dev(np.full(batch, -1, dtype=np.int32)),
+        gpu.to_dev(np.zeros(batch, dtype=np.int32)), dp[:batch], dp[batch:], dq[:batch], dq[batch:],
+        gpu.to_dev(np.full(batch, 1e6, dtype=np.float32)), gpu.to_dev(np.ones(batch, dtype=np.float32)), gpu.to_dev(resample_u), 1)
+    torch.cuda.synchronize()
+    assert ln.cpu().tolist() == [0] * batch and end.cpu().tolist() == [-1] * batch
+    p, q = (torch.softmax(x.double(), 1).numpy() for x in (lp, lq))
+    for b in range(batch):
+        cdf = np.cumsum(np.maximum(p[batch + b] - q[batch + b], 0))
+        x, target = int(bonus[b]), float(resample_u[b]) * cdf[-1]
+        assert (cdf[x - 1] if x else 0.0) - 2e-5 <= target <= cdf[x] + 2e-5 and p[batch + b][x] > 0
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("vocab", [5, 1000, 4096, 8200, 16384, 17001])
 def test_stochastic_many_sequences_equal_few(gpu, dtype, vocab):
     """More sequences than CUs take acceptance and draw as two kernels, with other segments in the general draw: the same
