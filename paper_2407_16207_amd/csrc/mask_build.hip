@@ -1,37 +1,41 @@
 // Visibility-mask builder: ancestor closure of the token graph, one work-group per sequence.
 //
 // Paper Section 4.1 lets a flattened token attend only to its ancestors; on the merged graph of Section 5.3
-// that set is the closure over all parent edges.  Rows live in LDS as packed 32-bit words and are relaxed
-//     row[i] <- bit(i) | OR_{p in parents(i)} row[p]
-// in data-flow order: a node takes its parents' rows as soon as they are final and publishes its own with a flag;
-// no work-group barrier inside the closure.  The chain of dependent layers is what the kernel's time consists of, and a
-// single wavefront issues one instruction every few cycles however few of its lanes are busy, so a node is not one lane
-// but a group of L lanes, one per 32-bit word of its row: a layer then costs a handful of instructions (each lane reads
-// one word per parent, ORs them and writes one word) instead of a row's worth.  A wavefront holds 64 / L nodes (a
-// "chunk"), the chunks are dealt round-robin to the work-group's wavefronts, and a wavefront takes its chunks in
-// ascending order.  Nodes are in topological order and only earlier nodes are ever waited for: the lowest unfinished
-// node is ready, and its wavefront is working either on its chunk or on an earlier one, whose nodes are all finished
-// or ready as well; so every poll loop ends.  It is bounded on top of that, so every wave leaves the kernel.
+// that set is the closure over all parent edges,
+//     row[i] = bit(i) | OR_{p in parents(i)} row[p].
+// Parents come before their children, so the matrix of rows is lower triangular; it is built in blocks of 64 x 64 bits, one
+// wavefront per column of blocks and one lane per row:
+//   the block on the diagonal   the closure of the edges that stay within 64 nodes, by Warshall's algorithm: node k's row is
+//                               final when it is its turn, and goes to every lane that has bit k (readlane, two or three
+//                               vector instructions for each of 64 steps);
+//   a block below it            what the parents outside the block's own 64 rows have in this column (read from LDS: a few
+//                               words per lane), spread over the rows by the diagonal block: row i takes it from every node j
+//                               that it descends from within its 64, handed out by readlane, nodes without such parents left out.
+// A wavefront needs the diagonal blocks of the others, and otherwise only words of its own column: one barrier in all, however
+// deep the graph.  Bound by latency: three round trips to memory (offsets, parent lists) and 0.5 us for the diagonal;
+// following the layers of the graph instead, one after the other with a flag per node, took 0.2 us for each of them.
+// Launches in a replayed graph, against that (us): 64 nodes in 8 layers 3.9 -> 2.9, 8 x 256 in 32 layers 9.3 -> 4.9, 32 x 512 in
+// 64 layers 19.3 -> 7.5; random graphs 77 nodes 3.5-5.1 -> 3.9, 8 x 512 15.6-19.9 -> 12.9; a chain of 512 101 -> 7.1.
 #include "gsd_internal.h"
 
 namespace gsd {
 
-constexpr int kEdgeCacheInts = 6144;   // per-sequence parent lists are staged in LDS when they fit
-constexpr int kMaskThreads = 512;
+constexpr int kEdgeCacheInts = 6144;   // parent lists with more than four entries somewhere are staged in LDS when they fit
 
+// W: words per row that are computed = wavefronts
 template <int W>
-__global__ __launch_bounds__(kMaskThreads) void build_mask_kernel(
+__global__ __launch_bounds__(64 * W) void build_mask_kernel(
     int32_t max_nodes, int32_t words_per_row, const int32_t *__restrict__ node_offsets,
     const int32_t *__restrict__ parent_offsets, const int32_t *__restrict__ parent_idx, uint64_t *__restrict__ mask,
     int32_t *__restrict__ dag_error_flag) {
-    constexpr int D = 2 * W;                                           // 32-bit words of a row
-    constexpr int L = D <= 2 ? 2 : D <= 4 ? 4 : D <= 8 ? 8 : 16;       // lanes of a node (a power of two)
-    constexpr int G = 64 / L;                                          // nodes of a wavefront's chunk
-    constexpr int kWaves = kMaskThreads / 64;
-    __shared__ __attribute__((aligned(16))) uint32_t rows[GSD_MAX_NODES_PER_SEQ * D];     // [n][D]
+    constexpr int kNodes = 64 * W;
+    constexpr uint32_t kNone = 0xffff;                       // no parent in an earlier block of rows
+    __shared__ uint64_t diagonal[kNodes];                    // word i / 64 of row i
+    __shared__ uint64_t outer[kNodes];                       // a node's first four parents in earlier blocks, 16 bits each
+    __shared__ uint64_t column[W][kNodes + 1];               // word w of the rows, by wavefront w; the last one stays 0
+    __shared__ int32_t offset[kNodes + 1];
+    __shared__ int32_t wave_more[W];
     __shared__ int32_t edge_cache[kEdgeCacheInts];
-    __shared__ int32_t off_cache[GSD_MAX_NODES_PER_SEQ + 1];
-    __shared__ int32_t done_at[GSD_MAX_NODES_PER_SEQ + 1];
 
     const int b = blockIdx.x;
     const int64_t base = node_offsets[b];
@@ -42,134 +46,156 @@ __global__ __launch_bounds__(kMaskThreads) void build_mask_kernel(
         bad = true;
     }
     if (n <= 0) return;
-    const int32_t e0 = parent_offsets[base];
-    const int32_t e1 = parent_offsets[base + n];
-    const bool cached = (e1 - e0) <= kEdgeCacheInts;
 
-    for (int i = threadIdx.x; i <= n; i += kMaskThreads) {
-        off_cache[i] = parent_offsets[base + i] - e0;
-        done_at[i] = i == n ? 1 : 0;                         // slot n: final from the start, what an absent parent reads
-    }
-    if (cached)
-        for (int e = threadIdx.x; e < e1 - e0; e += kMaskThreads) edge_cache[e] = parent_idx[e0 + e];
-    __syncthreads();
-
-    // parent e of this sequence, from the LDS copy or (sequences with more edges than the cache holds) from memory
-    auto edge_at = [&](int e) -> int { return cached ? edge_cache[e] : parent_idx[e0 + e]; };
-    // No instruction: the compiler keeps the LDS accesses before it before those after it, and reads LDS again after it.
-    auto in_this_order = [] { asm volatile("" ::: "memory"); };
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int d = lane % L;                                  // this lane's word of the row
-    const int slot = lane / L;                               // this lane's node within the chunk
+    const int i = threadIdx.x, lane = i & 63, w = __builtin_amdgcn_readfirstlane(i >> 6);
     constexpr int kRegParents = 4;
-    constexpr int kPollLimit = 1 << 16;
-    const int chunks = (n + G - 1) / G;
-    for (int c = wave; c < chunks; c += kWaves) {            // uniform per wavefront
-        const int i = c * G + slot;
-        const bool active = i < n && d < D;
-        // The first four parents live in registers as two indices each, so that a poll's reads carry no branches: an
-        // absent parent reads the node's own word, which holds nothing yet (OR-ing it in changes nothing), and slot n
-        // of done_at, which is final from the start.
-        int par_row[kRegParents], par_done[kRegParents];
-        int e_lo = 0, e_hi = 0;
+    int e_lo = 0, e_hi = 0;
+    if (i < n) {
+        e_lo = parent_offsets[base + i];
+        e_hi = parent_offsets[base + i + 1];
+        offset[i] = e_lo;
+        if (i == n - 1) offset[n] = e_hi;
+    }
+    const bool more = e_hi - e_lo > kRegParents;             // rare: a node with more than four parents
+    uint64_t own = i < n ? uint64_t(1) << lane : 0;
+    {
+        int par[kRegParents];
+#pragma unroll
+        for (int x = 0; x < kRegParents; ++x) par[x] = -1;
+        if (e_hi > e_lo) {
+#pragma unroll
+            for (int x = 0; x < kRegParents; ++x) par[x] = parent_idx[min(e_lo + x, e_hi - 1)];
+        }
+        uint64_t packed = 0;
+        auto take = [&](int p) {
+            if (p >= 0 && p < i) {
+                if (p >> 6 == w) own |= uint64_t(1) << (p & 63);
+            } else if (p != -1) {
+                bad = true;
+            }
+        };
 #pragma unroll
         for (int x = 0; x < kRegParents; ++x) {
-            par_row[x] = active ? i : 0;
-            par_done[x] = n;
+            const int p = e_lo + x < e_hi ? par[x] : -1;
+            take(p);
+            packed |= uint64_t(p >= 0 && p < 64 * w ? uint32_t(p) : kNone) << (16 * x);
         }
-        uint32_t mine = 0;
-        if (active) {
-            e_lo = off_cache[i];
-            e_hi = off_cache[i + 1];
+        outer[i] = packed;
+        constexpr int kBatch = 8;
+        for (int e0 = e_lo + kRegParents; e0 < e_hi; e0 += kBatch) {
+            int p[kBatch];
 #pragma unroll
-            for (int x = 0; x < kRegParents; ++x) {
-                if (e_lo + x < e_hi) {
-                    const int pp = edge_at(e_lo + x);
-                    if (pp >= 0 && pp < i) {
-                        par_row[x] = pp;
-                        par_done[x] = pp;
-                    } else if (pp != -1) {
-                        bad = true;
-                    }
-                }
-            }
-            mine = d == (i >> 5) ? 1u << (i & 31) : 0u;
-            rows[i * D + d] = 0;
-        }
-        const bool more = active && e_hi - e_lo > kRegParents;     // rare: a node with more than four parents
-        bool mine_done = !active;
-        for (int poll = 0; poll < kPollLimit; ++poll) {
-            if (!mine_done) {
-                // One batch of LDS reads per poll: the parents' flags, then, without waiting for them, this lane's
-                // word of the parents' rows.  The LDS unit serves a wavefront's instructions in the order they were
-                // issued (and the owner of a row writes the row before the flag), so a row word read after a flag that
-                // turned out to be set is final; if a flag was not set the words are thrown away.
-                in_this_order();
-                int fin[kRegParents];
+            for (int x = 0; x < kBatch; ++x) p[x] = parent_idx[min(e0 + x, e_hi - 1)];
 #pragma unroll
-                for (int x = 0; x < kRegParents; ++x) fin[x] = done_at[par_done[x]];
-                in_this_order();
-                uint32_t got = 0;
-#pragma unroll
-                for (int x = 0; x < kRegParents; ++x) got |= rows[par_row[x] * D + d];
-                bool ready = true;
-#pragma unroll
-                for (int x = 0; x < kRegParents; ++x) ready &= fin[x] != 0;
-                if (more) {
-                    for (int e = e_lo + kRegParents; e < e_hi; ++e) {
-                        const int pp = edge_at(e);
-                        if (pp >= 0 && pp < i) {
-                            in_this_order();
-                            const int f = done_at[pp];
-                            in_this_order();
-                            got |= rows[pp * D + d];
-                            ready &= f != 0;
-                        } else if (pp != -1) {
-                            bad = true;
-                        }
-                    }
-                }
-                if (ready) {
-                    mine |= got;
-                    rows[i * D + d] = mine;
-                    // The flag after the row: the lanes of a node take the same decision (same parents, and a flag
-                    // comes from one instruction for all of them), so all words of the row are written by the one
-                    // instruction above, and the flag by a later one.
-                    in_this_order();
-                    if (d == 0) done_at[i] = 1;
-                    in_this_order();
-                    mine_done = true;
-                }
-            }
-            if (__all(mine_done)) break;          // wave-uniform
-        }
-        if (!mine_done) {                         // poll limit reached (never, with the guarantees above): publish what
-            bad = true;                           // there is, so that nobody waits for this node for as long again
-            rows[i * D + d] = mine;
-            in_this_order();
-            if (d == 0) done_at[i] = 1;
-            in_this_order();
+            for (int x = 0; x < kBatch; ++x)
+                if (e0 + x < e_hi) take(p[x]);
         }
     }
-    __syncthreads();
 
-    // rows to memory, one 64-bit word per thread and turn; words that no node id can reach are zero
-    for (int x = threadIdx.x; x < n * words_per_row; x += kMaskThreads) {
-        const int i = x / words_per_row, w = x - i * words_per_row;
-        uint64_t v = 0;
-        if (w < W) v = uint64_t(rows[i * D + 2 * w]) | (uint64_t(rows[i * D + 2 * w + 1]) << 32);
-        mask[(base + i) * words_per_row + w] = v;
+    // The diagonal block.  Step k hands the row of lane k to the lanes that have bit k; rows of the lower half have no bits in
+    // the upper.
+    uint32_t lo = uint32_t(own), hi = uint32_t(own >> 32);
+    const int here = n - 64 * w;                             // rows of this block
+#pragma unroll
+    for (int k0 = 0; k0 < 32; k0 += 8) {
+        if (k0 >= here) break;                               // uniform
+#pragma unroll
+        for (int k = k0; k < k0 + 8; ++k) {
+            const uint32_t row = __builtin_amdgcn_readlane(lo, k);
+            lo |= row & uint32_t(__builtin_amdgcn_sbfe(int(lo), k, 1));
+        }
     }
+#pragma unroll
+    for (int k0 = 32; k0 < 64; k0 += 8) {
+        if (k0 >= here) break;
+#pragma unroll
+        for (int k = k0; k < k0 + 8; ++k) {
+            const uint32_t row_lo = __builtin_amdgcn_readlane(lo, k), row_hi = __builtin_amdgcn_readlane(hi, k);
+            const uint32_t has = uint32_t(__builtin_amdgcn_sbfe(int(hi), k - 32, 1));
+            lo |= row_lo & has;
+            hi |= row_hi & has;
+        }
+    }
+    own = lo | uint64_t(hi) << 32;
+    diagonal[i] = own;
+    column[w][i] = own;
+    const bool some_more = __any(more);                      // (in all lanes, or lane 0 speaks for itself only)
+    if (lane == 0) {
+        column[w][kNodes] = 0;
+        wave_more[w] = some_more;
+    }
+    uint64_t *const out = mask + base * words_per_row + w;
+    if (i < n) out[int64_t(i) * words_per_row] = own;
+    for (int j = lane; j < min(64 * w, n); j += 64) out[int64_t(j) * words_per_row] = 0;          // above the diagonal
+    for (int x = W + w; x < words_per_row; x += W)           // words that no node id can reach
+        for (int j = lane; j < n; j += 64) mask[(base + j) * words_per_row + x] = 0;
     if (bad && dag_error_flag) *dag_error_flag = 1;
+    const int blocks = (n + 63) / 64;
+    if (blocks == 1) return;                                 // uniform for the work-group
+    __syncthreads();
+    bool any_more = false;
+#pragma unroll
+    for (int x = 0; x < W; ++x) any_more |= wave_more[x] != 0;
+    int first = 0;
+    bool cached = false;
+    if (any_more) {                                          // uniform
+        first = offset[0];
+        const int edges = offset[n] - first;
+        cached = edges <= kEdgeCacheInts;
+        if (cached)
+            for (int e = threadIdx.x; e < edges; e += kNodes) edge_cache[e] = parent_idx[first + e];
+        __syncthreads();
+    }
+
+    // The blocks below the diagonal, downwards.
+    const uint64_t *const mine = column[w];
+    for (int c = w + 1; c < blocks; ++c) {
+        const int j = 64 * c + lane;
+        const uint64_t within = diagonal[j], packed = outer[j];
+        uint64_t ext = 0;
+#pragma unroll
+        for (int x = 0; x < kRegParents; ++x) {
+            const int p = int(packed >> (16 * x)) & int(kNone);
+            ext |= mine[p != int(kNone) && p >= 64 * w ? p : kNodes];
+        }
+        if (any_more && j < n) {
+            const int e_end = offset[j + 1];
+            for (int e = offset[j] + kRegParents; e < e_end; ++e) {
+                const int p = cached ? edge_cache[e - first] : parent_idx[e];
+                if (p >= 64 * w && p < 64 * c) ext |= mine[p];
+            }
+        }
+        uint32_t row_lo = 0, row_hi = 0;
+        const uint32_t ext_lo = uint32_t(ext), ext_hi = uint32_t(ext >> 32);
+        const uint64_t from = __ballot(ext != 0);
+        const uint32_t within_lo = uint32_t(within), within_hi = uint32_t(within >> 32);
+        // Eight nodes at a time: a layer of a graph is a run of nodes, and with the lanes as constants a node takes five vector
+        // instructions and no scalar ones (random graphs, where nearly all have such parents: 2.0 us for 64 nodes one by one).
+#pragma unroll
+        for (int k0 = 0; k0 < 64; k0 += 8) {
+            if (((from >> k0) & 0xff) == 0) continue;        // uniform
+#pragma unroll
+            for (int k = k0; k < k0 + 8; ++k) {
+                const uint32_t has = uint32_t(__builtin_amdgcn_sbfe(int(k < 32 ? within_lo : within_hi), k & 31, 1));
+                row_lo |= uint32_t(__builtin_amdgcn_readlane(ext_lo, k)) & has;
+                row_hi |= uint32_t(__builtin_amdgcn_readlane(ext_hi, k)) & has;
+            }
+        }
+        const uint64_t row = row_lo | uint64_t(row_hi) << 32;
+        column[w][j] = row;
+        // the other lanes of the wavefront read it in the next turn: the LDS unit takes its instructions in order
+        asm volatile("" ::: "memory");
+        if (j < n) out[int64_t(j) * words_per_row] = row;
+    }
 }
 
 hipError_t launch_build_mask(int32_t batch, int32_t max_nodes, int32_t words_per_row, const int32_t *node_offsets,
                              const int32_t *parent_offsets, const int32_t *parent_idx, uint64_t *mask,
                              int32_t *dag_error_flag, hipStream_t stream) {
-    const dim3 grid(batch), block(kMaskThreads);
+    const dim3 grid(batch);
 #define GSD_MASK_CASE(WORDS)                                                                                         \
     case WORDS:                                                                                                      \
-        hipLaunchKernelGGL(build_mask_kernel<WORDS>, grid, block, 0, stream, max_nodes, words_per_row, node_offsets,  \
+        hipLaunchKernelGGL(build_mask_kernel<WORDS>, grid, dim3(64 * WORDS), 0, stream, max_nodes, words_per_row, node_offsets,  \
                            parent_offsets, parent_idx, mask, dag_error_flag);                                        \
         break;
     // words computed per row: no node id reaches past word GSD_MAX_NODES_PER_SEQ/64 - 1, wider rows are zero-filled

@@ -120,6 +120,30 @@ def test_mask_and_accept_dense_dags(gpu, ref):
         assert np.array_equal(bonus.cpu().numpy(), wb)
 
 
+@pytest.mark.parametrize("n", [2, 63, 64, 65, 127, 129, 193, 257, 320, 449, 512])
+def test_mask_blocks_of_64(gpu, ref, n):
+    """Around the edges of the 64 x 64 blocks: parents within a block, in the one before and far back; no node with more than four
+    parents, exactly one (in any lane), and all of them; rows wider than they need to be."""
+    rng = np.random.default_rng(n)
+    for rep in range(6):
+        counts = np.ones(n, dtype=int) if rep < 5 else rng.integers(5, 9, n)
+        if 0 < rep < 5:
+            counts[:] = rng.integers(1, 5, n)
+            counts[n - 1 - rep * 11 % n] = 9
+        reach = [n, 3, 64, 70, n, 130][rep]
+        offsets, parents = [0], []
+        for i in range(n):
+            lo = max(0, i - reach)
+            pick = rng.choice(i - lo, min(counts[i], i - lo), replace=False) + lo if i else []
+            parents += sorted(int(x) for x in pick) or [-1]
+            offsets.append(len(parents))
+        w = custom_workload(rng, [n], [0], 1, 1, 64, "f32")
+        w.parent_offsets, w.parent_idx = np.array(offsets, dtype=np.int32), np.array(parents, dtype=np.int32)
+        words = (n + 63) // 64 + (rep % 3) * 5
+        got = gpu.mask_to_numpy(gpu.DeviceWorkload(w).build_mask(words_per_row=words))
+        assert np.array_equal(got, ref.build_mask(w.node_offsets, w.parent_offsets, w.parent_idx, words_per_row=words)[0]), rep
+
+
 def test_mask_bad_parent_sets_flag(gpu, ref):
     rng = np.random.default_rng(3)
     w = custom_workload(rng, [6], [0], 1, 1, 64, "f32")
