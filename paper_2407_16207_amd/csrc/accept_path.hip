@@ -3,9 +3,8 @@
 // An edge p -> i is accepted iff tokens[i] equals the LLM's choice after p (pred[p], or root_pred for the
 // root); the first mismatch on a hypothesis discards everything after it, and the longest accepted path from
 // the root is taken.  One work-group per sequence: L[i] (nodes on the longest accepted root path ending at i,
-// -1 if none) is relaxed over all nodes in parallel until it stops changing (at most depth+1 sweeps because
-// the nodes are in topological order; hard bound = node count), then the best end node is reduced and one
-// thread walks the back-pointers.  Ties: smallest end node id, then the smallest-id qualifying parent.
+// -1 if none) is relaxed over all nodes in parallel until it stops changing (hard bound = node count), then the best end
+// node is reduced and one thread walks the back-pointers.  Ties: smallest end node id, then the smallest-id qualifying parent.
 #include "gsd_internal.h"
 
 namespace gsd {
@@ -24,6 +23,7 @@ __global__ __launch_bounds__(THREADS) void accept_kernel(
     __shared__ int32_t back_s[THREADS];
     __shared__ int32_t edge_s[kAcceptEdgeCache];
     __shared__ uint32_t wave_best[THREADS / 64];
+    __shared__ int32_t grew_s[3];                  // of a round of the relaxation: some L has grown
     __shared__ int32_t len_s;
 
     const int b = blockIdx.x;
@@ -58,6 +58,7 @@ __global__ __launch_bounds__(THREADS) void accept_kernel(
             for (int x = 0; x < kRegParents; ++x) par[x] = parent_idx[min(e_lo + x, e_hi - 1)];
         }
     }
+    if (i < 3) grew_s[i] = 0;
     __syncthreads();
     if (active) {
 #pragma unroll
@@ -96,30 +97,48 @@ __global__ __launch_bounds__(THREADS) void accept_kernel(
             each_further(f);
     };
 
+    // L only grows and whatever is read is the length of a path that exists, so a wavefront follows its own nodes until
+    // they rest or for a few steps, and the wavefronts then meet to find out whether all rest (one alone does not have to meet).
+    // A wavefront that has to look at further parents takes one step at a time.  Launches in a replayed graph, against a sweep
+    // with a barrier and a reduction for every step (us): 64 nodes 3.2-5.3 -> 3.1-4.65, 8 x 256 of <= 3 parents 5.2-8.7 -> 4.7-6.6,
+    // 32 x 512 6.7-10.8 -> 5.8-9.2 (the longer times: paths of more than a dozen nodes are accepted).
+    constexpr bool kAlone = THREADS == 64;
+    const int steps = kAlone ? n + 1 : __any(more) ? 1 : 4;
     int32_t mine = -1;             // L[i]
-    for (int sweep = 0; sweep <= n; ++sweep) {
-        int changed = 0;
-        if (active) {
-            int32_t best = mine;
+    for (int round = 0; round <= n; ++round) {
+        bool grew = false;
+        for (int step = 0; step < steps; ++step) {
+            bool up = false;
+            if (active) {
+                int32_t best = mine;
 #pragma unroll
-            for (int x = 0; x < kRegParents; ++x) {
-                const int32_t l = L[par[x] >= 0 ? par[x] : i];
-                const int32_t lp = par[x] >= 0 ? l : (par[x] == -1 ? 0 : -1);
-                if (lp >= 0 && lp + 1 > best) best = lp + 1;
-            }
-            if (more) {
-                each_accepted([&](int p) {
-                    const int32_t lp = (p == -1) ? 0 : L[p];
+                for (int x = 0; x < kRegParents; ++x) {
+                    const int32_t l = __hip_atomic_load(&L[par[x] >= 0 ? par[x] : i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    const int32_t lp = par[x] >= 0 ? l : (par[x] == -1 ? 0 : -1);
                     if (lp >= 0 && lp + 1 > best) best = lp + 1;
-                });
+                }
+                if (more) {
+                    each_accepted([&](int p) {
+                        const int32_t lp = p == -1 ? 0 : __hip_atomic_load(&L[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        if (lp >= 0 && lp + 1 > best) best = lp + 1;
+                    });
+                }
+                up = best != mine;
+                if (up) {
+                    mine = best;
+                    __hip_atomic_store(&L[i], best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
             }
-            if (best != mine) {
-                mine = best;
-                L[i] = best;
-                changed = 1;
-            }
+            if (!__any(up)) break;
+            grew = true;
         }
-        if (!__syncthreads_or(changed)) break;
+        if (kAlone) break;
+        // three flags in turn: one is written, one read, and the one that everybody has read is cleared
+        const int at = round % 3;
+        if (grew) grew_s[at] = 1;
+        __syncthreads();
+        if (i == 0) grew_s[(round + 2) % 3] = 0;
+        if (grew_s[at] == 0) break;
     }
 
     // back pointer of every accepted node: the smallest-id accepted parent that ends a path one node shorter
