@@ -59,6 +59,13 @@ __device__ __forceinline__ void dma16_at(const void *gbase, uint32_t voff, uint3
     asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0"
                  :: "s"(gbase), "v"(voff), "s"(lds_base), "i"(lds_const) : "memory", "scc");
 }
+// From any address per lane, 16 or 4 bytes of it; lane l's land at lds_base + 16*l or + 4*l.
+__device__ __forceinline__ void dma16_from(const void *at, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(at), "s"(lds_base) : "memory");
+}
+__device__ __forceinline__ void dma4_from(const void *at, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" :: "v"(at), "s"(lds_base) : "memory");
+}
 template <int N> __device__ __forceinline__ void dma_wait() {   // at most N vector-memory operations in flight
     asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 }

@@ -13,13 +13,16 @@
 // The matrix-core mapping, the swizzles and the copies are those of dag_attention_bf16.hip.  The code is kept small on
 // purpose (one rolled loop, a real running maximum instead of the guessed offset and its repair path).
 //
-// What bounds it: a CU takes in K/V tiles at 45-50 bytes per ns, whatever is done with them (a step of 64 KB takes
-// 1.3-1.4 us with one row group and with two; tiles held in registers instead of LDS, three per wavefront on their way,
-// take the same), and ~6.5 us around the loop: 1.0 until the sequence's offsets are there, 0.6 to issue the first
-// copies, 1.4 until they and the queries have arrived, 1.8 to merge and store.  Hence two row groups at head_dim 128, where
-// 64 rows share a tile and its bytes; at head_dim 64 one, of which two work-groups fit a CU (with two row groups the best
-// plan over 1000 shapes would be 0.9 % faster).
-// Against the better of the other kernel's shapes (merge kernel included, best split count for each): 5 ragged sequences
+// What bounds it: the latency of memory, paid about 1 us at a time, and where the K/V tiles come from (a CU takes in 133 bytes
+// per ns from its L2 and all of them together 7 TB/s from the last-level cache).  32 heads of 64 rows over 1088 keys, three splits
+// (us inside the kernel): 1.0 until the sequence's offsets are there, 1.3 until all first copies have left, 0.3 until the
+// queries have arrived, three steps of 1.0, 0.85 and 0.7 (64 KB each; 1.35 when a step's copies were issued at the start of the step
+// before and awaited together), 1.5 to merge and store.  Launch with its merge kernel 14.0 -> 12.3, 24 heads of 64 channels over 5
+// ragged sequences of 231 rows 13.9 -> 12.0, 90 rows x 16 heads over 1490 keys 14.1 -> 12.5, a few rows over short contexts 1.1-1.2 times
+// as fast.
+// Two row groups at head_dim 128 let 64 rows share a tile; at head_dim 64 one row group, of which two work-groups fit a CU (with
+// two the best plan over 1000 shapes would be 0.9 % faster).
+// Against the better of the other kernel's shapes, before the copies were reordered (merge kernel included, best split count for each): 5 ragged sequences
 // of 231 rows, head_dim 64, 15.1 against 17.1 us; 32 heads of 20 rows over 320 keys 9.3-10.0 against 11.6; 192 groups of
 // 20 rows, head_dim 64, 10.0 against 13.0; 8 groups of 128 rows over 1056 keys 13.9 against 15.8; behind it from about
 // 256 work-groups of 64 rows on (128 groups of 512 rows over 1500 keys 57 against 38).
@@ -28,24 +31,39 @@
 namespace gsd {
 
 template <int D, int RG>
-__global__ __launch_bounds__(RG * 256, RG) void dag_attention_bf16_keys_kernel(const AttnParams p) {
-    constexpr int KG = 4;
+struct KeysLds {
+    static constexpr int kKeyGroups = 4;
+    static constexpr int kRows = RG * 32;
+    static constexpr int kTile = 32 * D * 2;                               // bytes of a K or V tile
+    static constexpr int kStage = kKeyGroups * 2 * kTile;                  // bytes of a step's tiles
+    static constexpr int kOut = kKeyGroups * kRows * D * 4;                // the outputs to be merged take the place of the tiles
+    static constexpr int kQ = kOut > 2 * kStage ? kOut : 2 * kStage;       // this step's tiles and the next; then the queries
+    static constexpr int kMask = kQ + kRows * D * 2;                       // then the tile's mask words, 16 of 32 bits per node
+    static constexpr int kMaskWords = GSD_MAX_NODES_PER_SEQ / 32;
+    static constexpr int kTotal = kMask + kRows * kMaskWords * 4;
+};
+
+// The LDS is dynamic: from a static size that leaves room for one wave per SIMD the compiler concludes that a wave may have 512
+// registers, and then keeps the scores in accumulator registers (32 to 64 moves a step).
+template <int D, int RG>
+__global__ __launch_bounds__(RG * 256, 2) void dag_attention_bf16_keys_kernel(const AttnParams p) {
+    using L = KeysLds<D, RG>;
+    constexpr int KG = L::kKeyGroups;
     constexpr int NW = RG * KG;
-    constexpr int ROWS = RG * 32;
+    constexpr int ROWS = L::kRows;
     constexpr int KS = D / 16;                     // k-steps of S^T = K Q^T
     constexpr int MBD = D / 32;                    // 32-channel blocks of O^T
     constexpr int RB = D * 2;                      // bytes of a K or V row
     constexpr int CHUNKS = D / 8;                  // 16-byte chunks of a row
-    constexpr int TB = 32 * RB;                    // bytes of a K or V tile
-    constexpr int STAGE = KG * 2 * TB;             // bytes of a step's tiles
+    constexpr int TB = L::kTile;
+    constexpr int STAGE = L::kStage;
     static_assert(D == 128 || RG == 1, "");
     constexpr int RPI = 1024 / RB;                 // rows per wavefront-wide copy
     constexpr int CPW = TB / 1024 / RG;            // copies of K (and of V) per wavefront and step
-    constexpr int MW = GSD_MAX_NODES_PER_SEQ / 64 + 2;     // mask words of a row in LDS, one more on either side
-    static_assert(CPW >= 1, "");
-    constexpr int OUT = NW * 32 * D * 4;           // the outputs to be merged take the place of the tiles
-    __shared__ __attribute__((aligned(1024))) char lds[OUT > 2 * STAGE ? OUT : 2 * STAGE];   // this step and the next
-    __shared__ uint64_t mask_lds[ROWS][MW];
+    constexpr int QPW = ROWS * RB / 1024 / NW;     // copies of the queries per wavefront
+    constexpr int MPW = ROWS * L::kMaskWords / 64 / NW;    // and of the mask words, 4 bytes per lane
+    static_assert(CPW >= 1 && QPW >= 1 && MPW >= 1, "");
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
     __shared__ float m_lds[NW * 32], l_lds[NW * 32];
     auto k_swz = [](int m) __attribute__((always_inline)) -> int { return D == 128 ? (m & 15) : ((m >> 1) & 7); };
 
@@ -84,15 +102,19 @@ __global__ __launch_bounds__(RG * 256, RG) void dag_attention_bf16_keys_kernel(c
     const int m0 = rg * CPW * RPI + lane / CHUNKS;             // row position in the tile that copy 0 fills
     const int slot = lane % CHUNKS;
     const uint32_t v_chunk = uint32_t((slot ^ ((CHUNKS / 4) * (m0 & 3))) & (CHUNKS - 1)) * 16u;
-    auto copy_step = [&](int s, int buf) __attribute__((always_inline)) {
+    auto copy_k = [&](int s) __attribute__((always_inline)) {
         const int first = (s * KG + kg) * 32;
-        const uint32_t to = wave_lds + buf * STAGE;
+        const uint32_t to = wave_lds + (s & 1) * STAGE;
 #pragma unroll
         for (int j = 0; j < CPW; ++j) {
             const int m = m0 + j * RPI;
             const uint32_t r = uint32_t(min(first + k_lds_row(m), keys - 1));
             dma16_at(k_seq, __umul24(r, row_stride) + uint32_t(slot ^ k_swz(m)) * 16u, to, j * 1024);
         }
+    };
+    auto copy_v = [&](int s) __attribute__((always_inline)) {
+        const int first = (s * KG + kg) * 32;
+        const uint32_t to = wave_lds + (s & 1) * STAGE;
 #pragma unroll
         for (int j = 0; j < CPW; ++j) {
             const uint32_t r = uint32_t(min(first + m0 + j * RPI, keys - 1));
@@ -100,27 +122,33 @@ __global__ __launch_bounds__(RG * 256, RG) void dag_attention_bf16_keys_kernel(c
         }
     };
     static_assert(RPI % 4 == 0, "v_chunk is the same for all copies of a wavefront");
-    if (s_begin < s_end) copy_step(s_begin, 0);
 
-    // ---- queries and mask words, while the first tiles are on their way ----------------------------------------
-    const int32_t my_row = min(row0 + rg * 32 + col, rows_total - 1);
-    const int32_t my_node = my_row / G;
-    const __bf16 *qp = p.q + (int64_t(node_base) + my_node) * p.q_ts + int64_t(kvh * G + my_row - my_node * G) * p.q_hs + 8 * half;
-    bf16x8 qf[KS];
+    // ---- queries and mask words: the same way, ahead of the first V tile ----------------------------------------------
+    // Loaded into registers they would be awaited by the compiler, which does not count the copies and would wait for all of
+    // them.  Queries lie like K rows, chunk x of row r in slot x ^ k_swz(r); of the mask the words of the tile's nodes.
+    const int32_t first_node = row0 / G, last_node = min(row0 + ROWS - 1, rows_total - 1) / G;
+    if (s_begin < s_end) {
+        copy_k(s_begin);                           // first: the addresses of the others take a while
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(qp + ks * 16);
-    // Word 0 of a row in LDS stands for the 64 keys before draft node 0 (prefix: visible), word 1+w for mask word w with
-    // the bits at and beyond n cleared; what lies beyond is 0.
-    for (int x = threadIdx.x; x < ROWS * MW; x += NW * 64) {
-        const int row = x / MW, w = x - row * MW - 1;
-        const int32_t node = min(row0 + row, rows_total - 1) / G;
-        uint64_t word = 0;
-        if (w >= 0 && w * 64 < n) {
-            word = p.mask[(int64_t(node_base) + node) * p.words_per_row + w];
-            if (n - w * 64 < 64) word &= (uint64_t(1) << (n - w * 64)) - 1;
+        for (int j = 0; j < QPW; ++j) {
+            const int m = (wave * QPW + j) * RPI + lane / CHUNKS;
+            const int32_t r = min(row0 + m, rows_total - 1), node = r / G;
+            dma16_from(p.q + (int64_t(node_base) + node) * p.q_ts + int64_t(kvh * G + r - node * G) * p.q_hs + (slot ^ k_swz(m)) * 8,
+                       lds_base + L::kQ + (wave * QPW + j) * 1024);
         }
-        mask_lds[row][w + 1] = w < 0 ? ~uint64_t(0) : word;
+#pragma unroll
+        for (int j = 0; j < MPW; ++j) {
+            const int x = (wave * MPW + j) * 64 + lane;
+            const int32_t node = min(first_node + x / L::kMaskWords, last_node);
+            const int word = min(x % L::kMaskWords, 2 * p.words_per_row - 1);
+            dma4_from(reinterpret_cast<const uint32_t *>(p.mask + (int64_t(node_base) + node) * p.words_per_row) + word,
+                      lds_base + L::kMask + (wave * MPW + j) * 256);
+        }
+        copy_v(s_begin);
+        if (RG == 1 && s_begin + 1 < s_end) copy_k(s_begin + 1);
     }
+    const int32_t my_row = min(row0 + rg * 32 + col, rows_total - 1);
+    const uint32_t *my_mask = reinterpret_cast<const uint32_t *>(lds + L::kMask) + (my_row / G - first_node) * L::kMaskWords;
 
     floatx16 acc[MBD];
 #pragma unroll
@@ -143,30 +171,66 @@ __global__ __launch_bounds__(RG * 256, RG) void dag_attention_bf16_keys_kernel(c
 #pragma unroll
         for (int x = 0; x < MBD; ++x) v_off[x] = (v0 ^ uint32_t(x * 64)) + uint32_t(kg * 2 * TB + TB);
     }
-    const uint32_t *my_mask = reinterpret_cast<const uint32_t *>(mask_lds[rg * 32 + col]);
-    // The queries have to be here before the loop: the compiler does not count the copies, and a wait of its own for the
-    // queries inside the loop would wait for the copies just issued.
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]));
-
-    int buf = 0;
-    for (int s = s_begin; s < s_end; ++s) {
-        // This step's tiles have landed and every wavefront is done with the step before, whose buffer is filled again.
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    bf16x8 qf[KS];
+    if (s_begin < s_end) {
+        // the queries, the mask words and the first K tile are older than the copies that may stay in flight
+        if (RG == 1 && s_begin + 1 < s_end) dma_wait<2 * CPW>();
+        else dma_wait<CPW>();
         wg_barrier();
-        if (s + 1 < s_end) copy_step(s + 1, buf ^ 1);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(lds + L::kQ + rg * 32 * RB + (k_off[ks] - kg * 2 * TB));
+    }
+
+    // Step s: scores from K(s), then P.V from V(s).
+    // With one row group a tile belongs to one wavefront, which has nobody to meet: V(s+1) is fetched from the top of the step
+    // on, K(s+2) from where K(s) has been read, so that one and a half to two steps' tiles are on their way at any time.
+    // With two, two wavefronts copy a half of a tile each and read both, and share a SIMD with two others: one barrier a step, at
+    // which the whole next step is fetched (the finer order above with its two barriers took 7 % longer).
+    for (int s = s_begin; s < s_end; ++s) {
+        const bool more = s + 1 < s_end;
+        if (RG > 1) dma_wait<0>();                               // K(s) and V(s) have landed
+        else if (more) dma_wait<2 * CPW>();                      // K(s) has; behind it V(s) and K(s+1) may be on their way
+        else dma_wait<CPW>();
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the tiles of step s-1 have been read
+        if (RG > 1) wg_barrier();
+        if (RG > 1 && more) copy_k(s + 1);
+        if (more) copy_v(s + 1);
         const int first = (s * KG + kg) * 32;
         uint32_t bits = ~0u;
         if (first + 32 > P) {                      // uniform: the tile reaches into the draft nodes
-            const int32_t pos = first - P;         // its first key's draft node; below 0: prefix
-            const int32_t w = min((pos + 64) >> 5, 2 * MW - 2);
-            bits = uint32_t(((uint64_t(my_mask[w + 1]) << 32) | my_mask[w]) >> (pos & 31));
+            const int32_t pos = first - P;         // its first key's draft node; below 0: prefix, 32 visible keys
+            const int32_t w = min((pos + 32) >> 5, L::kMaskWords), left = n - pos;
+            const uint32_t lo = w == 0 ? ~0u : my_mask[w - 1], hi = my_mask[min(w, L::kMaskWords - 1)];
+            bits = uint32_t(((uint64_t(hi) << 32) | lo) >> (pos & 31));
+            if (left < 32) bits &= left > 0 ? (1u << left) - 1 : 0u;
         }
-        if (__any(bits != 0)) {                    // uniform; else no row of the wavefront sees a key of the tile
-            const char *tile = lds + buf * STAGE;
-            bf16x8 kf[KS], vf[2][MBD];
+        const bool seen = __any(bits != 0);        // uniform; else no row of the wavefront sees a key of the tile
+        const char *tile = lds + (s & 1) * STAGE;
+        floatx16 sc;
+        if (seen) {
+            bf16x8 kf[KS];
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) kf[ks] = *reinterpret_cast<const bf16x8 *>(tile + k_off[ks]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) sc[j] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], sc, 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (RG == 1) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // K(s) has been read
+            if (s + 2 < s_end) {
+                copy_k(s + 2);
+                dma_wait<3 * CPW>();               // V(s) has landed; behind it K(s+1), V(s+1), K(s+2)
+            } else if (more) {
+                dma_wait<2 * CPW>();
+            } else {
+                dma_wait<0>();
+            }
+        }
+        if (seen) {
+            bf16x8 vf[2][MBD];
             auto read_v = [&](int ks2) __attribute__((always_inline)) {
 #pragma unroll
                 for (int x = 0; x < MBD; ++x) {
@@ -178,12 +242,6 @@ __global__ __launch_bounds__(RG * 256, RG) void dag_attention_bf16_keys_kernel(c
                     vf[ks2][x] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
                 }
             };
-            __builtin_amdgcn_sched_barrier(0);
-            floatx16 sc;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) sc[j] = 0.f;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], sc, 0, 0, 0);
             read_v(0);
             read_v(1);
             __builtin_amdgcn_sched_barrier(0);
@@ -222,7 +280,6 @@ __global__ __launch_bounds__(RG * 256, RG) void dag_attention_bf16_keys_kernel(c
                 for (int x = 0; x < MBD; ++x)
                     acc[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks2][x], __builtin_bit_cast(bf16x8, pf[ks2]), acc[x], 0, 0, 0);
         }
-        buf ^= 1;
     }
 
     // ---- merge of the KG states of every row ------------------------------------------------------------------
@@ -299,10 +356,12 @@ __global__ __launch_bounds__(RG * 256, RG) void dag_attention_bf16_keys_kernel(c
 hipError_t launch_attention_bf16_keys(const AttnParams &p, int head_dim, int row_groups, hipStream_t stream) {
     const dim3 grid((unsigned)(p.wg_per_xcd * 8)), block(row_groups * 256);
     if (head_dim == 128) {
-        if (row_groups == 1) hipLaunchKernelGGL((dag_attention_bf16_keys_kernel<128, 1>), grid, block, 0, stream, p);
-        else hipLaunchKernelGGL((dag_attention_bf16_keys_kernel<128, 2>), grid, block, 0, stream, p);
+        if (row_groups == 1)
+            hipLaunchKernelGGL((dag_attention_bf16_keys_kernel<128, 1>), grid, block, (KeysLds<128, 1>::kTotal), stream, p);
+        else
+            hipLaunchKernelGGL((dag_attention_bf16_keys_kernel<128, 2>), grid, block, (KeysLds<128, 2>::kTotal), stream, p);
     } else {
-        hipLaunchKernelGGL((dag_attention_bf16_keys_kernel<64, 1>), grid, block, 0, stream, p);
+        hipLaunchKernelGGL((dag_attention_bf16_keys_kernel<64, 1>), grid, block, (KeysLds<64, 1>::kTotal), stream, p);
     }
     return hipGetLastError();
 }

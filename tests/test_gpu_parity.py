@@ -314,6 +314,18 @@ def test_attention_bf16_few_rows(gpu, ref, hq, hkv, D, splits):
                     num_splits=splits)
 
 
+@pytest.mark.parametrize("hq,hkv,D", [(1, 1, 128), (3, 1, 128), (5, 1, 64), (8, 2, 128)])
+@pytest.mark.parametrize("splits", [0, 2])
+def test_attention_bf16_few_rows_prefixes_of_every_length(gpu, ref, hq, hkv, D, splits):
+    """The prefix ends at every position of a 128-key step, and the graph at the edges of mask words: the words of a tile that
+    reaches into the draft nodes are shifted together from two, ones before the first and nothing behind the last."""
+    rng = np.random.default_rng(10 * hq + D + splits)
+    prefixes = list(range(130)) + [0, 31, 32, 127, 128]
+    sizes = [int(rng.choice([1, 2, 31, 32, 33, 63, 64, 65])) for _ in range(130)] + [512, 511, 481, 480, 449]
+    w = custom_workload(rng, sizes, prefixes, hq, hkv, D, "bf16")
+    check_attention(gpu, ref, w, num_splits=splits)
+
+
 @pytest.mark.parametrize("hq,hkv,D", [(8, 8, 128), (4, 2, 128), (16, 4, 128), (3, 3, 64), (8, 2, 64)])
 @pytest.mark.parametrize("sizes,prefixes", [([64, 40, 33], [1500, 900, 2100]), ([63, 64, 65, 1], [2500, 1900, 100, 0]),
                                             ([20, 31, 32], [4000, 3777, 130])])
