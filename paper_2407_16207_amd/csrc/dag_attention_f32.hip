@@ -26,6 +26,11 @@
 // 32-row tiles (every K/V operand used twice) need 232 registers and lose more to the coarser split: 51 and 54 us.
 // With a workspace the keys are also split over work-groups where the tiles leave CUs idle (attention_f32_splits), merged
 // by the kernel that merges the bf16 splits: the 128 tiles above then take 23.5 us, merge included.
+// Since then a turn of the four wavefronts (16 keys each) takes 1.47 us instead of 1.73, 0.9 of them its matrix instructions: K operands
+// read from LDS a pair ahead, 32-bit offsets to scalar bases, rows moved to a new maximum only where it exceeds the old by
+// 2^3, first tiles fetched ahead of the mask words.  The same case 24.6 -> 23.1 us (replayed), 64 heads of 16 nodes over 1852 keys, 3
+// sequences, 31.7 -> 27.5, 8 of 319 rows over 1238 keys 33.2 -> 30.3; 50 random shapes 0.995-1.155 times as fast; the relative
+// error against 64 bits is what it was (2.0-3.4e-7 over 14 shapes, each within 0.5 % of before).
 #include "attention_bf16.h"
 
 namespace gsd {
@@ -67,7 +72,9 @@ __device__ __forceinline__ float sum_across_groups(float x) {
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-template <int D>
+// Offset: type of the byte offsets within a run of 16 K/V rows.  32 bits let the loads take their base from scalar registers (64-bit
+// offsets cost two registers and an addition per load); row strides that do not fit get 64.
+template <int D, typename Offset>
 __global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(const F32Params p) {
     constexpr int NW = kF32Waves;
     constexpr int KV4 = D / 16;           // float4 loads of a K row fragment (4 channels per lane and load)
@@ -107,27 +114,28 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(co
     const float *kv_base_k = p.k + kv_row0 * p.kv_ts + kvh * p.kv_hs, *kv_base_v = p.v + kv_row0 * p.kv_ts + kvh * p.kv_hs;
     const int k_row = lane / CHUNKS, k_chunk = lane % CHUNKS;
     floatx4 ks[KV4], vf[4][VV4];
-    int64_t k_off[KV4], v_off[4];                        // element offsets from the tile's first row
+    Offset k_off[KV4], v_off[4];                         // bytes from the tile's first row
+    const Offset row_bytes = Offset(p.kv_ts * 4);
     auto set_offsets = [&](int last) __attribute__((always_inline)) {     // rows past `last` repeat it
 #pragma unroll
-        for (int j = 0; j < KV4; ++j) k_off[j] = int64_t(min(j * KROWS + k_row, last)) * p.kv_ts + 4 * k_chunk;
+        for (int j = 0; j < KV4; ++j) k_off[j] = Offset(min(j * KROWS + k_row, last)) * row_bytes + 16 * k_chunk;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) v_off[r] = int64_t(min(4 * kg + r, last)) * p.kv_ts + 4 * col;
+        for (int r = 0; r < 4; ++r) v_off[r] = Offset(min(4 * kg + r, last)) * row_bytes + 16 * col;
     };
     set_offsets(15);
     auto load_k = [&](int tile) __attribute__((always_inline)) {          // past the last tile: loads that nothing waits for
         const int t = min(tile, tiles - 1);
         if (t * 16 + 16 > keys) set_offsets(keys - 1 - t * 16);           // uniform; no full tile comes after it
-        const float *base = kv_base_k + int64_t(t) * 16 * p.kv_ts;
+        const char *base = reinterpret_cast<const char *>(kv_base_k + int64_t(t) * 16 * p.kv_ts);
 #pragma unroll
         for (int j = 0; j < KV4; ++j) ks[j] = *reinterpret_cast<const floatx4 *>(base + k_off[j]);
     };
     auto load_v = [&](int tile) __attribute__((always_inline)) {          // after load_k of the same tile
-        const float *base = kv_base_v + int64_t(min(tile, tiles - 1)) * 16 * p.kv_ts;
+        const char *base = reinterpret_cast<const char *>(kv_base_v + int64_t(min(tile, tiles - 1)) * 16 * p.kv_ts);
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int t = 0; t < VV4; ++t) vf[r][t] = *reinterpret_cast<const floatx4 *>(base + v_off[r] + 64 * t);
+            for (int t = 0; t < VV4; ++t) vf[r][t] = *reinterpret_cast<const floatx4 *>(base + v_off[r] + 256 * t);
     };
     floatx4 *my_k = reinterpret_cast<floatx4 *>(o_lds) + wave * 16 * CHUNKS;
     auto store_k = [&]() __attribute__((always_inline)) {
@@ -137,6 +145,9 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(co
             my_k[r * CHUNKS + (k_chunk ^ r)] = ks[j];
         }
     };
+
+    load_k(first + wave);                                // ahead of the mask words, which are waited for on their way into LDS
+    load_v(first + wave);
 
     // Sums in two levels, or their rounding errors would grow with the length of the context: the running ones take
     // kFold tiles and are then added to the totals.
@@ -166,10 +177,17 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(co
         if (w == 0) mask_lds[row][0] = ~uint64_t(0);     // the keys before draft node 0: the end of the prefix
     }
     const float c = p.scale_log2e;
-    load_k(first + wave);
-    load_v(first + wave);
     store_k();
     __syncthreads();
+
+    // K operands are read from LDS one pair of 16-channel groups ahead of the matrix instructions that take them, the first pair of a
+    // run behind the stores of the run before.
+    floatx4 kf[2][2];
+    auto read_k = [&](int pair) __attribute__((always_inline)) {
+#pragma unroll
+        for (int x = 0; x < 2; ++x) kf[pair & 1][x] = my_k[col * CHUNKS + ((4 * (2 * pair + x) + kg) ^ col)];
+    };
+    read_k(0);
 
     int left = kFold;                                    // tiles until the next fold
     bool spoiled = false;                                // uniform: a V element that is no finite number was left out
@@ -178,13 +196,15 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(co
         __builtin_amdgcn_sched_barrier(0);
         floatx4 s = {0.f, 0.f, 0.f, 0.f}, s_odd = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int t = 0; t < KV4; ++t) {
-            const floatx4 kf = my_k[col * CHUNKS + ((4 * t + kg) ^ col)];
+        for (int pair = 0; pair < KV4 / 2; ++pair) {
+            if (pair + 1 < KV4 / 2) read_k(pair + 1);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                floatx4 &sum = t & 1 ? s_odd : s;
-                sum = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[e], qf[t][e], sum, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[pair & 1][0][e], qf[2 * pair][e], s, 0, 0, 0);
+                s_odd = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[pair & 1][1][e], qf[2 * pair + 1][e], s_odd, 0, 0, 0);
             }
+            __builtin_amdgcn_sched_barrier(0);
         }
         s += s_odd;
         if (tile * 16 + 16 > P) {                        // uniform: the tile reaches into the draft nodes
@@ -200,7 +220,9 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(co
         }
         const float mx = max_across_groups(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
         const float m_new = fmaxf(m, mx * c);
-        if (__any(m_new > m)) {                  // uniform: some row of the tile has a new maximum
+        // Rows are moved to a new maximum when some row's scores exceed the old by 2^3: probabilities up to 8 lose nothing, and
+        // with 16 rows there is a new maximum in most tiles, 66 multiplications each.
+        if (__any(m_new > m + 3.f)) {            // uniform
             const float alpha = __builtin_amdgcn_exp2f(m - m_new);
             l *= alpha;
             l_total *= alpha;
@@ -245,6 +267,7 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(co
             for (int cb = 0; cb < CB; ++cb)
                 acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][cb / 4][cb % 4], s[r], acc[cb], 0, 0, 0);
         store_k();
+        read_k(0);
         load_v(tile + NW);
         if (--left == 0) {                               // uniform
             fold();
@@ -374,8 +397,14 @@ hipError_t launch_attention_f32(const gsd_attn_desc &d, int splits, hipStream_t 
     p.part_o = splits > 1 ? (float *)d.workspace : nullptr;
     p.part_ml = splits > 1 ? p.part_o + splits * p.part_rows * d.head_dim : nullptr;
     const dim3 grid((unsigned)((p.groups + 7) / 8 * 8 * p.row_tiles * splits)), block(kF32Waves * 64);
-    if (d.head_dim == 64) hipLaunchKernelGGL(dag_attention_f32_kernel<64>, grid, block, 0, stream, p);
-    else hipLaunchKernelGGL(dag_attention_f32_kernel<128>, grid, block, 0, stream, p);
+    const bool near = p.kv_ts < (int64_t(1) << 25);      // 15 rows stay below 2^31 bytes
+    if (d.head_dim == 64) {
+        if (near) hipLaunchKernelGGL((dag_attention_f32_kernel<64, uint32_t>), grid, block, 0, stream, p);
+        else hipLaunchKernelGGL((dag_attention_f32_kernel<64, int64_t>), grid, block, 0, stream, p);
+    } else {
+        if (near) hipLaunchKernelGGL((dag_attention_f32_kernel<128, uint32_t>), grid, block, 0, stream, p);
+        else hipLaunchKernelGGL((dag_attention_f32_kernel<128, int64_t>), grid, block, 0, stream, p);
+    }
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess || splits <= 1) return err;
     AttnParams c = {};                                   // what the merge kernel reads

@@ -391,6 +391,29 @@ def test_attention_fp32_strided_layouts(gpu, D, splits):
     assert torch.equal(out, base) and torch.equal(lse, base_lse) and (o_all[:, :, D:] == 7.0).all()
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_attention_fp32_rows_far_apart(gpu, D):
+    """Row strides up to and beyond 2^25 elements (128 MiB), where offsets within a run of 16 rows no longer fit 32 bits: the
+    same bits as with the rows side by side."""
+    import paper_2407_16207_amd as gsd
+    w = custom_workload(np.random.default_rng(D), [5], [18], 2, 2, D, "f32")
+    d = gpu.DeviceWorkload(w)
+    mask = d.build_mask()
+
+    def attention(k, v):
+        return gsd.gsd_dag_attention(d.q, k, v, d.kv_offsets, d.prefix_lens, d.node_offsets, mask, d.max_nodes, d.max_prefix,
+                                     w.softmax_scale)
+    want, rows = attention(d.k, d.v), d.k.shape[0]
+    for stride in ((1 << 25) - 4, 1 << 25):
+        room = torch.empty(rows * stride, dtype=torch.float32, device="cuda")
+        k = room.as_strided((rows, 2, D), (stride, D, 1))
+        v = room.as_strided((rows, 2, D), (stride, D, 1), 4 * D)
+        k.copy_(d.k)
+        v.copy_(d.v)
+        assert torch.equal(attention(k, v), want), stride
+        del room, k, v
+
+
 def test_attention_chain_equals_causal_sdpa(gpu):
     """A chain-shaped graph is plain causal attention: checked against torch's own SDPA on the GPU in fp32."""
     rng = np.random.default_rng(9)
