@@ -16,6 +16,7 @@ import struct
 
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG_DIR, "libgsd.so")
+BINDING_PATH = os.path.join(_PKG_DIR, "_binding.so")      # the calls of a verify step without Python in between
 
 GSD_OK = 0
 GSD_ERR_INVALID_ARG, GSD_ERR_UNSUPPORTED, GSD_ERR_WORKSPACE, GSD_ERR_HIP = 1, 3, 4, 5
@@ -81,6 +82,7 @@ def _packed(kind, layout, *values):
 
 _NO_SIZE = ctypes.c_size_t(-1).value
 _lib = None
+_short = None                # csrc/binding.cpp, where it has been built: takes plain tensors, gives None for everything else
 torch = None                 # set by the first call: importing this module does not need it
 _raw_stream = _device = None
 _DTYPE_CODES = {}
@@ -139,6 +141,13 @@ def load_library() -> ctypes.CDLL:
         lib.gsd_accept_stochastic.argtypes = [ctypes.POINTER(StochasticDesc), vp]
         lib.gsd_build_token_graph.argtypes = [i32, i32, i32, ctypes.c_float, ctypes.c_float, vp, vp, vp, vp, vp, vp, vp,
                                               vp, i64, vp, vp, vp, vp]
+        if os.path.exists(BINDING_PATH):
+            from . import _binding
+            _binding.bind(*(ctypes.cast(getattr(lib, name), vp).value for name in (
+                "gsd_build_mask", "gsd_dag_attention_workspace", "gsd_dag_attention", "gsd_node_argmax",
+                "gsd_node_argmax_stats", "gsd_accept_longest_path")), _device, _raw_stream)
+            global _short
+            _short = _binding
         _lib = lib
     return _lib
 
@@ -148,6 +157,13 @@ def _check(status: int):
         lib = load_library()
         detail = lib.gsd_last_error().decode() or lib.gsd_status_string(status).decode()
         raise GsdError(status, detail)
+
+
+def _result(done):
+    """What the short way returned: the call's result, or the status of a refused call."""
+    if type(done) is int:
+        _check(done)
+    return done
 
 
 def _stream_ptr(stream):
@@ -194,6 +210,11 @@ def _logits_layout(logits, message="logits must be a GPU tensor [rows, vocab] wi
 def gsd_build_mask(node_offsets, parent_offsets, parent_idx, max_nodes: int, words_per_row: int | None = None,
                    mask=None, dag_error_flag=None, stream=None):
     """mask[T, W] (int64 storage of the uint64 words) from the packed token graph.  See gsd_build_mask in gsd.h."""
+    if _short is not None:
+        done = _short.build_mask(node_offsets, parent_offsets, parent_idx, max_nodes, words_per_row, mask, dag_error_flag,
+                                 stream)
+        if done is not None:
+            return _result(done)
     if torch is None:
         _import_torch()
     _require_graph(node_offsets, parent_offsets, parent_idx)
@@ -258,6 +279,11 @@ def gsd_dag_attention(q, k, v, kv_offsets, prefix_lens, node_offsets, mask, max_
                       softmax_scale: float, out=None, lse=None, num_splits: int = 0, workspace=None, stream=None,
                       return_lse: bool = False, wg_waves: int = 0):
     """DAG-masked attention of every packed node; returns out (same dtype/shape as q).  See gsd.h."""
+    if _short is not None and workspace is None:
+        done = _short.dag_attention(q, k, v, kv_offsets, prefix_lens, node_offsets, mask, max_nodes, max_prefix,
+                                    softmax_scale, out, lse, num_splits, wg_waves, return_lse, stream)
+        if done is not None:
+            return _result(done)
     if torch is None:
         _import_torch()
     if out is None:
@@ -295,6 +321,10 @@ def gsd_dag_attention_static(desc: AttnDesc, stream=None):
 
 def gsd_node_argmax(logits, pred=None, stream=None):
     """pred[r] = lowest index of the row maximum of logits[r].  See gsd_node_argmax in gsd.h."""
+    if _short is not None:
+        done = _short.node_argmax(logits, pred, stream)
+        if done is not None:
+            return _result(done)
     if torch is None:
         _import_torch()
     rows, vocab, row_stride = _logits_layout(logits)
@@ -310,6 +340,10 @@ def gsd_node_argmax(logits, pred=None, stream=None):
 def gsd_node_argmax_stats(logits, pred=None, row_max=None, row_sumexp=None, stream=None):
     """One pass over the logits: (pred, row_max, row_sumexp) as gsd_node_argmax and gsd_softmax_stats give them.
     See gsd_node_argmax_stats in gsd.h."""
+    if _short is not None:
+        done = _short.node_argmax_stats(logits, pred, row_max, row_sumexp, stream)
+        if done is not None:
+            return _result(done)
     if torch is None:
         _import_torch()
     rows, vocab, row_stride = _logits_layout(logits)
@@ -330,6 +364,11 @@ def gsd_accept_longest_path(node_offsets, parent_offsets, parent_idx, tokens, ro
                             stream=None):
     """Longest accepted root path per sequence; returns (accept_len[B], accept_path[B, max_nodes], bonus[B], pred).
     With `logits` the per-node argmax runs first on the same stream.  See gsd_accept_longest_path in gsd.h."""
+    if _short is not None:
+        done = _short.accept_longest_path(node_offsets, parent_offsets, parent_idx, tokens, root_pred, max_nodes, logits,
+                                          pred, accept_len, accept_path, bonus_token, stream)
+        if done is not None:
+            return _result(done)
     if torch is None:
         _import_torch()
     _require_graph(node_offsets, parent_offsets, parent_idx)

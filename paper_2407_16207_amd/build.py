@@ -1,13 +1,15 @@
-"""Builds libgsd.so (the gfx950 HIP library behind include/gsd.h) in-tree with hipcc."""
+"""Builds libgsd.so (the gfx950 HIP library behind include/gsd.h) in-tree with hipcc, and the native part of its Python binding."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libgsd.so")
+BINDING_PATH = os.path.join(PKG_DIR, "_binding.so")
 BENCH_LIB_PATH = os.path.join(PKG_DIR, "libgsd_bench.so")     # measurement aid of bench.py only
 
 SOURCES = ["gsd_api.hip", "mask_build.hip", "accept_path.hip", "node_argmax.hip", "dag_attention_f32.hip",
@@ -21,6 +23,24 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
                "-Wno-unused-command-line-argument"]
 
 
+def build_binding(verbose: bool = False) -> str:
+    """csrc/binding.cpp against the headers of the torch that is installed; host code only."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    headers = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+               sysconfig.get_paths()["include"]]
+    lib = os.path.join(root, "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wno-sign-compare",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[flag for path in headers for flag in ("-isystem", path)], "-I", os.path.join(ROOT, "include"),
+           os.path.join(CSRC, "binding.cpp"), "-o", BINDING_PATH, "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python",
+           f"-Wl,-rpath,{lib}"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    return BINDING_PATH
+
+
 def build_library(verbose: bool = False, extra_flags: list[str] | None = None) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc, *HIPCC_FLAGS, *(extra_flags or []), "-I", os.path.join(ROOT, "include"), "-I", CSRC,
@@ -32,6 +52,7 @@ def build_library(verbose: bool = False, extra_flags: list[str] | None = None) -
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
+    build_binding(verbose)
     return LIB_PATH
 
 

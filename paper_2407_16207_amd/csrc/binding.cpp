@@ -1,0 +1,338 @@
+// The short way through the Python binding: the calls of a verify step, from plain tensors to the library's entry points.
+//
+// A function here takes what its namesake in __init__.py takes, all arguments in their order, and
+//   returns the call's result                        if every argument is what it should be,
+//   returns the library's status, a number           if the library refuses the call,
+//   returns None, with nothing done                  otherwise: the caller then goes the long way, which has the messages.
+// "Plain" is a torch.Tensor or Parameter (no subclass) with ordinary memory on a GPU, of the right type and contiguous, while no
+// torch mode is active that would want to see the allocations.
+// What a call costs the host is then mostly its launches, 3.1-3.7 us each: mask 5.5 -> 3.8 us, argmax and acceptance 10.5 -> 7.7, a whole
+// verify step in the short call forms, which allocate nine outputs, 37-40 -> 23.6.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <ATen/ATen.h>
+#include <ATen/PythonTorchFunctionTLS.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
+#include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <cfloat>
+#include <climits>
+#include <cmath>
+
+#include "gsd.h"
+
+namespace {
+
+// The library is loaded by ctypes; its entry points come from there (bind below).
+decltype(&gsd_build_mask) build_mask_fn;
+decltype(&gsd_dag_attention_workspace) attention_workspace_fn;
+decltype(&gsd_dag_attention) attention_fn;
+decltype(&gsd_node_argmax) argmax_fn;
+decltype(&gsd_node_argmax_stats) argmax_stats_fn;
+decltype(&gsd_accept_longest_path) accept_fn;
+PyObject *device_fn, *raw_stream_fn;         // the current device, and its current stream, as numbers
+
+bool modes_active() {
+    return c10::impl::TorchDispatchModeTLS::any_modes_set() || at::impl::PythonTorchFunctionTLS::stack_len() > 0;
+}
+
+// the tensor behind a plain object, or NULL; of any layout
+const at::Tensor *tensor(PyObject *o) {
+    if (!THPVariable_CheckExact(o)) return nullptr;
+    const at::Tensor &t = THPVariable_Unpack(o);
+    if (!t.defined() || !t.is_cuda()) return nullptr;
+    const c10::DispatchKeySet keys = t.key_set() - c10::autograd_dispatch_keyset_with_ADInplaceOrView - c10::autocast_dispatch_keyset;
+    return keys == c10::DispatchKeySet(c10::DispatchKey::CUDA) ? &t : nullptr;
+}
+
+const at::Tensor *tensor(PyObject *o, at::ScalarType type) {
+    const at::Tensor *t = tensor(o);
+    return t && t->scalar_type() == type && t->is_contiguous() ? t : nullptr;
+}
+
+bool number(PyObject *o, int32_t &x) {
+    if (!PyLong_CheckExact(o)) return false;
+    int overflow = 0;
+    const long v = PyLong_AsLongAndOverflow(o, &overflow);
+    if (overflow || v < INT32_MIN || v > INT32_MAX) return false;
+    x = int32_t(v);
+    return true;
+}
+
+bool dtype_code(const at::Tensor &t, int &code) {
+    if (t.scalar_type() == at::kFloat) code = GSD_F32;
+    else if (t.scalar_type() == at::kBFloat16) code = GSD_BF16;
+    else return false;
+    return true;
+}
+
+bool logits_layout(const at::Tensor &t) { return t.dim() == 2 && t.stride(1) == 1 && t.size(0) <= INT32_MAX && t.size(1) <= INT32_MAX; }
+
+// An output: the caller's tensor, which has to be of the type and contiguous, or a new one.
+struct Output {
+    PyObject *given = nullptr;
+    at::Tensor t;
+    bool take(PyObject *o, at::ScalarType type) {
+        if (o == Py_None) return true;
+        const at::Tensor *x = tensor(o, type);
+        if (!x) return false;
+        given = o;
+        t = *x;
+        return true;
+    }
+    void make(at::IntArrayRef sizes, at::ScalarType type, c10::Device device) {
+        if (!given) t = at::empty(sizes, at::TensorOptions().dtype(type).device(device));
+    }
+    PyObject *object() const {
+        if (!given) return THPVariable_Wrap(t);
+        Py_INCREF(given);
+        return given;
+    }
+};
+
+PyObject *no_short_way() { Py_RETURN_NONE; }
+
+template <typename F>
+int call(F &&f) {           // without the interpreter's lock, as ctypes calls it
+    int status;
+    Py_BEGIN_ALLOW_THREADS
+    status = f();
+    Py_END_ALLOW_THREADS
+    return status;
+}
+
+struct Graph {
+    const at::Tensor *nodes, *offsets, *parents;
+    int32_t batch, total;
+    bool take(PyObject *const *args) {
+        nodes = tensor(args[0], at::kInt);
+        offsets = tensor(args[1], at::kInt);
+        parents = tensor(args[2], at::kInt);
+        if (!nodes || !offsets || !parents) return false;
+        const int64_t b = nodes->numel() - 1, t = offsets->numel() - 1;
+        batch = int32_t(b);
+        total = int32_t(t);
+        return b >= 1 && b <= INT32_MAX && t >= 0 && t <= INT32_MAX;
+    }
+    const int32_t *node_offsets() const { return static_cast<const int32_t *>(nodes->data_ptr()); }
+    const int32_t *parent_offsets() const { return static_cast<const int32_t *>(offsets->data_ptr()); }
+    const int32_t *parent_idx() const { return static_cast<const int32_t *>(parents->data_ptr()); }
+};
+
+// the stream of a call, asked for when everything else is in order: the caller's, or the current one
+bool stream_of(PyObject *o, void *&stream) {
+    PyObject *value;
+    if (o == Py_None) {
+        PyObject *device = PyObject_CallNoArgs(device_fn);
+        value = device ? PyObject_CallOneArg(raw_stream_fn, device) : nullptr;
+        Py_XDECREF(device);
+    } else {
+        value = PyObject_GetAttrString(o, "cuda_stream");
+    }
+    const bool number = value && PyLong_CheckExact(value);
+    if (number) stream = PyLong_AsVoidPtr(value);
+    Py_XDECREF(value);
+    if (!PyErr_Occurred()) return number;
+    PyErr_Clear();
+    return false;
+}
+
+// node_offsets, parent_offsets, parent_idx, max_nodes, words_per_row, mask, dag_error_flag, stream
+PyObject *build_mask(PyObject *, PyObject *const *args, Py_ssize_t count) {
+    HANDLE_TH_ERRORS
+    Graph g;
+    int32_t max_nodes, words;
+    Output mask, flag;
+    void *stream;
+    if (count != 8 || modes_active() || !g.take(args) || !number(args[3], max_nodes) || max_nodes < 1 || !mask.take(args[5], at::kLong) ||
+        !flag.take(args[6], at::kInt) || !stream_of(args[7], stream))
+        return no_short_way();
+    if (args[4] == Py_None) words = (max_nodes - 1) / 64 + 1;
+    else if (!number(args[4], words) || words < 1) return no_short_way();
+    if (mask.given && mask.t.numel() != int64_t(g.total) * words) return no_short_way();
+    mask.make({g.total, words}, at::kLong, g.nodes->device());
+    const int status = call([&] {
+        return build_mask_fn(g.batch, max_nodes, words, g.node_offsets(), g.parent_offsets(), g.parent_idx(),
+                             static_cast<uint64_t *>(mask.t.data_ptr()), flag.given ? static_cast<int32_t *>(flag.t.data_ptr()) : nullptr, stream);
+    });
+    return status ? PyLong_FromLong(status) : mask.object();
+    END_HANDLE_TH_ERRORS
+}
+
+// logits, pred, row_max, row_sumexp, stream; without the two in the middle: gsd_node_argmax
+PyObject *argmax(PyObject *const *args, bool stats) {
+    const at::Tensor *logits = modes_active() ? nullptr : tensor(args[0]);
+    int code;
+    Output pred, row_max, row_sumexp;
+    void *stream;
+    if (!logits || !logits_layout(*logits) || !dtype_code(*logits, code) || !pred.take(args[1], at::kInt) ||
+        (stats && (!row_max.take(args[2], at::kFloat) || !row_sumexp.take(args[3], at::kFloat))) || !stream_of(args[stats ? 4 : 2], stream))
+        return no_short_way();
+    const int32_t rows = int32_t(logits->size(0)), vocab = int32_t(logits->size(1));
+    pred.make({rows}, at::kInt, logits->device());
+    if (stats) {
+        row_max.make({rows}, at::kFloat, logits->device());
+        row_sumexp.make({rows}, at::kFloat, logits->device());
+    }
+    const int status = call([&] {
+        int32_t *to = static_cast<int32_t *>(pred.t.data_ptr());
+        if (!stats) return argmax_fn(rows, vocab, code, logits->data_ptr(), logits->stride(0), to, stream);
+        return argmax_stats_fn(rows, vocab, code, logits->data_ptr(), logits->stride(0), to, static_cast<float *>(row_max.t.data_ptr()),
+                               static_cast<float *>(row_sumexp.t.data_ptr()), stream);
+    });
+    if (status) return PyLong_FromLong(status);
+    return stats ? Py_BuildValue("(NNN)", pred.object(), row_max.object(), row_sumexp.object()) : pred.object();
+}
+
+PyObject *node_argmax(PyObject *, PyObject *const *args, Py_ssize_t count) {
+    HANDLE_TH_ERRORS
+    return count == 3 ? argmax(args, false) : no_short_way();
+    END_HANDLE_TH_ERRORS
+}
+
+PyObject *node_argmax_stats(PyObject *, PyObject *const *args, Py_ssize_t count) {
+    HANDLE_TH_ERRORS
+    return count == 5 ? argmax(args, true) : no_short_way();
+    END_HANDLE_TH_ERRORS
+}
+
+// node_offsets, parent_offsets, parent_idx, tokens, root_pred, max_nodes, logits, pred, accept_len, accept_path, bonus_token, stream
+PyObject *accept_longest_path(PyObject *, PyObject *const *args, Py_ssize_t count) {
+    HANDLE_TH_ERRORS
+    Graph g;
+    int32_t max_nodes;
+    Output pred, length, path, bonus;
+    void *stream;
+    if (count != 12 || modes_active() || !g.take(args)) return no_short_way();
+    const at::Tensor *tokens = tensor(args[3], at::kInt), *root_pred = tensor(args[4], at::kInt);
+    if (!tokens || !root_pred || tokens->numel() > INT32_MAX || !number(args[5], max_nodes) || max_nodes < 1 || !pred.take(args[7], at::kInt) ||
+        !length.take(args[8], at::kInt) || !path.take(args[9], at::kInt) || !bonus.take(args[10], at::kInt) || !stream_of(args[11], stream))
+        return no_short_way();
+    const int32_t total = int32_t(tokens->numel());
+    const at::Tensor *logits = nullptr;
+    int code = GSD_F32;
+    if (args[6] != Py_None) {
+        logits = tensor(args[6]);
+        if (!logits || !logits_layout(*logits) || logits->size(0) != total || !dtype_code(*logits, code)) return no_short_way();
+    } else if (!pred.given) {
+        return no_short_way();
+    }
+    const c10::Device device = tokens->device();
+    pred.make({total}, at::kInt, device);
+    length.make({g.batch}, at::kInt, device);
+    path.make({g.batch, max_nodes}, at::kInt, device);
+    bonus.make({g.batch}, at::kInt, device);
+    const int status = call([&] {
+        auto ints = [](const at::Tensor &t) { return static_cast<int32_t *>(t.data_ptr()); };
+        return accept_fn(g.batch, total, max_nodes, g.node_offsets(), g.parent_offsets(), g.parent_idx(), ints(*tokens),
+                         logits ? logits->data_ptr() : nullptr, code, logits ? int32_t(logits->size(1)) : 0, logits ? logits->stride(0) : 0,
+                         ints(pred.t), ints(*root_pred), ints(length.t), ints(path.t), ints(bonus.t), stream);
+    });
+    if (status) return PyLong_FromLong(status);
+    return Py_BuildValue("(NNNN)", length.object(), path.object(), bonus.object(), pred.object());
+    END_HANDLE_TH_ERRORS
+}
+
+// q, k, v, kv_offsets, prefix_lens, node_offsets, mask, max_nodes, max_prefix, softmax_scale, out, lse, num_splits, wg_waves, return_lse,
+// stream: only where no stream is given, so that a workspace allocated here belongs to the stream of the call
+PyObject *dag_attention(PyObject *, PyObject *const *args, Py_ssize_t count) {
+    HANDLE_TH_ERRORS
+    if (count != 16 || args[15] != Py_None || modes_active()) return no_short_way();
+    const at::Tensor *q = tensor(args[0]), *k = tensor(args[1]), *v = tensor(args[2]);
+    const at::Tensor *kv_offsets = tensor(args[3], at::kLong), *prefix = tensor(args[4], at::kInt), *nodes = tensor(args[5], at::kInt);
+    const at::Tensor *mask = tensor(args[6], at::kLong);
+    if (!q || !k || !v || !kv_offsets || !prefix || !nodes || !mask || mask->dim() < 2) return no_short_way();
+    gsd_attn_desc d = {};
+    int code, code_k, code_v;
+    if (q->dim() != 3 || k->dim() != 3 || v->dim() != 3 || q->stride(2) != 1 || k->stride(2) != 1 || v->stride(2) != 1 || !dtype_code(*q, code) ||
+        !dtype_code(*k, code_k) || !dtype_code(*v, code_v) || code != code_k || code != code_v || k->strides() != v->strides() ||
+        k->sizes() != v->sizes())
+        return no_short_way();
+    Output lse;
+    void *stream;
+    if (!number(args[7], d.max_nodes) || !number(args[8], d.max_prefix) || !PyFloat_CheckExact(args[9]) || !lse.take(args[11], at::kFloat) ||
+        !number(args[12], d.num_splits) || !number(args[13], d.wg_waves) || !PyBool_Check(args[14]) || !stream_of(args[15], stream))
+        return no_short_way();
+    const double scale = PyFloat_AS_DOUBLE(args[9]);
+    if (!(std::fabs(scale) <= FLT_MAX)) return no_short_way();
+    for (int64_t x : {prefix->numel(), q->size(0), q->size(1), q->size(2), k->size(1), mask->size(1)})
+        if (x > INT32_MAX) return no_short_way();
+    const at::Tensor *given = args[10] == Py_None ? nullptr : tensor(args[10]);
+    if (args[10] != Py_None && (!given || given->dim() != 3)) return no_short_way();
+    const bool return_lse = args[14] == Py_True;
+    at::Tensor out = given ? *given : at::empty(q->sizes(), at::TensorOptions().dtype(q->scalar_type()).device(q->device()));
+    if (return_lse) lse.make({q->size(0), q->size(1)}, at::kFloat, q->device());
+    d.batch = int32_t(prefix->numel());
+    d.total_nodes = int32_t(q->size(0));
+    d.num_q_heads = int32_t(q->size(1));
+    d.num_kv_heads = int32_t(k->size(1));
+    d.head_dim = int32_t(q->size(2));
+    d.dtype = code;
+    d.words_per_row = int32_t(mask->size(1));
+    d.softmax_scale = float(scale);
+    d.q = q->data_ptr();
+    d.o = out.data_ptr();
+    d.lse = lse.t.defined() ? static_cast<float *>(lse.t.data_ptr()) : nullptr;
+    d.k = k->data_ptr();
+    d.v = v->data_ptr();
+    d.kv_offsets = static_cast<const int64_t *>(kv_offsets->data_ptr());
+    d.prefix_lens = static_cast<const int32_t *>(prefix->data_ptr());
+    d.node_offsets = static_cast<const int32_t *>(nodes->data_ptr());
+    d.mask = static_cast<const uint64_t *>(mask->data_ptr());
+    d.q_token_stride = q->stride(0);
+    d.q_head_stride = q->stride(1);
+    d.o_token_stride = out.stride(0);
+    d.o_head_stride = out.stride(1);
+    d.kv_token_stride = k->stride(0);
+    d.kv_head_stride = k->stride(1);
+    const size_t need = attention_workspace_fn(&d);
+    if (need == size_t(-1)) return no_short_way();
+    at::Tensor workspace;
+    if (need > 0) {
+        workspace = at::empty({int64_t(need)}, at::TensorOptions().dtype(at::kByte).device(q->device()));
+        d.workspace = workspace.data_ptr();
+        d.workspace_bytes = need;
+    }
+    const int status = call([&] { return attention_fn(&d, stream); });
+    if (status) return PyLong_FromLong(status);
+    PyObject *result = args[10];
+    if (given) Py_INCREF(result);
+    else result = THPVariable_Wrap(out);
+    return return_lse ? Py_BuildValue("(NN)", result, lse.object()) : result;
+    END_HANDLE_TH_ERRORS
+}
+
+// the addresses of the library's entry points, in the order of the list at the top, and what tells the current device and stream
+PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t count) {
+    void *at[6];
+    if (count != 8) {
+        PyErr_SetString(PyExc_TypeError, "six addresses and two functions");
+        return nullptr;
+    }
+    for (int x = 0; x < 6; ++x) {
+        at[x] = PyLong_AsVoidPtr(args[x]);
+        if (PyErr_Occurred()) return nullptr;
+    }
+    build_mask_fn = reinterpret_cast<decltype(build_mask_fn)>(at[0]);
+    attention_workspace_fn = reinterpret_cast<decltype(attention_workspace_fn)>(at[1]);
+    attention_fn = reinterpret_cast<decltype(attention_fn)>(at[2]);
+    argmax_fn = reinterpret_cast<decltype(argmax_fn)>(at[3]);
+    argmax_stats_fn = reinterpret_cast<decltype(argmax_stats_fn)>(at[4]);
+    accept_fn = reinterpret_cast<decltype(accept_fn)>(at[5]);
+    Py_INCREF(args[6]);
+    Py_INCREF(args[7]);
+    device_fn = args[6];                          // kept for good, like the library
+    raw_stream_fn = args[7];
+    Py_RETURN_NONE;
+}
+
+#define GSD_METHOD(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(name)), METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {GSD_METHOD(bind), GSD_METHOD(build_mask), GSD_METHOD(node_argmax), GSD_METHOD(node_argmax_stats),
+                         GSD_METHOD(accept_longest_path), GSD_METHOD(dag_attention), {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__binding() { return PyModule_Create(&module); }

@@ -1,0 +1,147 @@
+"""The native part of the Python binding (csrc/binding.cpp) against the Python it stands in for: the same results, the caller's own
+tensors handed back, the same exceptions, and everything that is not a plain tensor left to Python."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2407_16207_amd as gsd
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def args():
+    g = torch.Generator(device="cuda").manual_seed(1)
+    dev = lambda x, t=torch.int32: torch.tensor(x, dtype=t, device="cuda")
+    n = 6
+    graph = (dev([0, n]), dev([0, 1, 2, 3, 5, 6, 7]), dev([-1, 0, 0, 1, 2, 3, 4]))
+    heads, dim, prefix = 4, 64, 40
+    a = {"graph": graph, "n": n, "tokens": dev([1, 2, 3, 4, 5, 6]), "root_pred": dev([1]), "prefix": dev([prefix]),
+         "kv_offsets": dev([0], torch.int64), "max_prefix": prefix, "mask": gsd.gsd_build_mask(*graph, n)}
+    for dtype in (torch.float32, torch.bfloat16):
+        r = lambda *shape: torch.randn(shape, generator=g, device="cuda").to(dtype)
+        a[dtype] = {"q": r(n, heads, dim), "k": r(prefix + n, 2, dim), "v": r(prefix + n, 2, dim), "logits": r(n, 1000)}
+    return a
+
+
+def both(monkeypatch, call):
+    """What `call` returns or raises with the native part and without."""
+    assert gsd._short is not None, "the binding's native part has not been built"
+    got = []
+    for short in (gsd._short, None):
+        with monkeypatch.context() as m:
+            m.setattr(gsd, "_short", short)
+            try:
+                got.append(call())
+            except Exception as e:        # noqa: BLE001 - compared below
+                got.append((type(e), str(e)))
+    torch.cuda.synchronize()
+    return got
+
+
+def flat(x):
+    return list(x) if isinstance(x, (tuple, list)) else [x]
+
+
+def same(monkeypatch, call):
+    a, b = (flat(x) for x in both(monkeypatch, call))
+    assert len(a) == len(b)
+    for x, y in zip(a, b):
+        assert type(x) is torch.Tensor and x.dtype == y.dtype and x.shape == y.shape and x.stride() == y.stride()
+        assert x.device == y.device and torch.equal(x, y)
+
+
+def attention_args(a, dtype):
+    t = a[dtype]
+    return (t["q"], t["k"], t["v"], a["kv_offsets"], a["prefix"], a["graph"][0], a["mask"], a["n"], a["max_prefix"], 0.125)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_results_are_the_same(args, monkeypatch, dtype):
+    a, t = args, args[dtype]
+    wide = torch.cat([t["logits"], t["logits"]], 1)[:, 3:1003]                     # rows that are not side by side
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    for kw in ({}, {"words_per_row": 3}, {"mask": torch.zeros((a["n"], 1), dtype=torch.int64, device="cuda")},
+               {"dag_error_flag": torch.zeros(1, dtype=torch.int32, device="cuda")}, {"stream": side}):
+        same(monkeypatch, lambda: gsd.gsd_build_mask(*a["graph"], a["n"], **kw))
+    for x in (t["logits"], wide):
+        same(monkeypatch, lambda: gsd.gsd_node_argmax(x))
+        same(monkeypatch, lambda: gsd.gsd_node_argmax_stats(x))
+        same(monkeypatch, lambda: gsd.gsd_accept_longest_path(*a["graph"], a["tokens"], a["root_pred"], a["n"], logits=x))
+    pred = gsd.gsd_node_argmax(t["logits"])
+    same(monkeypatch, lambda: gsd.gsd_accept_longest_path(*a["graph"], a["tokens"], a["root_pred"], a["n"], pred=pred))
+    for kw in ({}, {"return_lse": True}, {"num_splits": 2}, {"out": torch.zeros_like(t["q"])}, {"stream": side},
+               {"lse": torch.zeros((a["n"], 4), device="cuda"), "return_lse": True},
+               {"workspace": torch.zeros(1 << 16, dtype=torch.uint8, device="cuda"), "num_splits": 2}):
+        same(monkeypatch, lambda: gsd.gsd_dag_attention(*attention_args(a, dtype), **kw))
+
+
+def test_the_callers_tensors_come_back(args, monkeypatch):
+    a, t = args, args[torch.bfloat16]
+    kept = {name: torch.empty(shape, dtype=torch.int32, device="cuda") for name, shape in
+            (("pred", (a["n"],)), ("accept_len", (1,)), ("accept_path", (1, a["n"])), ("bonus_token", (1,)))}
+    mask, out, lse = torch.empty_like(a["mask"]), torch.empty_like(t["q"]), torch.empty((a["n"], 4), device="cuda")
+    for got in both(monkeypatch, lambda: gsd.gsd_accept_longest_path(*a["graph"], a["tokens"], a["root_pred"], a["n"],
+                                                                    logits=t["logits"], **kept)):
+        assert all(x is kept[name] for x, name in zip(got, ("accept_len", "accept_path", "bonus_token", "pred")))
+    assert all(x is mask for x in both(monkeypatch, lambda: gsd.gsd_build_mask(*a["graph"], a["n"], mask=mask)))
+    for got in both(monkeypatch, lambda: gsd.gsd_dag_attention(*attention_args(a, torch.bfloat16), out=out, lse=lse, return_lse=True)):
+        assert got[0] is out and got[1] is lse
+
+
+def test_plain_tensors_take_the_short_way(args):
+    a, t = args, args[torch.bfloat16]
+    short = gsd._short
+    assert short.build_mask(*a["graph"], a["n"], None, None, None, None) is not None
+    assert short.node_argmax(t["logits"], None, None) is not None
+    assert short.node_argmax_stats(torch.nn.Parameter(t["logits"]), None, None, None, None) is not None
+    assert short.accept_longest_path(*a["graph"], a["tokens"], a["root_pred"], a["n"], t["logits"], None, None, None, None, None) is not None
+    assert short.dag_attention(*attention_args(a, torch.bfloat16), None, None, 2, 0, True, None) is not None
+    torch.cuda.synchronize()
+
+
+class Subclass(torch.Tensor):
+    pass
+
+
+def test_exceptions_are_the_same(args, monkeypatch):
+    a, t = args, args[torch.float32]
+    att = attention_args(a, torch.float32)
+    half, host, wrong = t["q"].half(), a["graph"][0].cpu(), a["graph"][0].long()
+    calls = [lambda: gsd.gsd_build_mask(host, *a["graph"][1:], a["n"]), lambda: gsd.gsd_build_mask(wrong, *a["graph"][1:], a["n"]),
+             lambda: gsd.gsd_build_mask(*a["graph"], 0), lambda: gsd.gsd_build_mask(*a["graph"], 513), lambda: gsd.gsd_build_mask(*a["graph"], 1 << 40),
+             lambda: gsd.gsd_build_mask(*a["graph"], a["n"], mask=a["mask"][:3]), lambda: gsd.gsd_build_mask(*a["graph"], 80, words_per_row=1),
+             lambda: gsd.gsd_node_argmax(half.flatten(1)), lambda: gsd.gsd_node_argmax(t["logits"].t()), lambda: gsd.gsd_node_argmax(t["logits"][:0]),
+             lambda: gsd.gsd_node_argmax(t["logits"], pred=wrong), lambda: gsd.gsd_node_argmax_stats(t["logits"], row_max=wrong),
+             lambda: gsd.gsd_accept_longest_path(*a["graph"], a["tokens"], a["root_pred"], a["n"]),
+             lambda: gsd.gsd_accept_longest_path(*a["graph"], a["tokens"], a["root_pred"], a["n"], logits=t["logits"][:3]),
+             lambda: gsd.gsd_dag_attention(half, *att[1:]), lambda: gsd.gsd_dag_attention(att[0][:, :3], *att[1:]),
+             lambda: gsd.gsd_dag_attention(*att[:2], att[2][:-1], *att[3:]), lambda: gsd.gsd_dag_attention(*att[:-1], -1.0),
+             lambda: gsd.gsd_dag_attention(*att[:-1], 1e39), lambda: gsd.gsd_dag_attention(*att, num_splits=-1),
+             lambda: gsd.gsd_dag_attention(*att, lse=wrong), lambda: gsd.gsd_dag_attention(*att[:6], att[6][:, 0], *att[7:])]
+    for k, call in enumerate(calls):
+        x, y = both(monkeypatch, call)
+        assert isinstance(x, tuple) and isinstance(x[0], type) and x == y, (k, x, y)
+
+
+def test_other_tensors_go_the_long_way(args):
+    """Subclasses, and calls under a torch mode that wants to see them."""
+    from torch.utils._python_dispatch import TorchDispatchMode
+    a, t = args, args[torch.float32]
+    assert gsd._short.node_argmax(t["logits"].as_subclass(Subclass), None, None) is None
+    assert gsd._short.node_argmax(t["logits"].cpu(), None, None) is None
+
+    class Seen(TorchDispatchMode):
+        names = []
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            self.names.append(func.name())
+            return func(*args, **(kwargs or {}))
+    with Seen() as seen:
+        assert gsd._short.node_argmax(t["logits"], None, None) is None
+        pred = gsd.gsd_node_argmax(t["logits"])
+    assert any("empty" in name for name in seen.names)
+    assert torch.equal(pred, gsd.gsd_node_argmax(t["logits"]))
+    assert torch.equal(gsd.gsd_node_argmax(t["logits"].as_subclass(Subclass)), pred)
+    assert torch.equal(gsd.gsd_node_argmax(torch.nn.Parameter(t["logits"])), pred)
