@@ -16,7 +16,7 @@ import struct
 
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG_DIR, "libgsd.so")
-BINDING_PATH = os.path.join(_PKG_DIR, "_binding.so")      # the calls of a verify step without Python in between
+BINDING_PATH = os.path.join(_PKG_DIR, "_binding.so")      # the way of plain tensors to the library without Python in between
 
 GSD_OK = 0
 GSD_ERR_INVALID_ARG, GSD_ERR_UNSUPPORTED, GSD_ERR_WORKSPACE, GSD_ERR_HIP = 1, 3, 4, 5
@@ -145,7 +145,8 @@ def load_library() -> ctypes.CDLL:
             from . import _binding
             _binding.bind(*(ctypes.cast(getattr(lib, name), vp).value for name in (
                 "gsd_build_mask", "gsd_dag_attention_workspace", "gsd_dag_attention", "gsd_node_argmax",
-                "gsd_node_argmax_stats", "gsd_accept_longest_path")), _device, _raw_stream)
+                "gsd_node_argmax_stats", "gsd_accept_longest_path", "gsd_unmerge_to_tree", "gsd_gather_rows", "gsd_commit_kv",
+                "gsd_softmax_stats", "gsd_accept_stochastic", "gsd_build_token_graph")), _device, _raw_stream)
             global _short
             _short = _binding
         _lib = lib
@@ -409,6 +410,11 @@ def gsd_unmerge_to_tree(node_offsets, parent_offsets, parent_idx, max_nodes: int
     """Token graph -> token tree with replicated successors.  Returns (tree_node_offsets[B+1], tree_parent,
     tree_parent_offsets, tree_origin, path_count[B]); the three per-node arrays are allocated at their bound
     B*max_tree_nodes (+1) and only their first tree_node_offsets[B] (+1) entries are written.  See gsd.h."""
+    if _short is not None:
+        done = _short.unmerge_to_tree(node_offsets, parent_offsets, parent_idx, max_nodes, max_tree_nodes, dag_error_flag,
+                                      stream)
+        if done is not None:
+            return _result(done)
     if torch is None:
         _import_torch()
     _require_graph(node_offsets, parent_offsets, parent_idx)
@@ -437,6 +443,10 @@ def _rows_contiguous(t) -> bool:
 
 def gsd_gather_rows(src, index, out=None, rows: int | None = None, stream=None):
     """out[r] = src[index[r]] along dim 0 (rows of any trailing shape, contiguous within a row).  See gsd.h."""
+    if _short is not None:
+        done = _short.gather_rows(src, index, out, rows, stream)
+        if done is not None:
+            return _result(done)
     if torch is None:
         _import_torch()
     _require(index, torch.int32, "index")
@@ -465,6 +475,10 @@ def gsd_gather_rows(src, index, out=None, rows: int | None = None, stream=None):
 def gsd_commit_kv(k, v, kv_offsets, prefix_lens, accept_len, accept_path, new_prefix_lens=None, stream=None):
     """In-place KV-cache commit of the accepted path.  k, v: [L, R, Hkv, D] (or [R, Hkv, D] for one layer) with
     contiguous rows; returns new_prefix_lens[B].  See gsd_commit_kv in gsd.h."""
+    if _short is not None:
+        done = _short.commit_kv(k, v, kv_offsets, prefix_lens, accept_len, accept_path, new_prefix_lens, stream)
+        if done is not None:
+            return _result(done)
     if torch is None:
         _import_torch()
     if k.dim() == 3:
@@ -494,6 +508,10 @@ def gsd_commit_kv(k, v, kv_offsets, prefix_lens, accept_len, accept_path, new_pr
 
 def gsd_softmax_stats(logits, row_max=None, row_sumexp=None, stream=None):
     """(row_max[r], row_sumexp[r]) of every logits row.  See gsd_softmax_stats in gsd.h."""
+    if _short is not None:
+        done = _short.softmax_stats(logits, row_max, row_sumexp, stream)
+        if done is not None:
+            return _result(done)
     if torch is None:
         _import_torch()
     rows, vocab, row_stride = _logits_layout(logits)
@@ -511,6 +529,11 @@ def gsd_accept_stochastic(node_offsets, parent_offsets, parent_idx, tokens, logi
                           root_draft_logits, draft_prob, accept_u, resample_u, max_nodes: int, stream=None):
     """Non-deterministic verification; returns (accept_len[B], accept_path[B, max_nodes], end_node[B], bonus_token[B],
     row_max[T+B], row_sumexp[T+B]).  See gsd_accept_stochastic in gsd.h."""
+    if _short is not None:
+        done = _short.accept_stochastic(node_offsets, parent_offsets, parent_idx, tokens, logits, root_logits, draft_logits,
+                                        root_draft_logits, draft_prob, accept_u, resample_u, max_nodes, stream)
+        if done is not None:
+            return _result(done)
     if torch is None:
         _import_torch()
     _require_graph(node_offsets, parent_offsets, parent_idx)
@@ -551,6 +574,11 @@ def gsd_build_token_graph(node_offsets, tree_parent, tokens, draft_prob, max_nod
     """Drafted token trees -> pruned, merged token graphs.  Returns (graph_node_offsets[B+1], parent_offsets[T+1],
     parent_idx[edge_capacity], origin[T], flags[T], counts[B, 2]); only the first T' (+1) / E entries are written.
     See gsd_build_token_graph in gsd.h."""
+    if _short is not None:
+        done = _short.build_token_graph(node_offsets, tree_parent, tokens, draft_prob, max_nodes, tau, theta_prob, theta_sib,
+                                        edge_capacity, error_flag, stream)
+        if done is not None:
+            return _result(done)
     if torch is None:
         _import_torch()
     _require(node_offsets, torch.int32, "node_offsets")

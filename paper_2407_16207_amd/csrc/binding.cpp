@@ -1,4 +1,4 @@
-// The short way through the Python binding: the calls of a verify step, from plain tensors to the library's entry points.
+// The short way through the Python binding, from plain tensors to the library's entry points.
 //
 // A function here takes what its namesake in __init__.py takes, all arguments in their order, and
 //   returns the call's result                        if every argument is what it should be,
@@ -7,7 +7,8 @@
 // "Plain" is a torch.Tensor or Parameter (no subclass) with ordinary memory on a GPU, of the right type and contiguous, while no
 // torch mode is active that would want to see the allocations.
 // What a call costs the host is then mostly its launches, 3.1-3.7 us each: mask 5.5 -> 3.8 us, argmax and acceptance 10.5 -> 7.7, a whole
-// verify step in the short call forms, which allocate nine outputs, 37-40 -> 23.6.
+// verify step in the short call forms, which allocate nine outputs, 37-40 -> 23.6; building eight token graphs and reading them back
+// 58.6 -> 53 us, of which the kernels take half.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -20,6 +21,8 @@
 #include <cfloat>
 #include <climits>
 #include <cmath>
+#include <type_traits>
+#include <vector>
 
 #include "gsd.h"
 
@@ -32,6 +35,12 @@ decltype(&gsd_dag_attention) attention_fn;
 decltype(&gsd_node_argmax) argmax_fn;
 decltype(&gsd_node_argmax_stats) argmax_stats_fn;
 decltype(&gsd_accept_longest_path) accept_fn;
+decltype(&gsd_unmerge_to_tree) unmerge_fn;
+decltype(&gsd_gather_rows) gather_fn;
+decltype(&gsd_commit_kv) commit_fn;
+decltype(&gsd_softmax_stats) softmax_stats_fn;
+decltype(&gsd_accept_stochastic) accept_stochastic_fn;
+decltype(&gsd_build_token_graph) build_graph_fn;
 PyObject *device_fn, *raw_stream_fn;         // the current device, and its current stream, as numbers
 
 bool modes_active() {
@@ -304,33 +313,251 @@ PyObject *dag_attention(PyObject *, PyObject *const *args, Py_ssize_t count) {
     END_HANDLE_TH_ERRORS
 }
 
+template <typename T>
+T *to(const at::Tensor &t) { return static_cast<T *>(t.data_ptr()); }
+
+at::Tensor ints(at::IntArrayRef sizes, c10::Device device) { return at::empty(sizes, at::TensorOptions().dtype(at::kInt).device(device)); }
+at::Tensor floats(at::IntArrayRef sizes, c10::Device device) { return at::empty(sizes, at::TensorOptions().dtype(at::kFloat).device(device)); }
+
+// node_offsets, parent_offsets, parent_idx, max_nodes, max_tree_nodes, dag_error_flag, stream
+PyObject *unmerge_to_tree(PyObject *, PyObject *const *args, Py_ssize_t count) {
+    HANDLE_TH_ERRORS
+    Graph g;
+    int32_t max_nodes, cap;
+    Output flag;
+    void *stream;
+    if (count != 7 || modes_active() || !g.take(args) || !number(args[3], max_nodes) || !number(args[4], cap) || cap < 1 ||
+        int64_t(g.batch) * cap >= INT32_MAX || !flag.take(args[5], at::kInt) || !stream_of(args[6], stream))
+        return no_short_way();
+    const c10::Device device = g.nodes->device();
+    const int64_t bound = int64_t(g.batch) * cap;
+    at::Tensor offsets = ints({g.batch + 1}, device), parent = ints({bound}, device), parent_offsets = ints({bound + 1}, device),
+               origin = ints({bound}, device), paths = at::empty({g.batch}, at::TensorOptions().dtype(at::kLong).device(device));
+    const int status = call([&] {
+        return unmerge_fn(g.batch, max_nodes, cap, g.node_offsets(), g.parent_offsets(), g.parent_idx(), to<int32_t>(offsets), to<int32_t>(parent),
+                          to<int32_t>(parent_offsets), to<int32_t>(origin), to<int64_t>(paths), flag.given ? to<int32_t>(flag.t) : nullptr, stream);
+    });
+    if (status) return PyLong_FromLong(status);
+    return Py_BuildValue("(NNNNN)", THPVariable_Wrap(offsets), THPVariable_Wrap(parent), THPVariable_Wrap(parent_offsets),
+                         THPVariable_Wrap(origin), THPVariable_Wrap(paths));
+    END_HANDLE_TH_ERRORS
+}
+
+// src, index, out, rows, stream
+PyObject *gather_rows(PyObject *, PyObject *const *args, Py_ssize_t count) {
+    HANDLE_TH_ERRORS
+    if (count != 5 || modes_active()) return no_short_way();
+    const at::Tensor *src = tensor(args[0]), *index = tensor(args[1], at::kInt);
+    if (!src || !index || src->dim() < 1 || src->numel() == 0 || !src->is_contiguous()) return no_short_way();
+    int64_t rows = index->numel();
+    int32_t given_rows;
+    if (args[3] != Py_None) {
+        if (!number(args[3], given_rows)) return no_short_way();
+        rows = given_rows;
+    }
+    if (rows < 1) return no_short_way();
+    const at::Tensor *given = args[2] == Py_None ? nullptr : tensor(args[2]);
+    if (args[2] != Py_None && (!given || given->scalar_type() != src->scalar_type() || given->dim() != src->dim() ||
+                               given->sizes().slice(1) != src->sizes().slice(1) || given->size(0) < rows || given->numel() == 0 ||
+                               !given->is_contiguous()))
+        return no_short_way();
+    void *stream;
+    if (!stream_of(args[4], stream)) return no_short_way();
+    at::Tensor out;
+    if (given) {
+        out = *given;
+    } else {
+        std::vector<int64_t> sizes = src->sizes().vec();
+        sizes[0] = rows;
+        out = at::empty(sizes, at::TensorOptions().dtype(src->scalar_type()).device(src->device()));
+    }
+    const int64_t row_bytes = src->numel() / src->size(0) * int64_t(src->element_size());
+    const int status = call([&] { return gather_fn(rows, row_bytes, src->data_ptr(), src->size(0), row_bytes, to<int32_t>(*index), out.data_ptr(), row_bytes, stream); });
+    if (status) return PyLong_FromLong(status);
+    if (!given) return THPVariable_Wrap(out);
+    Py_INCREF(args[2]);
+    return args[2];
+    END_HANDLE_TH_ERRORS
+}
+
+// k, v, kv_offsets, prefix_lens, accept_len, accept_path, new_prefix_lens, stream; caches of several layers, whole
+PyObject *commit_kv(PyObject *, PyObject *const *args, Py_ssize_t count) {
+    HANDLE_TH_ERRORS
+    if (count != 8 || modes_active()) return no_short_way();
+    const at::Tensor *k = tensor(args[0]), *v = tensor(args[1]), *kv_offsets = tensor(args[2], at::kLong), *prefix = tensor(args[3], at::kInt);
+    const at::Tensor *length = tensor(args[4], at::kInt), *path = tensor(args[5], at::kInt);
+    Output new_prefix;
+    void *stream;
+    if (!k || !v || !kv_offsets || !prefix || !length || !path || k->dim() != 4 || k->numel() == 0 || !k->is_contiguous() ||
+        k->sizes() != v->sizes() || k->strides() != v->strides() || path->dim() < 2 || path->size(1) > INT32_MAX || prefix->numel() > INT32_MAX ||
+        k->size(0) > INT32_MAX || !new_prefix.take(args[6], at::kInt) || !stream_of(args[7], stream))
+        return no_short_way();
+    new_prefix.make({prefix->numel()}, at::kInt, k->device());
+    const int64_t element = int64_t(k->element_size());
+    const int status = call([&] {
+        return commit_fn(int32_t(prefix->numel()), int32_t(path->size(1)), int32_t(k->size(0)), k->size(2) * k->size(3) * element, k->data_ptr(),
+                         v->data_ptr(), k->stride(1) * element, k->stride(0) * element, to<int64_t>(*kv_offsets), to<int32_t>(*prefix),
+                         to<int32_t>(*length), to<int32_t>(*path), to<int32_t>(new_prefix.t), stream);
+    });
+    return status ? PyLong_FromLong(status) : new_prefix.object();
+    END_HANDLE_TH_ERRORS
+}
+
+// logits, row_max, row_sumexp, stream
+PyObject *softmax_stats(PyObject *, PyObject *const *args, Py_ssize_t count) {
+    HANDLE_TH_ERRORS
+    const at::Tensor *logits = count != 4 || modes_active() ? nullptr : tensor(args[0]);
+    int code;
+    Output row_max, row_sumexp;
+    void *stream;
+    if (!logits || !logits_layout(*logits) || !dtype_code(*logits, code) || !row_max.take(args[1], at::kFloat) ||
+        !row_sumexp.take(args[2], at::kFloat) || !stream_of(args[3], stream))
+        return no_short_way();
+    row_max.make({logits->size(0)}, at::kFloat, logits->device());
+    row_sumexp.make({logits->size(0)}, at::kFloat, logits->device());
+    const int status = call([&] {
+        return softmax_stats_fn(logits->size(0), int32_t(logits->size(1)), code, logits->data_ptr(), logits->stride(0), to<float>(row_max.t),
+                                to<float>(row_sumexp.t), stream);
+    });
+    if (status) return PyLong_FromLong(status);
+    return Py_BuildValue("(NN)", row_max.object(), row_sumexp.object());
+    END_HANDLE_TH_ERRORS
+}
+
+// node_offsets, parent_offsets, parent_idx, tokens, logits, root_logits, draft_logits, root_draft_logits, draft_prob, accept_u, resample_u,
+// max_nodes, stream
+PyObject *accept_stochastic(PyObject *, PyObject *const *args, Py_ssize_t count) {
+    HANDLE_TH_ERRORS
+    Graph g;
+    int32_t max_nodes;
+    int code;
+    void *stream;
+    if (count != 13 || modes_active() || !g.take(args)) return no_short_way();
+    const at::Tensor *tokens = tensor(args[3], at::kInt), *prob = tensor(args[8], at::kFloat), *accept_u = tensor(args[9], at::kFloat),
+                     *resample_u = tensor(args[10], at::kFloat), *logits = tensor(args[4]);
+    if (!tokens || !prob || !accept_u || !resample_u || !logits || !logits_layout(*logits) || !dtype_code(*logits, code) ||
+        !number(args[11], max_nodes) || max_nodes < 1)
+        return no_short_way();
+    const int64_t total = logits->size(0), vocab = logits->size(1), row_stride = logits->stride(0);
+    const at::Tensor *rows[4];
+    for (int x = 0; x < 4; ++x) {
+        const at::Tensor *t = rows[x] = tensor(args[4 + x]);
+        const int64_t want = x % 2 ? g.batch : total;
+        int other;
+        if (!t || t->dim() != 2 || t->size(0) != want || t->size(1) != vocab || t->stride(1) != 1 || !dtype_code(*t, other) || other != code ||
+            (want > 1 && t->stride(0) != row_stride))
+            return no_short_way();
+    }
+    if (!stream_of(args[12], stream)) return no_short_way();
+    const c10::Device device = logits->device();
+    at::Tensor row_max = floats({total + g.batch}, device), row_sumexp = floats({total + g.batch}, device), length = ints({g.batch}, device),
+               path = ints({g.batch, max_nodes}, device), end = ints({g.batch}, device), bonus = ints({g.batch}, device);
+    gsd_stochastic_desc d = {};
+    d.batch = g.batch;
+    d.total_nodes = int32_t(total);
+    d.max_nodes = max_nodes;
+    d.vocab = int32_t(vocab);
+    d.dtype = code;
+    d.node_offsets = g.node_offsets();
+    d.parent_offsets = g.parent_offsets();
+    d.parent_idx = g.parent_idx();
+    d.tokens = to<int32_t>(*tokens);
+    d.logits = rows[0]->data_ptr();
+    d.root_logits = rows[1]->data_ptr();
+    d.draft_logits = rows[2]->data_ptr();
+    d.root_draft_logits = rows[3]->data_ptr();
+    d.row_stride = row_stride;
+    d.draft_prob = to<float>(*prob);
+    d.accept_u = to<float>(*accept_u);
+    d.resample_u = to<float>(*resample_u);
+    d.row_max = to<float>(row_max);
+    d.row_sumexp = to<float>(row_sumexp);
+    d.accept_len = to<int32_t>(length);
+    d.accept_path = to<int32_t>(path);
+    d.end_node = to<int32_t>(end);
+    d.bonus_token = to<int32_t>(bonus);
+    const int status = call([&] { return accept_stochastic_fn(&d, stream); });
+    if (status) return PyLong_FromLong(status);
+    return Py_BuildValue("(NNNNNN)", THPVariable_Wrap(length), THPVariable_Wrap(path), THPVariable_Wrap(end), THPVariable_Wrap(bonus),
+                         THPVariable_Wrap(row_max), THPVariable_Wrap(row_sumexp));
+    END_HANDLE_TH_ERRORS
+}
+
+// node_offsets, tree_parent, tokens, draft_prob, max_nodes, tau, theta_prob, theta_sib, edge_capacity, error_flag, stream
+PyObject *build_token_graph(PyObject *, PyObject *const *args, Py_ssize_t count) {
+    HANDLE_TH_ERRORS
+    if (count != 11 || modes_active()) return no_short_way();
+    const at::Tensor *nodes = tensor(args[0], at::kInt), *parent = tensor(args[1], at::kInt), *tokens = tensor(args[2], at::kInt),
+                     *prob = tensor(args[3], at::kFloat);
+    int32_t max_nodes, tau, given_capacity;
+    Output flag;
+    void *stream;
+    if (!nodes || !parent || !tokens || !prob || !number(args[4], max_nodes) || !number(args[5], tau) || !PyFloat_CheckExact(args[6]) ||
+        !PyFloat_CheckExact(args[7]) || !flag.take(args[9], at::kInt))
+        return no_short_way();
+    const double theta_prob = PyFloat_AS_DOUBLE(args[6]), theta_sib = PyFloat_AS_DOUBLE(args[7]);
+    const int64_t batch = nodes->numel() - 1, total = tokens->numel();
+    int64_t capacity = 8 * total;
+    if (args[8] != Py_None) {
+        if (!number(args[8], given_capacity)) return no_short_way();
+        capacity = given_capacity;
+    }
+    if (batch < 1 || batch >= INT32_MAX || capacity < 0 || !(std::fabs(theta_prob) <= FLT_MAX) || !(std::fabs(theta_sib) <= FLT_MAX) ||
+        !stream_of(args[10], stream))
+        return no_short_way();
+    const c10::Device device = tokens->device();
+    at::Tensor counts = ints({batch, 2}, device), offsets = ints({batch + 1}, device), parent_offsets = ints({total + 1}, device),
+               parent_idx = ints({capacity}, device), origin = ints({total}, device), flags = ints({total}, device);
+    const int status = call([&] {
+        return build_graph_fn(int32_t(batch), max_nodes, tau, float(theta_prob), float(theta_sib), to<int32_t>(*nodes), to<int32_t>(*parent),
+                              to<int32_t>(*tokens), to<float>(*prob), to<int32_t>(counts), to<int32_t>(offsets), to<int32_t>(parent_offsets),
+                              to<int32_t>(parent_idx), capacity, to<int32_t>(origin), to<int32_t>(flags), flag.given ? to<int32_t>(flag.t) : nullptr,
+                              stream);
+    });
+    if (status) return PyLong_FromLong(status);
+    return Py_BuildValue("(NNNNNN)", THPVariable_Wrap(offsets), THPVariable_Wrap(parent_offsets), THPVariable_Wrap(parent_idx),
+                         THPVariable_Wrap(origin), THPVariable_Wrap(flags), THPVariable_Wrap(counts));
+    END_HANDLE_TH_ERRORS
+}
+
 // the addresses of the library's entry points, in the order of the list at the top, and what tells the current device and stream
 PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t count) {
-    void *at[6];
-    if (count != 8) {
-        PyErr_SetString(PyExc_TypeError, "six addresses and two functions");
+    constexpr int kEntries = 12;
+    void *at[kEntries];
+    if (count != kEntries + 2) {
+        PyErr_SetString(PyExc_TypeError, "twelve addresses and two functions");
         return nullptr;
     }
-    for (int x = 0; x < 6; ++x) {
+    for (int x = 0; x < kEntries; ++x) {
         at[x] = PyLong_AsVoidPtr(args[x]);
         if (PyErr_Occurred()) return nullptr;
     }
-    build_mask_fn = reinterpret_cast<decltype(build_mask_fn)>(at[0]);
-    attention_workspace_fn = reinterpret_cast<decltype(attention_workspace_fn)>(at[1]);
-    attention_fn = reinterpret_cast<decltype(attention_fn)>(at[2]);
-    argmax_fn = reinterpret_cast<decltype(argmax_fn)>(at[3]);
-    argmax_stats_fn = reinterpret_cast<decltype(argmax_stats_fn)>(at[4]);
-    accept_fn = reinterpret_cast<decltype(accept_fn)>(at[5]);
-    Py_INCREF(args[6]);
-    Py_INCREF(args[7]);
-    device_fn = args[6];                          // kept for good, like the library
-    raw_stream_fn = args[7];
+    int next = 0;
+    auto entry = [&](auto &fn) { fn = reinterpret_cast<std::remove_reference_t<decltype(fn)>>(at[next++]); };
+    entry(build_mask_fn);
+    entry(attention_workspace_fn);
+    entry(attention_fn);
+    entry(argmax_fn);
+    entry(argmax_stats_fn);
+    entry(accept_fn);
+    entry(unmerge_fn);
+    entry(gather_fn);
+    entry(commit_fn);
+    entry(softmax_stats_fn);
+    entry(accept_stochastic_fn);
+    entry(build_graph_fn);
+    Py_INCREF(args[kEntries]);
+    Py_INCREF(args[kEntries + 1]);
+    device_fn = args[kEntries];                   // kept for good, like the library
+    raw_stream_fn = args[kEntries + 1];
     Py_RETURN_NONE;
 }
 
 #define GSD_METHOD(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(name)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {GSD_METHOD(bind), GSD_METHOD(build_mask), GSD_METHOD(node_argmax), GSD_METHOD(node_argmax_stats),
-                         GSD_METHOD(accept_longest_path), GSD_METHOD(dag_attention), {nullptr, nullptr, 0, nullptr}};
+                         GSD_METHOD(accept_longest_path), GSD_METHOD(dag_attention), GSD_METHOD(unmerge_to_tree), GSD_METHOD(gather_rows),
+                         GSD_METHOD(commit_kv), GSD_METHOD(softmax_stats), GSD_METHOD(accept_stochastic), GSD_METHOD(build_token_graph),
+                         {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

@@ -77,6 +77,51 @@ def test_results_are_the_same(args, monkeypatch, dtype):
         same(monkeypatch, lambda: gsd.gsd_dag_attention(*attention_args(a, dtype), **kw))
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_results_of_the_surrounding_calls_are_the_same(args, monkeypatch, dtype):
+    a, t, short = args, args[dtype], gsd._short
+    flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for kw in ({}, {"dag_error_flag": flag}):
+        got = both(monkeypatch, lambda: gsd.gsd_unmerge_to_tree(*a["graph"], a["n"], 32, **kw))
+        size = int(got[0][0][-1])
+        assert size > a["n"] and [x.shape for x in got[0]] == [x.shape for x in got[1]]
+        assert all(torch.equal(x[:k], y[:k]) for x, y, k in zip(*got, (2, size, size + 1, size, 1)))      # what the call writes
+    index = torch.tensor([4, 0, 0, 5], dtype=torch.int32, device="cuda")
+    for src in (t["q"], a["tokens"], t["logits"], t["logits"][:, 2:], t["q"][:1]):
+        i = index.clamp(max=src.shape[0] - 1).to(torch.int32)
+        same(monkeypatch, lambda: gsd.gsd_gather_rows(src, i))
+        same(monkeypatch, lambda: gsd.gsd_gather_rows(src, i, rows=3))
+        same(monkeypatch, lambda: gsd.gsd_gather_rows(src, i, out=torch.zeros((6, *src.shape[1:]), dtype=src.dtype, device="cuda")))
+    same(monkeypatch, lambda: gsd.gsd_softmax_stats(t["logits"]))
+    same(monkeypatch, lambda: gsd.gsd_softmax_stats(t["logits"][:, 1:]))
+    path = torch.tensor([[1, 3, 5, -1, -1, -1]], dtype=torch.int32, device="cuda")
+    length = torch.tensor([3], dtype=torch.int32, device="cuda")
+
+    def commit(cut):
+        k, v = torch.stack([t["k"]] * 3), torch.stack([t["v"]] * 3)
+        k, v = (k, v) if cut is None else (k[0], v[0]) if cut == 3 else (k[:, :, :1], v[:, :, :1])
+        return gsd.gsd_commit_kv(k, v, a["kv_offsets"], a["prefix"], length, path), k, v
+    for cut in (None, 3, 1):
+        same(monkeypatch, lambda: commit(cut))
+    n, u = a["n"], torch.linspace(0, 0.9, a["n"], device="cuda")
+    for p, q in ((t["logits"], t["logits"].roll(1, 0)), (t["logits"][:, 3:], t["logits"].roll(1, 0)[:, 3:])):
+        same(monkeypatch, lambda: gsd.gsd_accept_stochastic(*a["graph"], a["tokens"], p, p[2:3], q, q[2:3], u + 0.05, u, u[:1], n))
+    tree = (a["graph"][0], torch.tensor([-1, -1, 0, 0, 1, 2], dtype=torch.int32, device="cuda"),
+            torch.tensor([1, 2, 2, 3, 3, 3], dtype=torch.int32, device="cuda"), u)
+    for kw in ({}, {"edge_capacity": 20}, {"error_flag": flag}):
+        got = both(monkeypatch, lambda: gsd.gsd_build_token_graph(*tree, n, 1, 0.0, 0.0, **kw))
+        nodes, edges = got[0][5][0].tolist()
+        assert [x.shape for x in got[0]] == [x.shape for x in got[1]]
+        assert all(torch.equal(x[:k], y[:k]) for x, y, k in zip(*got, (2, nodes + 1, edges, nodes, nodes, 1)))
+    # and all of these are short ways
+    assert short.unmerge_to_tree(*a["graph"], n, 32, None, None) is not None and short.gather_rows(t["q"], index, None, None, None) is not None
+    assert short.softmax_stats(t["logits"], None, None, None) is not None
+    assert short.commit_kv(torch.stack([t["k"]] * 3), torch.stack([t["v"]] * 3), a["kv_offsets"], a["prefix"], length, path, None, None) is not None
+    assert short.accept_stochastic(*a["graph"], a["tokens"], *[t["logits"], t["logits"][:1]] * 2, u, u, u[:1], n, None) is not None
+    assert short.build_token_graph(*tree, n, 1, 0.0, 0.0, None, None, None) is not None
+    torch.cuda.synchronize()
+
+
 def test_the_callers_tensors_come_back(args, monkeypatch):
     a, t = args, args[torch.bfloat16]
     kept = {name: torch.empty(shape, dtype=torch.int32, device="cuda") for name, shape in
@@ -108,7 +153,7 @@ class Subclass(torch.Tensor):
 def test_exceptions_are_the_same(args, monkeypatch):
     a, t = args, args[torch.float32]
     att = attention_args(a, torch.float32)
-    half, host, wrong = t["q"].half(), a["graph"][0].cpu(), a["graph"][0].long()
+    half, host, wrong, u = t["q"].half(), a["graph"][0].cpu(), a["graph"][0].long(), torch.ones(a["n"], device="cuda")
     calls = [lambda: gsd.gsd_build_mask(host, *a["graph"][1:], a["n"]), lambda: gsd.gsd_build_mask(wrong, *a["graph"][1:], a["n"]),
              lambda: gsd.gsd_build_mask(*a["graph"], 0), lambda: gsd.gsd_build_mask(*a["graph"], 513), lambda: gsd.gsd_build_mask(*a["graph"], 1 << 40),
              lambda: gsd.gsd_build_mask(*a["graph"], a["n"], mask=a["mask"][:3]), lambda: gsd.gsd_build_mask(*a["graph"], 80, words_per_row=1),
@@ -119,6 +164,20 @@ def test_exceptions_are_the_same(args, monkeypatch):
              lambda: gsd.gsd_dag_attention(half, *att[1:]), lambda: gsd.gsd_dag_attention(att[0][:, :3], *att[1:]),
              lambda: gsd.gsd_dag_attention(*att[:2], att[2][:-1], *att[3:]), lambda: gsd.gsd_dag_attention(*att[:-1], -1.0),
              lambda: gsd.gsd_dag_attention(*att[:-1], 1e39), lambda: gsd.gsd_dag_attention(*att, num_splits=-1),
+             lambda: gsd.gsd_unmerge_to_tree(*a["graph"], a["n"], 0), lambda: gsd.gsd_unmerge_to_tree(*a["graph"], 513, 8),
+             lambda: gsd.gsd_unmerge_to_tree(wrong, *a["graph"][1:], a["n"], 8), lambda: gsd.gsd_gather_rows(t["q"], wrong),
+             lambda: gsd.gsd_gather_rows(t["q"], a["tokens"], out=half), lambda: gsd.gsd_gather_rows(t["q"][:0], a["tokens"]),
+             lambda: gsd.gsd_gather_rows(half[:, 0, :1], a["tokens"]), lambda: gsd.gsd_softmax_stats(half.flatten(1)),
+             lambda: gsd.gsd_softmax_stats(t["logits"][:0]),
+             lambda: gsd.gsd_commit_kv(t["k"], t["v"][:3], a["kv_offsets"], a["prefix"], a["root_pred"], a["tokens"][None]),
+             lambda: gsd.gsd_commit_kv(t["k"][None], t["v"][None], a["kv_offsets"], a["prefix"], a["root_pred"], a["tokens"][None],
+                                       new_prefix_lens=a["prefix"]),
+             lambda: gsd.gsd_accept_stochastic(*a["graph"], a["tokens"], t["logits"], t["logits"][:1], t["logits"], t["logits"][:2], u, u,
+                                               u[:1], a["n"]),
+             lambda: gsd.gsd_accept_stochastic(*a["graph"], a["tokens"], *[t["logits"], t["logits"][:1]] * 2, u, u, u[:1], 513),
+             lambda: gsd.gsd_build_token_graph(a["graph"][0], a["tokens"], a["tokens"], u, a["n"], 0, 0.0, 0.0),
+             lambda: gsd.gsd_build_token_graph(a["graph"][0], a["tokens"], a["tokens"], u, a["n"], 1, -1.0, 0.0),
+             lambda: gsd.gsd_build_token_graph(a["graph"][0], a["tokens"], a["tokens"], u, a["n"], 1, 0.0, 0.0, edge_capacity=0),
              lambda: gsd.gsd_dag_attention(*att, lse=wrong), lambda: gsd.gsd_dag_attention(*att[:6], att[6][:, 0], *att[7:])]
     for k, call in enumerate(calls):
         x, y = both(monkeypatch, call)
