@@ -103,13 +103,15 @@ struct Output {
 
 PyObject *no_short_way() { Py_RETURN_NONE; }
 
+// The outputs' allocations and the library's call, without the interpreter's lock, as torch.empty and ctypes do them: another thread
+// may need it before the allocator or the device lets this one go on.  What is thrown leaves with the lock taken again.
 template <typename F>
-int call(F &&f) {           // without the interpreter's lock, as ctypes calls it
-    int status;
-    Py_BEGIN_ALLOW_THREADS
-    status = f();
-    Py_END_ALLOW_THREADS
-    return status;
+int call(F &&f) {
+    struct Unlocked {
+        PyThreadState *state = PyEval_SaveThread();
+        ~Unlocked() { PyEval_RestoreThread(state); }
+    } unlocked;
+    return f();
 }
 
 struct Graph {
@@ -161,8 +163,8 @@ PyObject *build_mask(PyObject *, PyObject *const *args, Py_ssize_t count) {
     if (args[4] == Py_None) words = (max_nodes - 1) / 64 + 1;
     else if (!number(args[4], words) || words < 1) return no_short_way();
     if (mask.given && mask.t.numel() != int64_t(g.total) * words) return no_short_way();
-    mask.make({g.total, words}, at::kLong, g.nodes->device());
     const int status = call([&] {
+        mask.make({g.total, words}, at::kLong, g.nodes->device());
         return build_mask_fn(g.batch, max_nodes, words, g.node_offsets(), g.parent_offsets(), g.parent_idx(),
                              static_cast<uint64_t *>(mask.t.data_ptr()), flag.given ? static_cast<int32_t *>(flag.t.data_ptr()) : nullptr, stream);
     });
@@ -180,12 +182,12 @@ PyObject *argmax(PyObject *const *args, bool stats) {
         (stats && (!row_max.take(args[2], at::kFloat) || !row_sumexp.take(args[3], at::kFloat))) || !stream_of(args[stats ? 4 : 2], stream))
         return no_short_way();
     const int32_t rows = int32_t(logits->size(0)), vocab = int32_t(logits->size(1));
-    pred.make({rows}, at::kInt, logits->device());
-    if (stats) {
-        row_max.make({rows}, at::kFloat, logits->device());
-        row_sumexp.make({rows}, at::kFloat, logits->device());
-    }
     const int status = call([&] {
+        pred.make({rows}, at::kInt, logits->device());
+        if (stats) {
+            row_max.make({rows}, at::kFloat, logits->device());
+            row_sumexp.make({rows}, at::kFloat, logits->device());
+        }
         int32_t *to = static_cast<int32_t *>(pred.t.data_ptr());
         if (!stats) return argmax_fn(rows, vocab, code, logits->data_ptr(), logits->stride(0), to, stream);
         return argmax_stats_fn(rows, vocab, code, logits->data_ptr(), logits->stride(0), to, static_cast<float *>(row_max.t.data_ptr()),
@@ -229,11 +231,11 @@ PyObject *accept_longest_path(PyObject *, PyObject *const *args, Py_ssize_t coun
         return no_short_way();
     }
     const c10::Device device = tokens->device();
-    pred.make({total}, at::kInt, device);
-    length.make({g.batch}, at::kInt, device);
-    path.make({g.batch, max_nodes}, at::kInt, device);
-    bonus.make({g.batch}, at::kInt, device);
     const int status = call([&] {
+        pred.make({total}, at::kInt, device);
+        length.make({g.batch}, at::kInt, device);
+        path.make({g.batch, max_nodes}, at::kInt, device);
+        bonus.make({g.batch}, at::kInt, device);
         auto ints = [](const at::Tensor &t) { return static_cast<int32_t *>(t.data_ptr()); };
         return accept_fn(g.batch, total, max_nodes, g.node_offsets(), g.parent_offsets(), g.parent_idx(), ints(*tokens),
                          logits ? logits->data_ptr() : nullptr, code, logits ? int32_t(logits->size(1)) : 0, logits ? logits->stride(0) : 0,
@@ -271,8 +273,7 @@ PyObject *dag_attention(PyObject *, PyObject *const *args, Py_ssize_t count) {
     const at::Tensor *given = args[10] == Py_None ? nullptr : tensor(args[10]);
     if (args[10] != Py_None && (!given || given->dim() != 3)) return no_short_way();
     const bool return_lse = args[14] == Py_True;
-    at::Tensor out = given ? *given : at::empty(q->sizes(), at::TensorOptions().dtype(q->scalar_type()).device(q->device()));
-    if (return_lse) lse.make({q->size(0), q->size(1)}, at::kFloat, q->device());
+    at::Tensor out, workspace;
     d.batch = int32_t(prefix->numel());
     d.total_nodes = int32_t(q->size(0));
     d.num_q_heads = int32_t(q->size(1));
@@ -282,8 +283,6 @@ PyObject *dag_attention(PyObject *, PyObject *const *args, Py_ssize_t count) {
     d.words_per_row = int32_t(mask->size(1));
     d.softmax_scale = float(scale);
     d.q = q->data_ptr();
-    d.o = out.data_ptr();
-    d.lse = lse.t.defined() ? static_cast<float *>(lse.t.data_ptr()) : nullptr;
     d.k = k->data_ptr();
     d.v = v->data_ptr();
     d.kv_offsets = static_cast<const int64_t *>(kv_offsets->data_ptr());
@@ -292,19 +291,27 @@ PyObject *dag_attention(PyObject *, PyObject *const *args, Py_ssize_t count) {
     d.mask = static_cast<const uint64_t *>(mask->data_ptr());
     d.q_token_stride = q->stride(0);
     d.q_head_stride = q->stride(1);
-    d.o_token_stride = out.stride(0);
-    d.o_head_stride = out.stride(1);
     d.kv_token_stride = k->stride(0);
     d.kv_head_stride = k->stride(1);
-    const size_t need = attention_workspace_fn(&d);
-    if (need == size_t(-1)) return no_short_way();
-    at::Tensor workspace;
-    if (need > 0) {
-        workspace = at::empty({int64_t(need)}, at::TensorOptions().dtype(at::kByte).device(q->device()));
-        d.workspace = workspace.data_ptr();
-        d.workspace_bytes = need;
-    }
-    const int status = call([&] { return attention_fn(&d, stream); });
+    bool sized = false;
+    const int status = call([&] {
+        out = given ? *given : at::empty(q->sizes(), at::TensorOptions().dtype(q->scalar_type()).device(q->device()));
+        if (return_lse) lse.make({q->size(0), q->size(1)}, at::kFloat, q->device());
+        d.o = out.data_ptr();
+        d.o_token_stride = out.stride(0);
+        d.o_head_stride = out.stride(1);
+        d.lse = lse.t.defined() ? static_cast<float *>(lse.t.data_ptr()) : nullptr;
+        const size_t need = attention_workspace_fn(&d);
+        sized = need != size_t(-1);
+        if (!sized) return 0;
+        if (need > 0) {
+            workspace = at::empty({int64_t(need)}, at::TensorOptions().dtype(at::kByte).device(q->device()));
+            d.workspace = workspace.data_ptr();
+            d.workspace_bytes = need;
+        }
+        return attention_fn(&d, stream);
+    });
+    if (!sized) return no_short_way();
     if (status) return PyLong_FromLong(status);
     PyObject *result = args[10];
     if (given) Py_INCREF(result);
@@ -331,9 +338,10 @@ PyObject *unmerge_to_tree(PyObject *, PyObject *const *args, Py_ssize_t count) {
         return no_short_way();
     const c10::Device device = g.nodes->device();
     const int64_t bound = int64_t(g.batch) * cap;
-    at::Tensor offsets = ints({g.batch + 1}, device), parent = ints({bound}, device), parent_offsets = ints({bound + 1}, device),
-               origin = ints({bound}, device), paths = at::empty({g.batch}, at::TensorOptions().dtype(at::kLong).device(device));
+    at::Tensor offsets, parent, parent_offsets, origin, paths;
     const int status = call([&] {
+        offsets = ints({g.batch + 1}, device), parent = ints({bound}, device), parent_offsets = ints({bound + 1}, device);
+        origin = ints({bound}, device), paths = at::empty({g.batch}, at::TensorOptions().dtype(at::kLong).device(device));
         return unmerge_fn(g.batch, max_nodes, cap, g.node_offsets(), g.parent_offsets(), g.parent_idx(), to<int32_t>(offsets), to<int32_t>(parent),
                           to<int32_t>(parent_offsets), to<int32_t>(origin), to<int64_t>(paths), flag.given ? to<int32_t>(flag.t) : nullptr, stream);
     });
@@ -363,16 +371,18 @@ PyObject *gather_rows(PyObject *, PyObject *const *args, Py_ssize_t count) {
         return no_short_way();
     void *stream;
     if (!stream_of(args[4], stream)) return no_short_way();
-    at::Tensor out;
-    if (given) {
-        out = *given;
-    } else {
-        std::vector<int64_t> sizes = src->sizes().vec();
-        sizes[0] = rows;
-        out = at::empty(sizes, at::TensorOptions().dtype(src->scalar_type()).device(src->device()));
-    }
     const int64_t row_bytes = src->numel() / src->size(0) * int64_t(src->element_size());
-    const int status = call([&] { return gather_fn(rows, row_bytes, src->data_ptr(), src->size(0), row_bytes, to<int32_t>(*index), out.data_ptr(), row_bytes, stream); });
+    at::Tensor out;
+    const int status = call([&] {
+        if (given) {
+            out = *given;
+        } else {
+            std::vector<int64_t> sizes = src->sizes().vec();
+            sizes[0] = rows;
+            out = at::empty(sizes, at::TensorOptions().dtype(src->scalar_type()).device(src->device()));
+        }
+        return gather_fn(rows, row_bytes, src->data_ptr(), src->size(0), row_bytes, to<int32_t>(*index), out.data_ptr(), row_bytes, stream);
+    });
     if (status) return PyLong_FromLong(status);
     if (!given) return THPVariable_Wrap(out);
     Py_INCREF(args[2]);
@@ -392,9 +402,9 @@ PyObject *commit_kv(PyObject *, PyObject *const *args, Py_ssize_t count) {
         k->sizes() != v->sizes() || k->strides() != v->strides() || path->dim() < 2 || path->size(1) > INT32_MAX || prefix->numel() > INT32_MAX ||
         k->size(0) > INT32_MAX || !new_prefix.take(args[6], at::kInt) || !stream_of(args[7], stream))
         return no_short_way();
-    new_prefix.make({prefix->numel()}, at::kInt, k->device());
     const int64_t element = int64_t(k->element_size());
     const int status = call([&] {
+        new_prefix.make({prefix->numel()}, at::kInt, k->device());
         return commit_fn(int32_t(prefix->numel()), int32_t(path->size(1)), int32_t(k->size(0)), k->size(2) * k->size(3) * element, k->data_ptr(),
                          v->data_ptr(), k->stride(1) * element, k->stride(0) * element, to<int64_t>(*kv_offsets), to<int32_t>(*prefix),
                          to<int32_t>(*length), to<int32_t>(*path), to<int32_t>(new_prefix.t), stream);
@@ -413,9 +423,9 @@ PyObject *softmax_stats(PyObject *, PyObject *const *args, Py_ssize_t count) {
     if (!logits || !logits_layout(*logits) || !dtype_code(*logits, code) || !row_max.take(args[1], at::kFloat) ||
         !row_sumexp.take(args[2], at::kFloat) || !stream_of(args[3], stream))
         return no_short_way();
-    row_max.make({logits->size(0)}, at::kFloat, logits->device());
-    row_sumexp.make({logits->size(0)}, at::kFloat, logits->device());
     const int status = call([&] {
+        row_max.make({logits->size(0)}, at::kFloat, logits->device());
+        row_sumexp.make({logits->size(0)}, at::kFloat, logits->device());
         return softmax_stats_fn(logits->size(0), int32_t(logits->size(1)), code, logits->data_ptr(), logits->stride(0), to<float>(row_max.t),
                                 to<float>(row_sumexp.t), stream);
     });
@@ -450,8 +460,7 @@ PyObject *accept_stochastic(PyObject *, PyObject *const *args, Py_ssize_t count)
     }
     if (!stream_of(args[12], stream)) return no_short_way();
     const c10::Device device = logits->device();
-    at::Tensor row_max = floats({total + g.batch}, device), row_sumexp = floats({total + g.batch}, device), length = ints({g.batch}, device),
-               path = ints({g.batch, max_nodes}, device), end = ints({g.batch}, device), bonus = ints({g.batch}, device);
+    at::Tensor row_max, row_sumexp, length, path, end, bonus;
     gsd_stochastic_desc d = {};
     d.batch = g.batch;
     d.total_nodes = int32_t(total);
@@ -470,13 +479,17 @@ PyObject *accept_stochastic(PyObject *, PyObject *const *args, Py_ssize_t count)
     d.draft_prob = to<float>(*prob);
     d.accept_u = to<float>(*accept_u);
     d.resample_u = to<float>(*resample_u);
-    d.row_max = to<float>(row_max);
-    d.row_sumexp = to<float>(row_sumexp);
-    d.accept_len = to<int32_t>(length);
-    d.accept_path = to<int32_t>(path);
-    d.end_node = to<int32_t>(end);
-    d.bonus_token = to<int32_t>(bonus);
-    const int status = call([&] { return accept_stochastic_fn(&d, stream); });
+    const int status = call([&] {
+        row_max = floats({total + g.batch}, device), row_sumexp = floats({total + g.batch}, device), length = ints({g.batch}, device);
+        path = ints({g.batch, max_nodes}, device), end = ints({g.batch}, device), bonus = ints({g.batch}, device);
+        d.row_max = to<float>(row_max);
+        d.row_sumexp = to<float>(row_sumexp);
+        d.accept_len = to<int32_t>(length);
+        d.accept_path = to<int32_t>(path);
+        d.end_node = to<int32_t>(end);
+        d.bonus_token = to<int32_t>(bonus);
+        return accept_stochastic_fn(&d, stream);
+    });
     if (status) return PyLong_FromLong(status);
     return Py_BuildValue("(NNNNNN)", THPVariable_Wrap(length), THPVariable_Wrap(path), THPVariable_Wrap(end), THPVariable_Wrap(bonus),
                          THPVariable_Wrap(row_max), THPVariable_Wrap(row_sumexp));
@@ -506,9 +519,10 @@ PyObject *build_token_graph(PyObject *, PyObject *const *args, Py_ssize_t count)
         !stream_of(args[10], stream))
         return no_short_way();
     const c10::Device device = tokens->device();
-    at::Tensor counts = ints({batch, 2}, device), offsets = ints({batch + 1}, device), parent_offsets = ints({total + 1}, device),
-               parent_idx = ints({capacity}, device), origin = ints({total}, device), flags = ints({total}, device);
+    at::Tensor counts, offsets, parent_offsets, parent_idx, origin, flags;
     const int status = call([&] {
+        counts = ints({batch, 2}, device), offsets = ints({batch + 1}, device), parent_offsets = ints({total + 1}, device);
+        parent_idx = ints({capacity}, device), origin = ints({total}, device), flags = ints({total}, device);
         return build_graph_fn(int32_t(batch), max_nodes, tau, float(theta_prob), float(theta_sib), to<int32_t>(*nodes), to<int32_t>(*parent),
                               to<int32_t>(*tokens), to<float>(*prob), to<int32_t>(counts), to<int32_t>(offsets), to<int32_t>(parent_offsets),
                               to<int32_t>(parent_idx), capacity, to<int32_t>(origin), to<int32_t>(flags), flag.given ? to<int32_t>(flag.t) : nullptr,

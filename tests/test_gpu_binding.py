@@ -204,3 +204,12 @@ def test_other_tensors_go_the_long_way(args):
     assert torch.equal(pred, gsd.gsd_node_argmax(t["logits"]))
     assert torch.equal(gsd.gsd_node_argmax(t["logits"].as_subclass(Subclass)), pred)
     assert torch.equal(gsd.gsd_node_argmax(torch.nn.Parameter(t["logits"])), pred)
+
+
+def test_an_allocation_that_fails(args, monkeypatch):
+    """2^31 - 1 words for each of 2^16 nodes: more than any memory.  The exception of torch.empty, and calls go on after it."""
+    nodes, _, parents = args["graph"]
+    offsets = torch.zeros((1 << 16) + 1, dtype=torch.int32, device="cuda")
+    got = both(monkeypatch, lambda: gsd.gsd_build_mask(nodes, offsets, parents, 6, words_per_row=2**31 - 1))
+    assert [x[0] for x in got] == [torch.OutOfMemoryError] * 2
+    same(monkeypatch, lambda: gsd.gsd_build_mask(*args["graph"], args["n"]))
