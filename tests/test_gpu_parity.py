@@ -368,6 +368,15 @@ def test_attention_strided_layouts_and_wide_mask_rows(gpu, ref):
     assert torch.equal(out.contiguous().view(torch.int16), base.view(torch.int16))
 
 
+@pytest.mark.parametrize("splits", [2, 4, 5, 8, 9, 17, 33])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_merge_of_any_number_of_splits(gpu, ref, dtype, D, splits):
+    """Up to and past the outputs that the merge fetches first (4 or 8) and the 16 or 32 lanes of a row; rows over a work-group's end."""
+    rng = np.random.default_rng(1200 + D + splits)
+    check_attention(gpu, ref, custom_workload(rng, [3, 4], [2300, 40], 3, 3, D, dtype), num_splits=splits)
+
+
 @pytest.mark.parametrize("splits", [1, 4])
 @pytest.mark.parametrize("D", [64, 128])
 def test_attention_fp32_strided_layouts(gpu, D, splits):
