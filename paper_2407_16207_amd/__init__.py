@@ -184,14 +184,17 @@ def _dtype_code(t) -> int:
     return code
 
 
-def _require(t, dtype, name):
-    if t.is_cuda and t.dtype is dtype and t.is_contiguous():
+def _require(t, dtype, name, least=0):
+    """`least`: elements that a call writes (or, of an input, reads); the kernels know no end of a buffer."""
+    if t.is_cuda and t.dtype is dtype and t.is_contiguous() and t.numel() >= least:
         return
     if not t.is_cuda:
         raise ValueError(f"{name} must live on the GPU")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
-    raise ValueError(f"{name} must be contiguous")
+    if not t.is_contiguous():
+        raise ValueError(f"{name} must be contiguous")
+    raise ValueError(f"{name} must hold {least} elements, has {t.numel()}")
 
 
 def _require_graph(node_offsets, parent_offsets, parent_idx):
@@ -254,6 +257,13 @@ def make_attn_desc(q, k, v, kv_offsets, prefix_lens, node_offsets, mask, max_nod
     _require(mask, torch.int64, "mask")
     total_nodes, num_q_heads, head_dim = q.shape
     o_stride = out.stride() if out is not None else (0, 0)
+    if out is not None and (out.dtype is not q.dtype or len(o_stride) != 3 or o_stride[2] != 1 or
+                            any(has < needs for has, needs in zip(out.shape, q.shape))):
+        raise ValueError("out must have q's dtype, q's shape or more in every dim, and a contiguous last dim")
+    if out is not None and out.device != q.device and not out.is_cuda and not out.is_pinned():
+        raise ValueError("out must live on the GPU")
+    if lse is not None and lse.numel() < total_nodes * num_q_heads:
+        raise ValueError(f"lse must hold {total_nodes * num_q_heads} elements, has {lse.numel()}")
     return _packed(
         AttnDesc, _ATTN_FORMAT,
         prefix_lens.numel(), total_nodes, int(max_nodes), int(max_prefix), num_q_heads, k.shape[1], head_dim, code,
@@ -331,7 +341,7 @@ def gsd_node_argmax(logits, pred=None, stream=None):
     rows, vocab, row_stride = _logits_layout(logits)
     if pred is None:
         pred = torch.empty(rows, dtype=torch.int32, device=logits.device)
-    _require(pred, torch.int32, "pred")
+    _require(pred, torch.int32, "pred", rows)
     lib = _lib or load_library()
     _check(lib.gsd_node_argmax(rows, vocab, _dtype_code(logits), logits.data_ptr(), row_stride, pred.data_ptr(),
                                _stream_ptr(stream)))
@@ -351,9 +361,9 @@ def gsd_node_argmax_stats(logits, pred=None, row_max=None, row_sumexp=None, stre
     pred = torch.empty(rows, dtype=torch.int32, device=logits.device) if pred is None else pred
     row_max = torch.empty(rows, dtype=torch.float32, device=logits.device) if row_max is None else row_max
     row_sumexp = torch.empty(rows, dtype=torch.float32, device=logits.device) if row_sumexp is None else row_sumexp
-    _require(pred, torch.int32, "pred")
-    _require(row_max, torch.float32, "row_max")
-    _require(row_sumexp, torch.float32, "row_sumexp")
+    _require(pred, torch.int32, "pred", rows)
+    _require(row_max, torch.float32, "row_max", rows)
+    _require(row_sumexp, torch.float32, "row_sumexp", rows)
     lib = _lib or load_library()
     _check(lib.gsd_node_argmax_stats(rows, vocab, _dtype_code(logits), logits.data_ptr(), row_stride, pred.data_ptr(),
                                      row_max.data_ptr(), row_sumexp.data_ptr(), _stream_ptr(stream)))
@@ -382,13 +392,13 @@ def gsd_accept_longest_path(node_offsets, parent_offsets, parent_idx, tokens, ro
         if logits is None:
             raise ValueError("give logits or pred")
         pred = torch.empty(total, dtype=torch.int32, device=dev)
-    _require(pred, torch.int32, "pred")
+    _require(pred, torch.int32, "pred", total)
     accept_len = torch.empty(batch, dtype=torch.int32, device=dev) if accept_len is None else accept_len
     accept_path = torch.empty((batch, max_nodes), dtype=torch.int32, device=dev) if accept_path is None else accept_path
     bonus_token = torch.empty(batch, dtype=torch.int32, device=dev) if bonus_token is None else bonus_token
-    _require(accept_len, torch.int32, "accept_len")
-    _require(accept_path, torch.int32, "accept_path")
-    _require(bonus_token, torch.int32, "bonus_token")
+    _require(accept_len, torch.int32, "accept_len", batch)
+    _require(accept_path, torch.int32, "accept_path", batch * max_nodes)
+    _require(bonus_token, torch.int32, "bonus_token", batch)
     if logits is not None:
         message = "logits must be a GPU tensor [T, vocab] with a contiguous last dim"
         rows, vocab, row_stride = _logits_layout(logits, message)
@@ -494,7 +504,7 @@ def gsd_commit_kv(k, v, kv_offsets, prefix_lens, accept_len, accept_path, new_pr
     max_nodes = accept_path.shape[1]
     if new_prefix_lens is None:
         new_prefix_lens = torch.empty(batch, dtype=torch.int32, device=k.device)
-    _require(new_prefix_lens, torch.int32, "new_prefix_lens")
+    _require(new_prefix_lens, torch.int32, "new_prefix_lens", batch)
     es = k.element_size()
     layers, _, heads, head_dim = k.shape
     layer_stride, token_stride = k.stride()[:2]
@@ -517,8 +527,8 @@ def gsd_softmax_stats(logits, row_max=None, row_sumexp=None, stream=None):
     rows, vocab, row_stride = _logits_layout(logits)
     row_max = torch.empty(rows, dtype=torch.float32, device=logits.device) if row_max is None else row_max
     row_sumexp = torch.empty(rows, dtype=torch.float32, device=logits.device) if row_sumexp is None else row_sumexp
-    _require(row_max, torch.float32, "row_max")
-    _require(row_sumexp, torch.float32, "row_sumexp")
+    _require(row_max, torch.float32, "row_max", rows)
+    _require(row_sumexp, torch.float32, "row_sumexp", rows)
     lib = _lib or load_library()
     _check(lib.gsd_softmax_stats(rows, vocab, _dtype_code(logits), logits.data_ptr(), row_stride, row_max.data_ptr(),
                                  row_sumexp.data_ptr(), _stream_ptr(stream)))

@@ -79,14 +79,14 @@ bool dtype_code(const at::Tensor &t, int &code) {
 
 bool logits_layout(const at::Tensor &t) { return t.dim() == 2 && t.stride(1) == 1 && t.size(0) <= INT32_MAX && t.size(1) <= INT32_MAX; }
 
-// An output: the caller's tensor, which has to be of the type and contiguous, or a new one.
+// An output: the caller's tensor, which has to be of the type, contiguous and large enough, or a new one.
 struct Output {
     PyObject *given = nullptr;
     at::Tensor t;
-    bool take(PyObject *o, at::ScalarType type) {
+    bool take(PyObject *o, at::ScalarType type, int64_t least = 0) {
         if (o == Py_None) return true;
         const at::Tensor *x = tensor(o, type);
-        if (!x) return false;
+        if (!x || x->numel() < least) return false;
         given = o;
         t = *x;
         return true;
@@ -178,8 +178,9 @@ PyObject *argmax(PyObject *const *args, bool stats) {
     int code;
     Output pred, row_max, row_sumexp;
     void *stream;
-    if (!logits || !logits_layout(*logits) || !dtype_code(*logits, code) || !pred.take(args[1], at::kInt) ||
-        (stats && (!row_max.take(args[2], at::kFloat) || !row_sumexp.take(args[3], at::kFloat))) || !stream_of(args[stats ? 4 : 2], stream))
+    if (!logits || !logits_layout(*logits) || !dtype_code(*logits, code) || !pred.take(args[1], at::kInt, logits->size(0)) ||
+        (stats && (!row_max.take(args[2], at::kFloat, logits->size(0)) || !row_sumexp.take(args[3], at::kFloat, logits->size(0)))) ||
+        !stream_of(args[stats ? 4 : 2], stream))
         return no_short_way();
     const int32_t rows = int32_t(logits->size(0)), vocab = int32_t(logits->size(1));
     const int status = call([&] {
@@ -218,8 +219,9 @@ PyObject *accept_longest_path(PyObject *, PyObject *const *args, Py_ssize_t coun
     void *stream;
     if (count != 12 || modes_active() || !g.take(args)) return no_short_way();
     const at::Tensor *tokens = tensor(args[3], at::kInt), *root_pred = tensor(args[4], at::kInt);
-    if (!tokens || !root_pred || tokens->numel() > INT32_MAX || !number(args[5], max_nodes) || max_nodes < 1 || !pred.take(args[7], at::kInt) ||
-        !length.take(args[8], at::kInt) || !path.take(args[9], at::kInt) || !bonus.take(args[10], at::kInt) || !stream_of(args[11], stream))
+    if (!tokens || !root_pred || tokens->numel() > INT32_MAX || !number(args[5], max_nodes) || max_nodes < 1 ||
+        !pred.take(args[7], at::kInt, tokens->numel()) || !length.take(args[8], at::kInt, g.batch) ||
+        !path.take(args[9], at::kInt, int64_t(g.batch) * max_nodes) || !bonus.take(args[10], at::kInt, g.batch) || !stream_of(args[11], stream))
         return no_short_way();
     const int32_t total = int32_t(tokens->numel());
     const at::Tensor *logits = nullptr;
@@ -263,7 +265,8 @@ PyObject *dag_attention(PyObject *, PyObject *const *args, Py_ssize_t count) {
         return no_short_way();
     Output lse;
     void *stream;
-    if (!number(args[7], d.max_nodes) || !number(args[8], d.max_prefix) || !PyFloat_CheckExact(args[9]) || !lse.take(args[11], at::kFloat) ||
+    if (!number(args[7], d.max_nodes) || !number(args[8], d.max_prefix) || !PyFloat_CheckExact(args[9]) ||
+        !lse.take(args[11], at::kFloat, q->size(0) * q->size(1)) ||
         !number(args[12], d.num_splits) || !number(args[13], d.wg_waves) || !PyBool_Check(args[14]) || !stream_of(args[15], stream))
         return no_short_way();
     const double scale = PyFloat_AS_DOUBLE(args[9]);
@@ -271,7 +274,9 @@ PyObject *dag_attention(PyObject *, PyObject *const *args, Py_ssize_t count) {
     for (int64_t x : {prefix->numel(), q->size(0), q->size(1), q->size(2), k->size(1), mask->size(1)})
         if (x > INT32_MAX) return no_short_way();
     const at::Tensor *given = args[10] == Py_None ? nullptr : tensor(args[10]);
-    if (args[10] != Py_None && (!given || given->dim() != 3)) return no_short_way();
+    if (args[10] != Py_None && (!given || given->dim() != 3 || given->scalar_type() != q->scalar_type() || given->stride(2) != 1 ||
+                                given->size(0) < q->size(0) || given->size(1) < q->size(1) || given->size(2) < q->size(2)))
+        return no_short_way();
     const bool return_lse = args[14] == Py_True;
     at::Tensor out, workspace;
     d.batch = int32_t(prefix->numel());
@@ -400,7 +405,7 @@ PyObject *commit_kv(PyObject *, PyObject *const *args, Py_ssize_t count) {
     void *stream;
     if (!k || !v || !kv_offsets || !prefix || !length || !path || k->dim() != 4 || k->numel() == 0 || !k->is_contiguous() ||
         k->sizes() != v->sizes() || k->strides() != v->strides() || path->dim() < 2 || path->size(1) > INT32_MAX || prefix->numel() > INT32_MAX ||
-        k->size(0) > INT32_MAX || !new_prefix.take(args[6], at::kInt) || !stream_of(args[7], stream))
+        k->size(0) > INT32_MAX || !new_prefix.take(args[6], at::kInt, prefix->numel()) || !stream_of(args[7], stream))
         return no_short_way();
     const int64_t element = int64_t(k->element_size());
     const int status = call([&] {
@@ -420,8 +425,8 @@ PyObject *softmax_stats(PyObject *, PyObject *const *args, Py_ssize_t count) {
     int code;
     Output row_max, row_sumexp;
     void *stream;
-    if (!logits || !logits_layout(*logits) || !dtype_code(*logits, code) || !row_max.take(args[1], at::kFloat) ||
-        !row_sumexp.take(args[2], at::kFloat) || !stream_of(args[3], stream))
+    if (!logits || !logits_layout(*logits) || !dtype_code(*logits, code) || !row_max.take(args[1], at::kFloat, logits->size(0)) ||
+        !row_sumexp.take(args[2], at::kFloat, logits->size(0)) || !stream_of(args[3], stream))
         return no_short_way();
     const int status = call([&] {
         row_max.make({logits->size(0)}, at::kFloat, logits->device());

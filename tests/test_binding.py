@@ -141,3 +141,63 @@ def test_empty_sources_and_caches_are_refused():
     for shape in ((0, 4, 1, 8), (2, 0, 1, 8)):
         with pytest.raises(IndexError):
             gsd.gsd_commit_kv(on_gpu(*shape), on_gpu(*shape), on_gpu(1, dtype=torch.int64), on_gpu(1), on_gpu(1), on_gpu(1, 4))
+
+
+def recording_library(monkeypatch):
+    """Stands in for the library: every call is noted and succeeds."""
+    class Library:
+        calls = []
+
+        def __getattr__(self, name):
+            return lambda *args: self.calls.append(name) or 0
+    gsd._import_torch()
+    monkeypatch.setattr(gsd, "_lib", Library())
+    monkeypatch.setattr(gsd, "_raw_stream", lambda device: 3)
+    monkeypatch.setattr(gsd, "_device", lambda: 0)
+    return Library.calls
+
+
+def calls_with_outputs():
+    """(call, its outputs as keywords, of the size they have to have)"""
+    rows = on_gpu(4, 8, dtype=torch.float32)
+    f4 = dict(dtype=torch.float32)
+    yield (lambda **kw: gsd.gsd_node_argmax(rows, **kw), {"pred": on_gpu(4)})
+    yield (lambda **kw: gsd.gsd_node_argmax_stats(rows, **kw), {"pred": on_gpu(4), "row_max": on_gpu(4, **f4), "row_sumexp": on_gpu(4, **f4)})
+    yield (lambda **kw: gsd.gsd_softmax_stats(rows, **kw), {"row_max": on_gpu(4, **f4), "row_sumexp": on_gpu(4, **f4)})
+    outputs = {"pred": on_gpu(4), "accept_len": on_gpu(1), "accept_path": on_gpu(1, 6), "bonus_token": on_gpu(1)}
+    yield (lambda **kw: gsd.gsd_accept_longest_path(*graph_tensors(), on_gpu(4), on_gpu(1), 6, logits=rows, **kw), outputs)
+    yield (lambda **kw: gsd.gsd_accept_longest_path(*graph_tensors(), on_gpu(4), on_gpu(1), 6, **kw), outputs)
+    cache = on_gpu(2, 9, 1, 8, **f4)
+    yield (lambda **kw: gsd.gsd_commit_kv(cache, cache, on_gpu(2, dtype=torch.int64), on_gpu(2), on_gpu(2), on_gpu(2, 4), **kw),
+           {"new_prefix_lens": on_gpu(2)})
+    yield (lambda **kw: gsd.gsd_dag_attention(*attention_tensors(), 4, 8, 0.1, workspace=on_gpu(16), **kw),
+           {"out": on_gpu(4, 2, 64, **f4), "lse": on_gpu(4, 2, **f4)})
+
+
+def test_outputs_that_a_call_would_write_past_are_refused(monkeypatch):
+    """A kernel knows no end of the buffers it is given: one element less than a call writes is refused before the library is
+    reached, one more is as good as the exact size."""
+    calls = recording_library(monkeypatch)
+    for call, outputs in calls_with_outputs():
+        call(**outputs)
+        for name, t in outputs.items():
+            for wrong in ([t[:-1], t[:0]] if t.dim() == 1 else [t[:-1], t[:, :-1].contiguous()]):
+                del calls[:]
+                with pytest.raises(ValueError, match=name):
+                    call(**{**outputs, name: wrong})
+                assert not calls
+            call(**{**outputs, name: on_gpu(*(size + 1 for size in t.shape), dtype=t.dtype)})
+            assert calls
+
+
+def test_attention_outputs_of_another_kind_are_refused(monkeypatch):
+    """What the descriptor cannot say of `out`: its type, its last stride, and that it is memory of the GPU."""
+    calls = recording_library(monkeypatch)
+    f4 = dict(dtype=torch.float32)
+    for wrong in (on_gpu(4, 2, 64, dtype=torch.bfloat16), on_gpu(4, 2, 64, dtype=torch.float64), on_gpu(4, 2, 128, **f4)[:, :, ::2],
+                  on_gpu(4, 2, 32, **f4), on_gpu(8, 64, **f4)):
+        with pytest.raises(ValueError, match="out"):
+            gsd.gsd_dag_attention(*attention_tensors(), 4, 8, 0.1, workspace=on_gpu(16), out=wrong)
+    assert not calls
+    gsd.gsd_dag_attention(*attention_tensors(), 4, 8, 0.1, workspace=on_gpu(16), out=on_gpu(4, 2, 96, **f4)[:, :, :64])
+    assert calls == ["gsd_dag_attention"]

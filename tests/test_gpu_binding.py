@@ -184,6 +184,35 @@ def test_exceptions_are_the_same(args, monkeypatch):
         assert isinstance(x, tuple) and isinstance(x[0], type) and x == y, (k, x, y)
 
 
+def test_outputs_that_a_call_would_write_past_are_refused_either_way(args, monkeypatch):
+    """Refused on the host, with nothing launched; a larger buffer is as good as the exact one."""
+    a, t = args, args[torch.bfloat16]
+    i4 = lambda *shape: torch.full(shape, 7, dtype=torch.int32, device="cuda")
+    f4 = lambda *shape: torch.full(shape, 7.0, device="cuda")
+    n, q = a["n"], t["q"]
+    accept = {"pred": i4(n), "accept_len": i4(1), "accept_path": i4(1, n), "bonus_token": i4(1)}
+    cache = torch.stack([t["k"]] * 2)
+    calls = [(lambda **kw: gsd.gsd_node_argmax(t["logits"], **kw), {"pred": i4(n)}),
+             (lambda **kw: gsd.gsd_node_argmax_stats(t["logits"], **kw), {"pred": i4(n), "row_max": f4(n), "row_sumexp": f4(n)}),
+             (lambda **kw: gsd.gsd_softmax_stats(t["logits"], **kw), {"row_max": f4(n), "row_sumexp": f4(n)}),
+             (lambda **kw: gsd.gsd_accept_longest_path(*a["graph"], a["tokens"], a["root_pred"], n, logits=t["logits"], **kw), accept),
+             (lambda **kw: gsd.gsd_commit_kv(cache, cache.clone(), a["kv_offsets"], a["prefix"], i4(1) * 0, i4(1, n) * 0, **kw),
+              {"new_prefix_lens": i4(1)}),
+             (lambda **kw: gsd.gsd_dag_attention(*attention_args(a, torch.bfloat16), return_lse=True, **kw),
+              {"out": torch.zeros_like(q), "lse": f4(n, 4)})]
+    for call, outputs in calls:
+        for name, full in outputs.items():
+            for wrong in (full[:-1], full[:0]) + ((full[:, :-1].contiguous(),) if full.dim() > 1 else ()):
+                x, y = both(monkeypatch, lambda: call(**{**outputs, name: wrong}))
+                assert isinstance(x, tuple) and x[0] is ValueError and x == y, (name, x, y)
+            longer = torch.full((full.shape[0] + 1, *full.shape[1:]), 7, dtype=full.dtype, device="cuda")
+            same(monkeypatch, lambda: call(**{**outputs, name: longer}))
+            assert (longer[full.shape[0]:] == 7).all()
+    for wrong in (q.float(), torch.zeros(n, 4, 128, dtype=q.dtype, device="cuda")[:, :, ::2], torch.zeros(n, 4, 64, dtype=q.dtype)):
+        x, y = both(monkeypatch, lambda: gsd.gsd_dag_attention(*attention_args(a, torch.bfloat16), out=wrong))
+        assert isinstance(x, tuple) and x[0] is ValueError and x == y
+
+
 def test_other_tensors_go_the_long_way(args):
     """Subclasses, and calls under a torch mode that wants to see them."""
     from torch.utils._python_dispatch import TorchDispatchMode
