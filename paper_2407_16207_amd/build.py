@@ -23,22 +23,34 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
                "-Wno-unused-command-line-argument"]
 
 
-def build_binding(verbose: bool = False) -> str:
-    """csrc/binding.cpp against the headers of the torch that is installed; host code only."""
+def build_binding(verbose: bool = False) -> str | None:
+    """csrc/binding.cpp against the headers of the torch that is installed; host code only.  The library does not need it, nor
+    does the Python binding: where it cannot be built (no torch, no compiler, no headers) a line says so, none is left behind
+    from an earlier build, and None is returned."""
+    if os.path.exists(BINDING_PATH):
+        os.remove(BINDING_PATH)
+    try:
+        cmd = _binding_command()
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.check_call(cmd)
+    except (ImportError, OSError, subprocess.CalledProcessError) as e:
+        print(f"{os.path.basename(BINDING_PATH)} was not built ({e}): Python calls go without it, which takes them longer", flush=True)
+        return None
+    return BINDING_PATH
+
+
+def _binding_command() -> list[str]:
     import torch
     root = os.path.dirname(torch.__file__)
     headers = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
                sysconfig.get_paths()["include"]]
     lib = os.path.join(root, "lib")
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wno-sign-compare",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-           *[flag for path in headers for flag in ("-isystem", path)], "-I", os.path.join(ROOT, "include"),
-           os.path.join(CSRC, "binding.cpp"), "-o", BINDING_PATH, "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python",
-           f"-Wl,-rpath,{lib}"]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd)
-    return BINDING_PATH
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wno-sign-compare",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            *[flag for path in headers for flag in ("-isystem", path)], "-I", os.path.join(ROOT, "include"),
+            os.path.join(CSRC, "binding.cpp"), "-o", BINDING_PATH, "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python",
+            f"-Wl,-rpath,{lib}"]
 
 
 def build_library(verbose: bool = False, extra_flags: list[str] | None = None) -> str:
