@@ -11,8 +11,10 @@ mirror the C entry points of the same names.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 import struct
+import warnings
 
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG_DIR, "libgsd.so")
@@ -110,9 +112,26 @@ def _load_hip_runtime():
     raise RuntimeError("no HIP runtime (libamdhip64.so) found next to torch or under /opt/rocm")
 
 
+def _load_binding(lib):
+    """csrc/binding.cpp, bound to the library; None, with a warning, if it is not there or does not load.  Every call has its
+    way through this module and ctypes as well, which only takes the host longer (a verify step 39 us instead of 24)."""
+    try:
+        spec = importlib.util.spec_from_file_location(__name__ + "._binding", BINDING_PATH)
+        binding = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(binding)
+        binding.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in (
+            "gsd_build_mask", "gsd_dag_attention_workspace", "gsd_dag_attention", "gsd_node_argmax",
+            "gsd_node_argmax_stats", "gsd_accept_longest_path", "gsd_unmerge_to_tree", "gsd_gather_rows", "gsd_commit_kv",
+            "gsd_softmax_stats", "gsd_accept_stochastic", "gsd_build_token_graph")), _device, _raw_stream)
+    except (ImportError, OSError) as e:
+        warnings.warn(f"calls go without {BINDING_PATH}, which takes them longer: {e}", RuntimeWarning, stacklevel=3)
+        return None
+    return binding
+
+
 def load_library() -> ctypes.CDLL:
     """Load libgsd.so (built in-tree by paper_2407_16207_amd.build); raises if it is not there."""
-    global _lib
+    global _lib, _short
     if _lib is None:
         if torch is None:
             _import_torch()
@@ -141,14 +160,7 @@ def load_library() -> ctypes.CDLL:
         lib.gsd_accept_stochastic.argtypes = [ctypes.POINTER(StochasticDesc), vp]
         lib.gsd_build_token_graph.argtypes = [i32, i32, i32, ctypes.c_float, ctypes.c_float, vp, vp, vp, vp, vp, vp, vp,
                                               vp, i64, vp, vp, vp, vp]
-        if os.path.exists(BINDING_PATH):
-            from . import _binding
-            _binding.bind(*(ctypes.cast(getattr(lib, name), vp).value for name in (
-                "gsd_build_mask", "gsd_dag_attention_workspace", "gsd_dag_attention", "gsd_node_argmax",
-                "gsd_node_argmax_stats", "gsd_accept_longest_path", "gsd_unmerge_to_tree", "gsd_gather_rows", "gsd_commit_kv",
-                "gsd_softmax_stats", "gsd_accept_stochastic", "gsd_build_token_graph")), _device, _raw_stream)
-            global _short
-            _short = _binding
+        _short = _load_binding(lib)
         _lib = lib
     return _lib
 

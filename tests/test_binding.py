@@ -1,7 +1,10 @@
 """The Python binding on its own, without a GPU: what it hands to the library and what it refuses, with stand-ins for the
 library and for torch's allocator."""
 import contextlib
+import os
+import subprocess
 import types
+import warnings
 
 import pytest
 import torch
@@ -201,3 +204,44 @@ def test_attention_outputs_of_another_kind_are_refused(monkeypatch):
     assert not calls
     gsd.gsd_dag_attention(*attention_tensors(), 4, 8, 0.1, workspace=on_gpu(16), out=on_gpu(4, 2, 96, **f4)[:, :, :64])
     assert calls == ["gsd_dag_attention"]
+
+
+@pytest.fixture
+def reload(monkeypatch):
+    """Loads the library again with what stands at `path` for the binding's native part: (library, native part, warnings)."""
+    gsd.load_library()
+
+    def load(path):
+        monkeypatch.setattr(gsd, "_lib", None)
+        monkeypatch.setattr(gsd, "_short", None)
+        monkeypatch.setattr(gsd, "BINDING_PATH", str(path))
+        with warnings.catch_warnings(record=True) as said:
+            warnings.simplefilter("always")
+            lib = gsd.load_library()
+        return lib, gsd._short, [str(w.message) for w in said if w.category is RuntimeWarning]
+    return load
+
+
+@pytest.mark.parametrize("kind", ["none", "text", "undefined symbol"])
+def test_a_native_part_that_does_not_load_is_done_without(reload, tmp_path, kind):
+    """As after an upgrade of torch: the calls' way through Python and ctypes is whole, and one warning says that they take it."""
+    path = tmp_path / "_binding.so"
+    if kind == "text":
+        path.write_text("no library")
+    elif kind == "undefined symbol":
+        (tmp_path / "b.c").write_text("extern int gone_from_torch(void);\nvoid *PyInit__binding(void) { gone_from_torch(); return 0; }\n")
+        subprocess.check_call(["gcc", "-shared", "-fPIC", "-o", str(path), str(tmp_path / "b.c")])
+    lib, short, said = reload(path)
+    assert lib.gsd_version().startswith(b"gsd") and short is None
+    assert len(said) == 1 and str(path) in said[0]
+    desc = gsd.make_attn_desc(*attention_tensors(), 4, 8, 0.1)
+    assert gsd.gsd_dag_attention_workspace(desc) >= 0
+
+
+def test_the_native_part_that_has_been_built_loads(reload):
+    from paper_2407_16207_amd import build
+    if not os.path.exists(gsd.BINDING_PATH):
+        assert build.build_binding() == gsd.BINDING_PATH
+    lib, short, said = reload(gsd.BINDING_PATH)
+    assert short is not None and not said
+    assert short.node_argmax(torch.zeros(4, 8), None, None) is None        # a host tensor: not for the native part
