@@ -11,6 +11,7 @@ mirror the C entry points of the same names.
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
 import importlib.util
 import os
 import struct
@@ -18,7 +19,8 @@ import warnings
 
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG_DIR, "libgsd.so")
-BINDING_PATH = os.path.join(_PKG_DIR, "_binding.so")      # the way of plain tensors to the library without Python in between
+# the way of plain tensors to the library without Python in between, for the Python that its name says
+BINDING_PATH = os.path.join(_PKG_DIR, "_binding" + importlib.machinery.EXTENSION_SUFFIXES[0])
 
 GSD_OK = 0
 GSD_ERR_INVALID_ARG, GSD_ERR_UNSUPPORTED, GSD_ERR_WORKSPACE, GSD_ERR_HIP = 1, 3, 4, 5
@@ -112,13 +114,27 @@ def _load_hip_runtime():
     raise RuntimeError("no HIP runtime (libamdhip64.so) found next to torch or under /opt/rocm")
 
 
+def built_for(module, header: str) -> str:
+    """What csrc/binding.cpp depends on and cannot notice by itself: how the torch in `module` lays out a tensor, and the
+    declarations in gsd.h (`header`: their identity)."""
+    return f"torch {module.__version__} {module.version.git_version}, gsd.h {header}"
+
+
 def _load_binding(lib):
-    """csrc/binding.cpp, bound to the library; None, with a warning, if it is not there or does not load.  Every call has its
-    way through this module and ctypes as well, which only takes the host longer (a verify step 39 us instead of 24)."""
+    """csrc/binding.cpp, bound to the library; None, with a warning, if it is not there, does not load or was built for another
+    torch or another library.  Every call has its way through this module and ctypes as well, which only takes the host longer
+    (a verify step 39 us instead of 24)."""
     try:
         spec = importlib.util.spec_from_file_location(__name__ + "._binding", BINDING_PATH)
         binding = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(binding)
+        header = getattr(lib, "gsd_header_id", None)
+        if header is not None:
+            header.restype = ctypes.c_char_p
+        wanted = built_for(torch, header().decode() if header is not None else "of another time")
+        found = getattr(binding, "built_for", "something unknown")
+        if found != wanted:
+            raise ImportError(f"built for {found}; here is {wanted}")
         binding.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in (
             "gsd_build_mask", "gsd_dag_attention_workspace", "gsd_dag_attention", "gsd_node_argmax",
             "gsd_node_argmax_stats", "gsd_accept_longest_path", "gsd_unmerge_to_tree", "gsd_gather_rows", "gsd_commit_kv",

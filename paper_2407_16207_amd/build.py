@@ -1,6 +1,8 @@
 """Builds libgsd.so (the gfx950 HIP library behind include/gsd.h) in-tree with hipcc, and the native part of its Python binding."""
 from __future__ import annotations
 
+import hashlib
+import importlib.machinery
 import os
 import subprocess
 import sysconfig
@@ -9,7 +11,7 @@ PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libgsd.so")
-BINDING_PATH = os.path.join(PKG_DIR, "_binding.so")
+BINDING_PATH = os.path.join(PKG_DIR, "_binding" + importlib.machinery.EXTENSION_SUFFIXES[0])
 BENCH_LIB_PATH = os.path.join(PKG_DIR, "libgsd_bench.so")     # measurement aid of bench.py only
 
 SOURCES = ["gsd_api.hip", "mask_build.hip", "accept_path.hip", "node_argmax.hip", "dag_attention_f32.hip",
@@ -21,6 +23,12 @@ SOURCES = ["gsd_api.hip", "mask_build.hip", "accept_path.hip", "node_argmax.hip"
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-no-hip-rt",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall",
                "-Wno-unused-command-line-argument"]
+
+
+def header_id() -> str:
+    """Identity of gsd.h, compiled into the library and into the binding's native part: whether they go together."""
+    with open(os.path.join(ROOT, "include", "gsd.h"), "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()[:16]
 
 
 def build_binding(verbose: bool = False) -> str | None:
@@ -42,12 +50,13 @@ def build_binding(verbose: bool = False) -> str | None:
 
 def _binding_command() -> list[str]:
     import torch
+    from . import built_for
     root = os.path.dirname(torch.__file__)
     headers = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
                sysconfig.get_paths()["include"]]
     lib = os.path.join(root, "lib")
     return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wno-sign-compare",
-            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DGSD_BUILT_FOR="{built_for(torch, header_id())}"',
             *[flag for path in headers for flag in ("-isystem", path)], "-I", os.path.join(ROOT, "include"),
             os.path.join(CSRC, "binding.cpp"), "-o", BINDING_PATH, "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python",
             f"-Wl,-rpath,{lib}"]
@@ -55,7 +64,7 @@ def _binding_command() -> list[str]:
 
 def build_library(verbose: bool = False, extra_flags: list[str] | None = None) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc, *HIPCC_FLAGS, *(extra_flags or []), "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+    cmd = [hipcc, *HIPCC_FLAGS, *(extra_flags or []), f'-DGSD_HEADER_ID="{header_id()}"', "-I", os.path.join(ROOT, "include"), "-I", CSRC,
            *[os.path.join(CSRC, s) for s in SOURCES], "-o", LIB_PATH]
     if verbose:
         print(" ".join(cmd), flush=True)

@@ -581,4 +581,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__binding() { return PyModule_Create(&module); }
+// GSD_BUILT_FOR: the torch and the gsd.h this was compiled with, which is compared before anything here is called
+PyMODINIT_FUNC PyInit__binding() {
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", GSD_BUILT_FOR) < 0) Py_CLEAR(m);
+    return m;
+}

@@ -66,6 +66,12 @@ const char *gsd_last_error(void) { return g_last_error; }
 
 const char *gsd_version(void) { return "gsd-gfx950 0.1"; }
 
+// Identity of the gsd.h this was built with, for the native part of the Python binding (not part of the interface).
+#ifndef GSD_HEADER_ID
+#define GSD_HEADER_ID "unknown"
+#endif
+const char *gsd_header_id(void) { return GSD_HEADER_ID; }
+
 int gsd_build_mask(int32_t batch, int32_t max_nodes, int32_t words_per_row, const int32_t *node_offsets,
                    const int32_t *parent_offsets, const int32_t *parent_idx, uint64_t *mask,
                    int32_t *dag_error_flag, void *hip_stream) {

@@ -1,6 +1,7 @@
 """The Python binding on its own, without a GPU: what it hands to the library and what it refuses, with stand-ins for the
 library and for torch's allocator."""
 import contextlib
+import ctypes
 import os
 import subprocess
 import types
@@ -245,3 +246,25 @@ def test_the_native_part_that_has_been_built_loads(reload):
     lib, short, said = reload(gsd.BINDING_PATH)
     assert short is not None and not said
     assert short.node_argmax(torch.zeros(4, 8), None, None) is None        # a host tensor: not for the native part
+
+
+@pytest.mark.parametrize("other", ["torch", "library"])
+def test_a_native_part_built_for_something_else_is_done_without(reload, monkeypatch, other):
+    """It loads, but would misread tensors (another torch) or descriptors (another gsd.h)."""
+    path = gsd.BINDING_PATH
+    if other == "torch":
+        monkeypatch.setattr(torch.version, "git_version", "0" * 40)
+    elif other == "library":
+        monkeypatch.setattr(gsd, "built_for", lambda module, header, right=gsd.built_for: right(module, "0" * len(header)))
+    _, short, said = reload(path)
+    assert short is None and len(said) == 1 and "built for" in said[0]
+
+
+def test_names_and_identities_of_the_build():
+    """The native part's file is named for the Python it is for; the library says which gsd.h it was built with."""
+    import importlib.machinery
+    from paper_2407_16207_amd import build
+    assert gsd.BINDING_PATH == build.BINDING_PATH and gsd.BINDING_PATH.endswith(importlib.machinery.EXTENSION_SUFFIXES[0])
+    identity = gsd.load_library().gsd_header_id
+    identity.restype = ctypes.c_char_p
+    assert identity().decode() == build.header_id()
