@@ -386,7 +386,8 @@ __device__ __forceinline__ void resample_phase(const gsd_stochastic_desc &d, int
     constexpr int kStride = SEG_BYTES / 4 + 1;                    // words from one slice's segment to the next
     constexpr int kWaves = kResampleWaves;
     __shared__ uint32_t seg_p[kResampleThreads * kStride], seg_q[kResampleThreads * kStride];
-    __shared__ float part[2][kResampleThreads];
+    constexpr int kBefore = kResampleThreads - 64;                // zeros in front: what the first waves find before themselves
+    __shared__ float part[kResampleThreads], part_of_waves[kBefore + kResampleThreads];
     __shared__ float red_m[kWaves], red_s[kWaves], stat[2];
     __shared__ int owner_s, pick_s;
 
@@ -398,6 +399,7 @@ __device__ __forceinline__ void resample_phase(const gsd_stochastic_desc &d, int
         owner_s = 0x7fffffff;
         pick_s = -1;
     }
+    if (t < kBefore) part_of_waves[t] = 0.f;
     const int64_t row_off = (end < 0 ? int64_t(b) : base + end) * d.row_stride;
     const char *p_row = reinterpret_cast<const char *>(end < 0 ? d.root_logits : d.logits) + row_off * ELT;
     const char *q_row = reinterpret_cast<const char *>(end < 0 ? d.root_draft_logits : d.draft_logits) + row_off * ELT;
@@ -513,14 +515,16 @@ __device__ __forceinline__ void resample_phase(const gsd_stochastic_desc &d, int
     // Inclusive scan of the slices' weights in one fixed order, that of ten doubling steps: value t takes in value t - 1, then
     // t - 2, t - 4, ... t - 512, each as the step before left it.  The steps up to 32 reach into the wave before at most, so a
     // wave takes them on its own, with that wave's values in a second register; the others stay in the lane, sixteen
-    // values from LDS.  Three barriers instead of eleven, 2.9 instead of 5.4 us.
+    // values from LDS.  Three barriers instead of eleven, 2.9 instead of 5.4 us.  A wave with fewer than sixteen before it finds
+    // zeros there; deciding that per value keeps sixteen lane masks, which spills scalar registers where two work-groups share a
+    // CU (512 sequences of 4 nodes, 1000 tokens, whole call 19.8 us instead of 19.4; 2048 of 2 nodes 49.5 instead of 47.2).
     float before = 0.f, upto = 0.f, total = 0.f;
     const int lane = t & 63, wave = t >> 6;
     auto scan = [&](bool residual) {
         float a = slice_sum(residual);
-        part[0][t] = a;
+        part[t] = a;
         __syncthreads();
-        float prev = wave > 0 ? part[0][t - 64] : 0.f;           // (lanes below a step's reach are not needed after it)
+        float prev = wave > 0 ? part[t - 64] : 0.f;              // (lanes below a step's reach are not needed after it)
 #pragma unroll
         for (int dd = 1; dd < 64; dd <<= 1) {
             const int src = (lane - dd) & 63;
@@ -528,20 +532,20 @@ __device__ __forceinline__ void resample_phase(const gsd_stochastic_desc &d, int
             if (t >= dd) a += lane >= dd ? from_a : from_prev;
             prev += lane >= dd ? from_prev : 0.f;
         }
-        part[1][t] = a;
+        part_of_waves[kBefore + t] = a;
         __syncthreads();
         float x[kWaves];
 #pragma unroll
-        for (int j = 0; j < kWaves; ++j) x[j] = j <= wave ? part[1][t - (j <= wave ? 64 * j : 0)] : 0.f;
+        for (int j = 0; j < kWaves; ++j) x[j] = part_of_waves[kBefore + t - 64 * j];
 #pragma unroll
         for (int step = 1; step < kWaves; step <<= 1)            // x[j] stands for wave - j
 #pragma unroll
             for (int j = 0; j + step < kWaves; j += 2 * step) x[j] += x[j + step];
         upto = x[0];
-        part[0][t] = upto;
+        part[t] = upto;
         __syncthreads();
-        before = t > 0 ? part[0][t - 1] : 0.f;
-        total = part[0][kResampleThreads - 1];
+        before = t > 0 ? part[t - 1] : 0.f;
+        total = part[kResampleThreads - 1];
     };
     bool residual = use_residual;
     scan(residual);
