@@ -16,6 +16,11 @@
 // following the layers of the graph instead, one after the other with a flag per node, took 0.2 us for each of them.
 // Launches in a replayed graph, against that (us): 64 nodes in 8 layers 3.9 -> 2.9, 8 x 256 in 32 layers 9.3 -> 4.9, 32 x 512 in
 // 64 layers 19.3 -> 7.5; random graphs 77 nodes 3.5-5.1 -> 3.9, 8 x 512 15.6-19.9 -> 12.9; a chain of 512 101 -> 7.1.
+// Shallow graphs have little for it to save.  Blocks without edges within (children of the root, layers of 64 and more) skip both
+// kinds of steps, which costs the others less than 1 %: a star of 77 nodes 3.5 -> 3.0 (2.9 by layers), 2 layers of 64 4.4 -> 2.9
+// (3.0), 2 of 256 9.9 -> 5.6 (15.0).  Behind following the layers are still 4 layers of 32, 3.9 (3.4), 5 of 25, 4.1 (3.6), and random
+// trees of 128 to 256 nodes, by up to a tenth; leaving out eight nodes at a time by whether they have children in the block mends a third of
+// that at most and takes every deep graph 3-6 % more.
 #include "gsd_internal.h"
 
 namespace gsd {
@@ -34,7 +39,7 @@ __global__ __launch_bounds__(64 * W) void build_mask_kernel(
     __shared__ uint64_t outer[kNodes];                       // a node's first four parents in earlier blocks, 16 bits each
     __shared__ uint64_t column[W][kNodes + 1];               // word w of the rows, by wavefront w; the last one stays 0
     __shared__ int32_t offset[kNodes + 1];
-    __shared__ int32_t wave_more[W];
+    __shared__ int32_t wave_says[W];                         // bit 0: some node has more than four parents; 1: edges within the block
     __shared__ int32_t edge_cache[kEdgeCacheInts];
 
     const int b = blockIdx.x;
@@ -93,9 +98,10 @@ __global__ __launch_bounds__(64 * W) void build_mask_kernel(
     }
 
     // The diagonal block.  Step k hands the row of lane k to the lanes that have bit k; rows of the lower half have no bits in
-    // the upper.
+    // the upper.  (One block alone: nearly all such graphs have edges, and a branch that waits for them costs 0.1 us.)
     uint32_t lo = uint32_t(own), hi = uint32_t(own >> 32);
-    const int here = n - 64 * w;                             // rows of this block
+    const bool edges_within = W == 1 || __any((own & ~(uint64_t(1) << lane)) != 0);
+    const int here = edges_within ? n - 64 * w : 0;          // rows of this block
 #pragma unroll
     for (int k0 = 0; k0 < 32; k0 += 8) {
         if (k0 >= here) break;                               // uniform
@@ -122,7 +128,7 @@ __global__ __launch_bounds__(64 * W) void build_mask_kernel(
     const bool some_more = __any(more);                      // (in all lanes, or lane 0 speaks for itself only)
     if (lane == 0) {
         column[w][kNodes] = 0;
-        wave_more[w] = some_more;
+        wave_says[w] = (some_more ? 1 : 0) | (edges_within ? 2 : 0);
     }
     uint64_t *const out = mask + base * words_per_row + w;
     if (i < n) out[int64_t(i) * words_per_row] = own;
@@ -133,9 +139,12 @@ __global__ __launch_bounds__(64 * W) void build_mask_kernel(
     const int blocks = (n + 63) / 64;
     if (blocks == 1) return;                                 // uniform for the work-group
     __syncthreads();
-    bool any_more = false;
+    int says = 0;
 #pragma unroll
-    for (int x = 0; x < W; ++x) any_more |= wave_more[x] != 0;
+    for (int x = 0; x < W; ++x) says |= wave_says[x];
+    says = __builtin_amdgcn_readfirstlane(says);
+    const bool any_more = says & 1;
+    const uint64_t spread = says & 2 ? ~uint64_t(0) : 0;
     int first = 0;
     bool cached = false;
     if (any_more) {                                          // uniform
@@ -165,9 +174,9 @@ __global__ __launch_bounds__(64 * W) void build_mask_kernel(
                 if (p >= 64 * w && p < 64 * c) ext |= mine[p];
             }
         }
-        uint32_t row_lo = 0, row_hi = 0;
         const uint32_t ext_lo = uint32_t(ext), ext_hi = uint32_t(ext >> 32);
-        const uint64_t from = __ballot(ext != 0);
+        uint32_t row_lo = ext_lo, row_hi = ext_hi;
+        const uint64_t from = __ballot(ext != 0) & spread;
         const uint32_t within_lo = uint32_t(within), within_hi = uint32_t(within >> 32);
         // Eight nodes at a time: a layer of a graph is a run of nodes, and with the lanes as constants a node takes five vector
         // instructions and no scalar ones (random graphs, where nearly all have such parents: 2.0 us for 64 nodes one by one).

@@ -144,6 +144,28 @@ def test_mask_blocks_of_64(gpu, ref, n):
         assert np.array_equal(got, ref.build_mask(w.node_offsets, w.parent_offsets, w.parent_idx, words_per_row=words)[0]), rep
 
 
+@pytest.mark.parametrize("n", [65, 77, 128, 129, 256, 300, 511, 512])
+def test_mask_blocks_without_edges_within(gpu, ref, n):
+    """Blocks of 64 nodes whose parents all lie in earlier blocks, or are the root, take no steps of their own: no such edge in any
+    block, in one block only, one edge in the last lane; with nodes of more than four parents and without."""
+    rng = np.random.default_rng(40 + n)
+    for rep in range(8):
+        deep = int(rng.integers(0, (n + 63) // 64)) if rep % 4 else -1            # the block that has edges within, if any
+        offsets, parents = [0], []
+        for i in range(n):
+            block = i // 64
+            few = int(rng.integers(1, 9 if rep >= 4 else 5))
+            pick = rng.choice(64 * block, min(few, 64 * block), replace=False).tolist() if block and rep != 4 else []
+            if block == deep and i % 64 and (rep % 4 != 3 or i % 64 == 63 or i == n - 1):
+                pick.append(int(rng.integers(64 * block, i)))
+            parents += sorted(set(pick)) or [-1]
+            offsets.append(len(parents))
+        w = custom_workload(rng, [n], [0], 1, 1, 64, "f32")
+        w.parent_offsets, w.parent_idx = np.array(offsets, dtype=np.int32), np.array(parents, dtype=np.int32)
+        got = gpu.mask_to_numpy(gpu.DeviceWorkload(w).build_mask())
+        assert np.array_equal(got, ref.build_mask(w.node_offsets, w.parent_offsets, w.parent_idx)[0]), rep
+
+
 def test_mask_bad_parent_sets_flag(gpu, ref):
     rng = np.random.default_rng(3)
     w = custom_workload(rng, [6], [0], 1, 1, 64, "f32")
