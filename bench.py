@@ -422,6 +422,13 @@ def bench_config5_dag_vs_tree(gsd, dev, reps=10):
     return res
 
 
+def default_streams(config: int) -> int:
+    """The faster schedule.  The fork and the join cost more than the overlap returns up to config 4 (ms per step, two streams
+    and one in the same run, seven runs: 0.286-0.320 and 0.278-0.297, 2-10 % between them), less on config 5 (2.423 and 2.433,
+    2.508 and 2.526)."""
+    return 2 if config >= 5 else 1
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -434,8 +441,7 @@ def main():
     ap.add_argument("--streams", type=int, default=0, choices=[0, 1, 2],
                     help="2: the argmax + acceptance call runs on a second stream of the same priority next to mask + "
                          "attention, forked at the start of every step and joined at its end; 1: all on one stream; "
-                         "0 (default): 2 for configs 4 and 5, 1 for the small configs, whose steps are shorter than "
-                         "what the fork and the join cost")
+                         "0 (default): whichever is the faster, 2 for config 5 and 1 for the others")
     ap.add_argument("--no-config5", action="store_true", help="skip the config-5 graph-against-tree attention leg")
     ap.add_argument("--cache-layers", type=int, default=80, help="depth of the KV cache the commit step is timed on")
     ap.add_argument("--splits", type=int, default=0, help="force the attention KV split count (0 = library's choice)")
@@ -447,7 +453,7 @@ def main():
     if args.gpus != 1:
         sys.exit("bench.py: this build runs on ONE GPU only (no collectives, no sharding); use --gpus 1")
     if args.streams == 0:
-        args.streams = 2 if args.config >= 4 else 1
+        args.streams = default_streams(args.config)
 
     import numpy as np
     import torch
@@ -564,8 +570,8 @@ def main():
     # The timed region: W warm-up steps, then exactly K steps with nothing but the steps' own launches (and, with two
     # streams, the fork and join of each step) between two synchronisations.  Events between the launches of a step
     # cost 13 us per step here (0.293 ms without, 0.306 ms with four), so the per-stage times and the attention kernel's
-    # launch duration come from a further, single-stream pass of K steps that carries them.  With --streams 2 both schedules
-    # are timed and the headline is the two-stream one; --streams 1 runs the one-stream schedule only.
+    # launch duration come from a further, single-stream pass of K steps that carries them.  With two streams both schedules
+    # are timed and the headline is the two-stream one; with one the two-stream schedule does not run.
     # Order of the passes: a chip that has idled (here: while the inputs were generated and uploaded) raises its clocks
     # over roughly its first hundred steps of work (0.345 ms for the first ten steps after half a second of idling,
     # 0.305 for steps 21-30, 0.291 from about step 110 on), so the passes whose figures are secondary run first and
