@@ -92,6 +92,14 @@ int gsd_dag_attention_splits(const gsd_attn_desc *desc) {
     return desc->dtype == GSD_BF16 ? gsd::attention_bf16_plan(*desc).splits : gsd::attention_f32_splits(*desc);
 }
 
+// Which kernel a bf16 descriptor gets with all the workspace it asks for, for tests that are about one of them (not part of the
+// interface): 1 or 2 = the keys kernel with that many row groups; 4, 8 or 64 = the other one, as gsd_attn_desc.wg_waves names its shapes.
+int gsd_dag_attention_kernel(const gsd_attn_desc *desc) {
+    if (check_attn_desc(desc) != GSD_OK || desc->dtype != GSD_BF16) return -1;
+    const gsd::AttnPlan plan = gsd::attention_bf16_plan(*desc);
+    return plan.row_groups ? plan.row_groups : plan.blocks == 2 ? 64 : plan.waves;
+}
+
 size_t gsd_dag_attention_workspace(const gsd_attn_desc *desc) {
     if (check_attn_desc(desc) != GSD_OK) return (size_t)-1;
     return gsd::attention_workspace(*desc, gsd_dag_attention_splits(desc));

@@ -209,6 +209,19 @@ def check_attention(gpu, ref, w, d=None, rows=None, **kw):
     return out
 
 
+def planned_kernel(w, **kw):
+    """Which kernel the library takes for a bf16 call: 1 or 2 = the one whose wavefronts deal out the keys, with that many row
+    groups; 4, 8 or 64 = the other one.  Tests that are about one kernel say which, so that a new fit of the plan cannot empty them."""
+    import ctypes
+
+    import paper_2407_16207_amd as gsd
+    d = gsd.AttnDesc()
+    d.batch, d.total_nodes, d.max_nodes, d.max_prefix = w.cfg.batch, w.total_nodes, w.max_nodes, int(w.prefix_lens.max())
+    d.num_q_heads, d.num_kv_heads, d.head_dim, d.dtype = w.cfg.num_q_heads, w.cfg.num_kv_heads, w.cfg.head_dim, gsd.GSD_BF16
+    d.words_per_row, d.num_splits, d.softmax_scale = (w.max_nodes + 63) // 64, kw.get("num_splits", 0), w.softmax_scale
+    return gsd.load_library().gsd_dag_attention_kernel(ctypes.byref(d))
+
+
 def test_attention_config1_fp32(gpu, ref):
     check_attention(gpu, ref, workload(1))
 
@@ -332,31 +345,56 @@ def test_attention_bf16_few_rows(gpu, ref, hq, hkv, D, splits):
     """Shapes the library gives to the kernel whose wavefronts deal out the keys: rows and keys one below, at and above its
     32-row groups, 32-key tiles and 128-key steps, more splits than steps, an empty prefix."""
     rng = np.random.default_rng(700 + hq + D + splits)
-    check_attention(gpu, ref, custom_workload(rng, [1, 5, 10, 11, 21, 32, 33], [0, 1, 31, 117, 107, 96, 300], hq, hkv, D, "bf16"),
-                    num_splits=splits)
-
-
-@pytest.mark.parametrize("hq,hkv,D", [(1, 1, 128), (3, 1, 128), (5, 1, 64), (8, 2, 128)])
-@pytest.mark.parametrize("splits", [0, 2])
-def test_attention_bf16_few_rows_prefixes_of_every_length(gpu, ref, hq, hkv, D, splits):
-    """The prefix ends at every position of a 128-key step, and the graph at the edges of mask words: the words of a tile that
-    reaches into the draft nodes are shifted together from two, ones before the first and nothing behind the last."""
-    rng = np.random.default_rng(10 * hq + D + splits)
-    prefixes = list(range(130)) + [0, 31, 32, 127, 128]
-    sizes = [int(rng.choice([1, 2, 31, 32, 33, 63, 64, 65])) for _ in range(130)] + [512, 511, 481, 480, 449]
-    w = custom_workload(rng, sizes, prefixes, hq, hkv, D, "bf16")
+    w = custom_workload(rng, [1, 5, 10, 11, 21, 32, 33], [0, 1, 31, 117, 107, 96, 300], hq, hkv, D, "bf16")
+    assert planned_kernel(w, num_splits=splits) == (2 if (hq, splits) == (16, 3) else 1)
     check_attention(gpu, ref, w, num_splits=splits)
 
 
-@pytest.mark.parametrize("hq,hkv,D", [(8, 8, 128), (4, 2, 128), (16, 4, 128), (3, 3, 64), (8, 2, 64)])
-@pytest.mark.parametrize("sizes,prefixes", [([64, 40, 33], [1500, 900, 2100]), ([63, 64, 65, 1], [2500, 1900, 100, 0]),
-                                            ([20, 31, 32], [4000, 3777, 130])])
-@pytest.mark.parametrize("splits", [0, 1, 3])
-def test_attention_bf16_few_rows_long_contexts(gpu, ref, hq, hkv, D, sizes, prefixes, splits):
-    """The same kernel with both of its row-group counts at head_dim 128 (more than 32 rows to a KV head get two) over 8 to 33
-    steps: its two buffers come round many times, with rows one below, at and above 32 and 64."""
+@pytest.mark.parametrize("hq,hkv,D,splits,small,large", [
+    (1, 1, 128, 0, 1, 1), (1, 1, 128, 2, 1, 1), (1, 1, 128, 3, 1, 2), (3, 1, 128, 0, 1, 2), (3, 1, 128, 2, 1, None), (3, 1, 128, 3, 2, None),
+    (8, 2, 128, 0, 1, 2), (8, 2, 128, 2, 2, None), (4, 2, 128, 2, 1, 2), (5, 1, 64, 0, 1, None), (5, 1, 64, 2, 1, None),
+    (3, 1, 64, 0, 1, 1), (2, 1, 64, 2, 1, 1)])
+def test_attention_bf16_few_rows_prefixes_of_every_length(gpu, ref, hq, hkv, D, splits, small, large):
+    """The prefix ends at every position of a 128-key step, and the graph at the edges of mask words, the last ones among them:
+    the words of a tile that reaches into the draft nodes are shifted together from two, ones before the first and nothing behind
+    the last.  Few sequences to a call, so that all calls take the kernel that deals out the keys, with `small` row groups for
+    graphs of up to 65 nodes and `large` for 449 to 512 (None: those are the other kernel's)."""
+    rng = np.random.default_rng(10 * hq + D + splits)
+    for part in range(13):                           # prefixes part, part + 13, part + 26 ...
+        sizes = [65] + [int(rng.choice([1, 2, 31, 32, 33, 63, 64, 65])) for _ in range(9)]
+        w = custom_workload(rng, [sizes[(i + part) % 10] for i in range(10)], list(range(part, 130, 13)), hq, hkv, D, "bf16")
+        assert planned_kernel(w, num_splits=splits) == small
+        check_attention(gpu, ref, w, num_splits=splits)
+    for sizes, prefixes in (([512, 511], [0, 31]), ([481, 480, 449], [32, 127, 128])):
+        if large is not None:
+            w = custom_workload(rng, sizes, prefixes, hq, hkv, D, "bf16")
+            assert planned_kernel(w, num_splits=splits) == large
+            check_attention(gpu, ref, w, num_splits=splits)
+
+
+LONG_CONTEXTS = [          # sizes, prefixes; per (query heads, KV heads, head_dim) the kernel with 0 (chosen), 1 and 3 splits
+    ([64, 40, 33], [1500, 900, 2100], {(8, 8, 128): (1, 1, 1), (4, 2, 128): (1, 1, 1), (16, 4, 128): (2, 1, 2), (3, 3, 64): (1, 1, 1),
+                                       (8, 2, 64): (1, 1, 1)}),
+    ([63, 64, 65, 1], [2500, 1900, 100, 0], {(8, 8, 128): (4, 1, 2), (4, 2, 128): (1, 1, 1), (16, 4, 128): (2, 1, 2),
+                                             (3, 3, 64): (1, 1, 1), (8, 2, 64): (1, 1, 1)}),
+    ([20, 31, 32], [4000, 3777, 130], {(8, 8, 128): (1, 1, 1), (4, 2, 128): (1, 1, 1), (16, 4, 128): (1, 1, 1), (3, 3, 64): (1, 1, 1),
+                                       (8, 2, 64): (1, 1, 1)}),
+    ([200, 199, 161], [1000, 871, 0], {(16, 4, 128): (2, 2, None)}), ([150, 97], [2100, 1000], {(16, 2, 128): (None, 2, None)}),
+    ([65, 64, 63, 33, 8], [1000, 999, 870, 31, 0], {(16, 2, 128): (2, 2, None)}),
+    ([200, 3], [4000, 4001], {(16, 2, 128): (None, 2, None)})]
+
+
+@pytest.mark.parametrize("sizes,prefixes,heads,splits,kernel", [
+    (sizes, prefixes, heads, splits, kernel) for sizes, prefixes, by_heads in LONG_CONTEXTS for heads, kernels in by_heads.items()
+    for splits, kernel in zip((0, 1, 3), kernels) if kernel is not None])
+def test_attention_bf16_few_rows_long_contexts(gpu, ref, sizes, prefixes, heads, splits, kernel):
+    """The same kernel over up to 33 steps: its two buffers come round many times, with rows one below, at and above 32 and 64; at
+    head_dim 128 with one row group and with two, unsplit and split."""
+    hq, hkv, D = heads
     rng = np.random.default_rng(750 + hq + D + len(sizes))
-    check_attention(gpu, ref, custom_workload(rng, sizes, prefixes, hq, hkv, D, "bf16"), num_splits=splits)
+    w = custom_workload(rng, sizes, prefixes, hq, hkv, D, "bf16")
+    assert planned_kernel(w, num_splits=splits) == kernel
+    check_attention(gpu, ref, w, num_splits=splits)
 
 
 def test_attention_bf16_mha_and_odd_group(gpu, ref):
