@@ -242,3 +242,65 @@ def test_an_allocation_that_fails(args, monkeypatch):
     got = both(monkeypatch, lambda: gsd.gsd_build_mask(nodes, offsets, parents, 6, words_per_row=2**31 - 1))
     assert [x[0] for x in got] == [torch.OutOfMemoryError] * 2
     same(monkeypatch, lambda: gsd.gsd_build_mask(*args["graph"], args["n"]))
+
+
+def test_steps_from_several_threads(args):
+    """Four threads, each with its own stream and its own outputs from the allocator, which the calls ask without the interpreter's
+    lock: the results of the same calls one after the other."""
+    import threading
+    a, t = args, args[torch.bfloat16]
+
+    def step(scale):
+        mask = gsd.gsd_build_mask(*a["graph"], a["n"])
+        q, k, v, *rest = attention_args(a, torch.bfloat16)
+        out, lse = gsd.gsd_dag_attention((q.float() * scale).to(q.dtype), k, v, *rest, num_splits=2, return_lse=True)
+        accepted = gsd.gsd_accept_longest_path(*a["graph"], a["tokens"], a["root_pred"], a["n"], logits=t["logits"] * scale)
+        return [mask, out, lse, *accepted, *gsd.gsd_node_argmax_stats(t["logits"] * scale), *gsd.gsd_softmax_stats(t["logits"] * scale)]
+    scales = [0.5, 1.0, -1.0, 2.0]
+    want = [step(scale) for scale in scales]
+    torch.cuda.synchronize()
+    got, failed = [[] for _ in scales], []
+
+    def run(i):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(25):
+                    got[i].append(step(scales[i]))
+                torch.cuda.current_stream().synchronize()
+        except Exception as e:        # noqa: BLE001 - reported below
+            failed.append(e)
+    threads = [threading.Thread(target=run, args=(i,)) for i in range(4)]
+    for thread in threads:
+        thread.start()
+    for thread in threads:
+        thread.join()
+    assert not failed, failed
+    for i in range(4):
+        assert len(got[i]) == 25
+        assert all(torch.equal(x, y) for results in got[i] for x, y in zip(results, want[i]))
+
+
+@pytest.mark.parametrize("transform", ["vmap", "grad", "jvp"])
+def test_calls_under_a_function_transform(args, monkeypatch, transform):
+    """Inside a torch.func transform, on tensors that it has nothing to do with and on one that it has wrapped: what Python does."""
+    t, seen = args[torch.float32], []
+
+    def body(x):
+        seen.append(both(monkeypatch, lambda: gsd.gsd_node_argmax(t["logits"])))
+        seen.append(both(monkeypatch, lambda: gsd.gsd_softmax_stats(x.expand(4, 3) if x.dim() == 1 else x)))
+        return x.sum()
+    x = torch.ones(4, 3, device="cuda")
+    if transform == "vmap":
+        torch.func.vmap(body)(x)
+    elif transform == "grad":
+        torch.func.grad(body)(x)
+    else:
+        torch.func.jvp(body, (x,), (x,))
+    assert len(seen) == 2
+    for a, b in seen:
+        raised = isinstance(a, tuple) and isinstance(a[0], type)
+        assert raised == (isinstance(b, tuple) and isinstance(b[0], type)), (a, b)
+        if raised:
+            assert a == b
+        else:
+            assert all(torch.equal(p, q) for p, q in zip(flat(a), flat(b)))
