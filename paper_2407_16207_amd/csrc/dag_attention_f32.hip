@@ -356,8 +356,10 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void dag_attention_f32_kernel(co
 // Splits of the keys that a small timing model likes best (microseconds, 256 CUs): 4.5 outside the loop and 1.45 (head_dim
 // 64: 0.75) per turn of the four wavefronts, in rounds of one work-group per CU, and for splitting the merge kernel: 2.5,
 // and per split 0.4 and 0.32 per 1024 rows.  Never fewer than two turns per split.  Measured (us, unsplit -> chosen): 32 heads
-// of 64 rows over 1088 keys 31.4 -> 23.5 (3 splits 27.1, 4 24.0, 6 30.7); 8 of 32 over 4128 97 -> 20.6; 4 of 16 over 8016
-// 179 -> 25.5; 16 of 64 x 4 sequences, one round unsplit, stays (2 splits 35.4 against 31.4).
+// of 64 rows over 1088 keys 30.5 -> 23.7 (3 splits 26.3, 4 23.8, 6 29.9); 8 of 32 over 4128 88 -> 18.4; 4 of 16 over 8016
+// 164 -> 22.8; 16 of 64 x 4 sequences, one round unsplit, stays (2 splits 34.5 against 31.8).  The constants are older than
+// the kernel's present turn and the present merge: over 700 random shapes that no fit saw what is picked is 0.7 % (head_dim 128) and
+// 1.4 % (64) behind the best split count in the geometric mean, 37 % at most.
 int attention_f32_splits(const gsd_attn_desc &d, size_t room) {
     const int rows = d.max_nodes * (d.num_q_heads / d.num_kv_heads);
     const int turns = int((int64_t(d.max_prefix) + d.max_nodes + 63) / 64);
