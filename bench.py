@@ -424,8 +424,8 @@ def bench_config5_dag_vs_tree(gsd, dev, reps=10):
 
 def default_streams(config: int) -> int:
     """The faster schedule.  The fork and the join cost more than the overlap returns up to config 4 (ms per step, two streams
-    and one in the same run, seven runs: 0.286-0.320 and 0.278-0.297, 2-10 % between them), less on config 5 (2.423 and 2.433,
-    2.508 and 2.526)."""
+    and one in the same run, seven runs: 0.286-0.320 and 0.278-0.297, 2-10 % between them), a little less on config 5 (2.423 and
+    2.433, 2.508 and 2.526, 2.483 and 2.489; with 20 steps a run they are level)."""
     return 2 if config >= 5 else 1
 
 
