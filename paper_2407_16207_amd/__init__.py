@@ -29,9 +29,9 @@ GSD_MAX_NODES_PER_SEQ = 512
 GSD_STATIC_SCRATCH_BYTES = 32 << 20
 
 EXPORTS = ("gsd_status_string", "gsd_last_error", "gsd_version", "gsd_build_mask", "gsd_dag_attention_workspace",
-           "gsd_dag_attention_splits", "gsd_dag_attention", "gsd_dag_attention_static", "gsd_node_argmax", "gsd_node_argmax_stats", "gsd_accept_longest_path",
-           "gsd_unmerge_to_tree", "gsd_gather_rows", "gsd_commit_kv", "gsd_softmax_stats", "gsd_accept_stochastic",
-           "gsd_build_token_graph")
+           "gsd_dag_attention_splits", "gsd_dag_attention", "gsd_dag_attention_static", "gsd_node_argmax",
+           "gsd_node_argmax_stats", "gsd_accept_longest_path", "gsd_unmerge_to_tree", "gsd_gather_rows", "gsd_commit_kv",
+           "gsd_softmax_stats", "gsd_accept_stochastic", "gsd_build_token_graph")
 
 
 class GsdError(RuntimeError):

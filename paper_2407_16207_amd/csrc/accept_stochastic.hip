@@ -17,7 +17,8 @@
 //                           (resample_held_phase: the same with the slices kept in registers, where they fit.)
 // Both phases are chains of dependent round trips on one CU per sequence.  As two kernels (7.0 + 11.7 us on 8 sequences
 // of 256 nodes, 32000 tokens) the second waited for a launch and fetched end node, offsets and parents again: together
-// 16.7 us, now 14.6.  What is left is mostly the vector work of one CU: exponentials of 32000 draft logits 2.2 us, weights 3.5.  With more sequences than CUs they are two kernels all the same (accept_stochastic_kernel, resample_kernel).
+// 16.7 us, now 14.6.  What is left is mostly the vector work of one CU: exponentials of 32000 draft logits 2.2 us, weights 3.5.
+// With more sequences than CUs they are two kernels all the same (accept_stochastic_kernel, resample_kernel).
 #include <type_traits>
 
 #include "gsd_internal.h"
@@ -337,7 +338,9 @@ __device__ __forceinline__ void merge_waves(const float *red_m, const float *red
     const int w = threadIdx.x & 15;
     const float empty = -__builtin_inff(), mw = red_m[w];
     auto from_below = [&](float x, auto shift) -> float {              // lane w - shift of the row; none: empty
-        return __uint_as_float(__builtin_amdgcn_update_dpp(__float_as_uint(empty), __float_as_uint(x), 0x110 + decltype(shift)::value, 0xf, 0xf, false));
+        constexpr int kRowShr = 0x110;
+        return __uint_as_float(__builtin_amdgcn_update_dpp(__float_as_uint(empty), __float_as_uint(x), kRowShr + decltype(shift)::value,
+                                                           0xf, 0xf, false));
     };
     float top = mw;
     top = fmaxf(top, from_below(top, std::integral_constant<int, 1>{}));
@@ -793,7 +796,8 @@ __global__ __launch_bounds__(kAcceptOnlyThreads) void accept_stochastic_kernel(c
 // (The general draw has to leave room for a second work-group: at 7 wavefronts to a SIMD 512 sequences over 1000 tokens take
 // 22.8 us a call instead of 19.5.)
 template <Resample KIND>
-__global__ __launch_bounds__(kResampleThreads, KIND == Resample::general_f32 || KIND == Resample::general_bf16 ? 8 : 4) void resample_kernel(const gsd_stochastic_desc d) {
+__global__ __launch_bounds__(kResampleThreads, KIND == Resample::general_f32 || KIND == Resample::general_bf16 ? 8 : 4)
+void resample_kernel(const gsd_stochastic_desc d) {
     const int64_t base = d.node_offsets[blockIdx.x];
     const int n = max(0, min(d.node_offsets[blockIdx.x + 1] - int32_t(base), d.max_nodes));
     const int end = __builtin_amdgcn_readfirstlane(d.end_node[blockIdx.x]);

@@ -22,8 +22,8 @@
 // as fast.
 // Two row groups at head_dim 128 let 64 rows share a tile; at head_dim 64 one row group, of which two work-groups fit a CU (with
 // two the best plan over 1000 shapes would be 0.9 % faster).
-// Against the better of the other kernel's shapes, before the copies were reordered (merge kernel included, best split count for each): 5 ragged sequences
-// of 231 rows, head_dim 64, 15.1 against 17.1 us; 32 heads of 20 rows over 320 keys 9.3-10.0 against 11.6; 192 groups of
+// Against the better of the other kernel's shapes, before the copies were reordered (merge kernel included, best split count for
+// each): 5 ragged sequences of 231 rows, head_dim 64, 15.1 against 17.1 us; 32 heads of 20 rows over 320 keys 9.3-10.0 against 11.6; 192 groups of
 // 20 rows, head_dim 64, 10.0 against 13.0; 8 groups of 128 rows over 1056 keys 13.9 against 15.8; behind it from about
 // 256 work-groups of 64 rows on (128 groups of 512 rows over 1500 keys 57 against 38).
 #include "attention_bf16.h"
