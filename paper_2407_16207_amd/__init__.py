@@ -420,7 +420,7 @@ def gsd_accept_longest_path(node_offsets, parent_offsets, parent_idx, tokens, ro
         if logits is None:
             raise ValueError("give logits or pred")
         pred = torch.empty(total, dtype=torch.int32, device=dev)
-    _require(pred, torch.int32, "pred", total)
+    _require(pred, torch.int32, "pred", total if logits is not None else 0)
     accept_len = torch.empty(batch, dtype=torch.int32, device=dev) if accept_len is None else accept_len
     accept_path = torch.empty((batch, max_nodes), dtype=torch.int32, device=dev) if accept_path is None else accept_path
     bonus_token = torch.empty(batch, dtype=torch.int32, device=dev) if bonus_token is None else bonus_token

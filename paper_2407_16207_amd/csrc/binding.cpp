@@ -220,7 +220,7 @@ PyObject *accept_longest_path(PyObject *, PyObject *const *args, Py_ssize_t coun
     if (count != 12 || modes_active() || !g.take(args)) return no_short_way();
     const at::Tensor *tokens = tensor(args[3], at::kInt), *root_pred = tensor(args[4], at::kInt);
     if (!tokens || !root_pred || tokens->numel() > INT32_MAX || !number(args[5], max_nodes) || max_nodes < 1 ||
-        !pred.take(args[7], at::kInt, tokens->numel()) || !length.take(args[8], at::kInt, g.batch) ||
+        !pred.take(args[7], at::kInt, args[6] == Py_None ? 0 : tokens->numel()) || !length.take(args[8], at::kInt, g.batch) ||
         !path.take(args[9], at::kInt, int64_t(g.batch) * max_nodes) || !bonus.take(args[10], at::kInt, g.batch) || !stream_of(args[11], stream))
         return no_short_way();
     const int32_t total = int32_t(tokens->numel());

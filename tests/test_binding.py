@@ -169,8 +169,9 @@ def calls_with_outputs():
     yield (lambda **kw: gsd.gsd_node_argmax_stats(rows, **kw), {"pred": on_gpu(4), "row_max": on_gpu(4, **f4), "row_sumexp": on_gpu(4, **f4)})
     yield (lambda **kw: gsd.gsd_softmax_stats(rows, **kw), {"row_max": on_gpu(4, **f4), "row_sumexp": on_gpu(4, **f4)})
     outputs = {"pred": on_gpu(4), "accept_len": on_gpu(1), "accept_path": on_gpu(1, 6), "bonus_token": on_gpu(1)}
-    yield (lambda **kw: gsd.gsd_accept_longest_path(*graph_tensors(), on_gpu(4), on_gpu(1), 6, logits=rows, **kw), outputs)
-    yield (lambda **kw: gsd.gsd_accept_longest_path(*graph_tensors(), on_gpu(4), on_gpu(1), 6, **kw), outputs)
+    yield (lambda **kw: gsd.gsd_accept_longest_path(*graph_tensors(), on_gpu(4), on_gpu(1), 6, logits=rows, **kw), dict(outputs))
+    del outputs["pred"]                                  # an input without logits, of which the nodes there are are read
+    yield (lambda **kw: gsd.gsd_accept_longest_path(*graph_tensors(), on_gpu(4), on_gpu(1), 6, pred=on_gpu(3), **kw), outputs)
     cache = on_gpu(2, 9, 1, 8, **f4)
     yield (lambda **kw: gsd.gsd_commit_kv(cache, cache, on_gpu(2, dtype=torch.int64), on_gpu(2), on_gpu(2), on_gpu(2, 4), **kw),
            {"new_prefix_lens": on_gpu(2)})
