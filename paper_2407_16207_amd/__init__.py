@@ -279,9 +279,9 @@ def make_attn_desc(q, k, v, kv_offsets, prefix_lens, node_offsets, mask, max_nod
             raise ValueError(f"{name} must be a GPU tensor [rows, heads, head_dim] with a contiguous last dim")
     if k_stride != v.stride() or k.shape != v.shape:
         raise ValueError("k and v must share shape and strides")
-    _require(kv_offsets, torch.int64, "kv_offsets")
+    _require(kv_offsets, torch.int64, "kv_offsets", prefix_lens.numel())
     _require(prefix_lens, torch.int32, "prefix_lens")
-    _require(node_offsets, torch.int32, "node_offsets")
+    _require(node_offsets, torch.int32, "node_offsets", prefix_lens.numel() + 1)
     _require(mask, torch.int64, "mask")
     total_nodes, num_q_heads, head_dim = q.shape
     o_stride = out.stride() if out is not None else (0, 0)
@@ -411,9 +411,9 @@ def gsd_accept_longest_path(node_offsets, parent_offsets, parent_idx, tokens, ro
     if torch is None:
         _import_torch()
     _require_graph(node_offsets, parent_offsets, parent_idx)
-    _require(tokens, torch.int32, "tokens")
-    _require(root_pred, torch.int32, "root_pred")
     batch = node_offsets.numel() - 1
+    _require(tokens, torch.int32, "tokens")
+    _require(root_pred, torch.int32, "root_pred", batch)
     total = tokens.numel()
     dev = tokens.device
     if pred is None:
@@ -498,6 +498,7 @@ def gsd_gather_rows(src, index, out=None, rows: int | None = None, stream=None):
         raise ValueError("out must match src's dtype and row shape and hold `rows` rows")
     if rows == 0:
         return out
+    _require(index, torch.int32, "index", rows)
     es = src.element_size()
     row_elems = 1
     for d in src.shape[1:]:
@@ -524,12 +525,13 @@ def gsd_commit_kv(k, v, kv_offsets, prefix_lens, accept_len, accept_path, new_pr
     if k.dim() != 4 or k.shape != v.shape or k.stride() != v.stride() or not k.is_cuda or \
             not (k.numel() and k.is_contiguous() or k[0, 0].is_contiguous()):
         raise ValueError("k and v must be GPU tensors [layers, rows, kv_heads, head_dim] with contiguous rows")
-    _require(kv_offsets, torch.int64, "kv_offsets")
-    _require(prefix_lens, torch.int32, "prefix_lens")
-    _require(accept_len, torch.int32, "accept_len")
-    _require(accept_path, torch.int32, "accept_path")
     batch = prefix_lens.numel()
+    _require(kv_offsets, torch.int64, "kv_offsets", batch)
+    _require(prefix_lens, torch.int32, "prefix_lens")
+    _require(accept_len, torch.int32, "accept_len", batch)
+    _require(accept_path, torch.int32, "accept_path")
     max_nodes = accept_path.shape[1]
+    _require(accept_path, torch.int32, "accept_path", batch * max_nodes)
     if new_prefix_lens is None:
         new_prefix_lens = torch.empty(batch, dtype=torch.int32, device=k.device)
     _require(new_prefix_lens, torch.int32, "new_prefix_lens", batch)
@@ -578,7 +580,7 @@ def gsd_accept_stochastic(node_offsets, parent_offsets, parent_idx, tokens, logi
     _require(tokens, torch.int32, "tokens")
     _require(draft_prob, torch.float32, "draft_prob")
     _require(accept_u, torch.float32, "accept_u")
-    _require(resample_u, torch.float32, "resample_u")
+    _require(resample_u, torch.float32, "resample_u", node_offsets.numel() - 1)
     code = _dtype_code(logits)
     (T, V), row_stride = logits.shape, logits.stride(0)
     B = node_offsets.numel() - 1

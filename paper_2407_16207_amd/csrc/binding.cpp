@@ -56,9 +56,9 @@ const at::Tensor *tensor(PyObject *o) {
     return keys == c10::DispatchKeySet(c10::DispatchKey::CUDA) ? &t : nullptr;
 }
 
-const at::Tensor *tensor(PyObject *o, at::ScalarType type) {
+const at::Tensor *tensor(PyObject *o, at::ScalarType type, int64_t least = 0) {
     const at::Tensor *t = tensor(o);
-    return t && t->scalar_type() == type && t->is_contiguous() ? t : nullptr;
+    return t && t->scalar_type() == type && t->is_contiguous() && t->numel() >= least ? t : nullptr;
 }
 
 bool number(PyObject *o, int32_t &x) {
@@ -85,8 +85,8 @@ struct Output {
     at::Tensor t;
     bool take(PyObject *o, at::ScalarType type, int64_t least = 0) {
         if (o == Py_None) return true;
-        const at::Tensor *x = tensor(o, type);
-        if (!x || x->numel() < least) return false;
+        const at::Tensor *x = tensor(o, type, least);
+        if (!x) return false;
         given = o;
         t = *x;
         return true;
@@ -218,7 +218,7 @@ PyObject *accept_longest_path(PyObject *, PyObject *const *args, Py_ssize_t coun
     Output pred, length, path, bonus;
     void *stream;
     if (count != 12 || modes_active() || !g.take(args)) return no_short_way();
-    const at::Tensor *tokens = tensor(args[3], at::kInt), *root_pred = tensor(args[4], at::kInt);
+    const at::Tensor *tokens = tensor(args[3], at::kInt), *root_pred = tensor(args[4], at::kInt, g.batch);
     if (!tokens || !root_pred || tokens->numel() > INT32_MAX || !number(args[5], max_nodes) || max_nodes < 1 ||
         !pred.take(args[7], at::kInt, args[6] == Py_None ? 0 : tokens->numel()) || !length.take(args[8], at::kInt, g.batch) ||
         !path.take(args[9], at::kInt, int64_t(g.batch) * max_nodes) || !bonus.take(args[10], at::kInt, g.batch) || !stream_of(args[11], stream))
@@ -256,7 +256,9 @@ PyObject *dag_attention(PyObject *, PyObject *const *args, Py_ssize_t count) {
     const at::Tensor *q = tensor(args[0]), *k = tensor(args[1]), *v = tensor(args[2]);
     const at::Tensor *kv_offsets = tensor(args[3], at::kLong), *prefix = tensor(args[4], at::kInt), *nodes = tensor(args[5], at::kInt);
     const at::Tensor *mask = tensor(args[6], at::kLong);
-    if (!q || !k || !v || !kv_offsets || !prefix || !nodes || !mask || mask->dim() < 2) return no_short_way();
+    if (!q || !k || !v || !kv_offsets || !prefix || !nodes || !mask || mask->dim() < 2 || kv_offsets->numel() < prefix->numel() ||
+        nodes->numel() <= prefix->numel())
+        return no_short_way();
     gsd_attn_desc d = {};
     int code, code_k, code_v;
     if (q->dim() != 3 || k->dim() != 3 || v->dim() != 3 || q->stride(2) != 1 || k->stride(2) != 1 || v->stride(2) != 1 || !dtype_code(*q, code) ||
@@ -368,7 +370,7 @@ PyObject *gather_rows(PyObject *, PyObject *const *args, Py_ssize_t count) {
         if (!number(args[3], given_rows)) return no_short_way();
         rows = given_rows;
     }
-    if (rows < 1) return no_short_way();
+    if (rows < 1 || rows > index->numel()) return no_short_way();
     const at::Tensor *given = args[2] == Py_None ? nullptr : tensor(args[2]);
     if (args[2] != Py_None && (!given || given->scalar_type() != src->scalar_type() || given->dim() != src->dim() ||
                                given->sizes().slice(1) != src->sizes().slice(1) || given->size(0) < rows || given->numel() == 0 ||
@@ -405,6 +407,7 @@ PyObject *commit_kv(PyObject *, PyObject *const *args, Py_ssize_t count) {
     void *stream;
     if (!k || !v || !kv_offsets || !prefix || !length || !path || k->dim() != 4 || k->numel() == 0 || !k->is_contiguous() ||
         k->sizes() != v->sizes() || k->strides() != v->strides() || path->dim() < 2 || path->size(1) > INT32_MAX || prefix->numel() > INT32_MAX ||
+        kv_offsets->numel() < prefix->numel() || length->numel() < prefix->numel() || path->numel() < prefix->numel() * path->size(1) ||
         k->size(0) > INT32_MAX || !new_prefix.take(args[6], at::kInt, prefix->numel()) || !stream_of(args[7], stream))
         return no_short_way();
     const int64_t element = int64_t(k->element_size());
@@ -449,7 +452,7 @@ PyObject *accept_stochastic(PyObject *, PyObject *const *args, Py_ssize_t count)
     void *stream;
     if (count != 13 || modes_active() || !g.take(args)) return no_short_way();
     const at::Tensor *tokens = tensor(args[3], at::kInt), *prob = tensor(args[8], at::kFloat), *accept_u = tensor(args[9], at::kFloat),
-                     *resample_u = tensor(args[10], at::kFloat), *logits = tensor(args[4]);
+                     *resample_u = tensor(args[10], at::kFloat, g.batch), *logits = tensor(args[4]);
     if (!tokens || !prob || !accept_u || !resample_u || !logits || !logits_layout(*logits) || !dtype_code(*logits, code) ||
         !number(args[11], max_nodes) || max_nodes < 1)
         return no_short_way();

@@ -195,6 +195,35 @@ def test_outputs_that_a_call_would_write_past_are_refused(monkeypatch):
             assert calls
 
 
+def test_inputs_that_a_call_would_read_past_are_refused(monkeypatch):
+    """What there is one of per sequence (or gathered row): two sequences, and one too few of each."""
+    calls = recording_library(monkeypatch)
+    f4, i8 = dict(dtype=torch.float32), dict(dtype=torch.int64)
+    graph, rows, roots = (on_gpu(3), on_gpu(5), on_gpu(4)), on_gpu(4, 8, **f4), on_gpu(2, 8, **f4)
+    q, cache = on_gpu(4, 2, 64, **f4), on_gpu(2, 9, 1, 8, **f4)
+    cases = [(lambda kv_offsets, node_offsets: gsd.gsd_dag_attention(q, q, q, kv_offsets, on_gpu(2), node_offsets, on_gpu(4, 1, **i8), 4, 8,
+                                                                   0.1, out=q, workspace=on_gpu(16)),
+              {"kv_offsets": on_gpu(2, **i8), "node_offsets": on_gpu(3)}),
+             (lambda root_pred: gsd.gsd_accept_longest_path(*graph, on_gpu(4), root_pred, 4, pred=on_gpu(4), accept_len=on_gpu(2),
+                                                            accept_path=on_gpu(2, 4), bonus_token=on_gpu(2)), {"root_pred": on_gpu(2)}),
+             (lambda kv_offsets, accept_len, accept_path: gsd.gsd_commit_kv(cache, cache, kv_offsets, on_gpu(2), accept_len, accept_path,
+                                                                            new_prefix_lens=on_gpu(2)),
+              {"kv_offsets": on_gpu(2, **i8), "accept_len": on_gpu(2), "accept_path": on_gpu(2, 4)}),
+             (lambda index: gsd.gsd_gather_rows(rows, index, rows=3, out=on_gpu(3, 8, **f4)), {"index": on_gpu(3)}),
+             (lambda resample_u: gsd.gsd_accept_stochastic(*graph, on_gpu(4), rows, roots, rows, roots, on_gpu(4, **f4), on_gpu(4, **f4),
+                                                           resample_u, 4), {"resample_u": on_gpu(2, **f4)})]
+    for call, inputs in cases:
+        call(**inputs)
+        assert calls
+        for name, t in inputs.items():
+            del calls[:]
+            with pytest.raises(ValueError, match=name):
+                call(**{**inputs, name: t[:-1]})
+            assert not calls
+            call(**{**inputs, name: on_gpu(t.shape[0] + 1, *t.shape[1:], dtype=t.dtype)})
+            assert calls
+
+
 def test_attention_outputs_of_another_kind_are_refused(monkeypatch):
     """What the descriptor cannot say of `out`: its type, its last stride, and that it is memory of the GPU."""
     calls = recording_library(monkeypatch)

@@ -213,6 +213,23 @@ def test_outputs_that_a_call_would_write_past_are_refused_either_way(args, monke
         assert isinstance(x, tuple) and x[0] is ValueError and x == y
 
 
+def test_inputs_that_a_call_would_read_past_are_refused_either_way(args, monkeypatch):
+    a, t, short = args, args[torch.float32], lambda x: x[:-1]
+    att, n, u = attention_args(a, torch.float32), a["n"], torch.ones(a["n"], device="cuda")
+    length, path = a["root_pred"] * 0, a["tokens"][None] * 0
+    cache = torch.stack([t["k"]] * 2)
+    both_logits = [t["logits"], t["logits"][:1]] * 2
+    for call in (lambda: gsd.gsd_dag_attention(*att[:3], short(att[3]), *att[4:]), lambda: gsd.gsd_dag_attention(*att[:5], short(att[5]), *att[6:]),
+                 lambda: gsd.gsd_accept_longest_path(*a["graph"], a["tokens"], short(a["root_pred"]), n, logits=t["logits"]),
+                 lambda: gsd.gsd_commit_kv(cache, cache, short(a["kv_offsets"]), a["prefix"], length, path),
+                 lambda: gsd.gsd_commit_kv(cache, cache, a["kv_offsets"], a["prefix"], short(length), path),
+                 lambda: gsd.gsd_commit_kv(cache, cache, a["kv_offsets"], a["prefix"], length, short(path)),
+                 lambda: gsd.gsd_gather_rows(t["q"], a["tokens"] - 1, rows=n + 1),
+                 lambda: gsd.gsd_accept_stochastic(*a["graph"], a["tokens"], *both_logits, u, u, u[:0], n)):
+        x, y = both(monkeypatch, call)
+        assert isinstance(x, tuple) and x[0] is ValueError and x == y, (x, y)
+
+
 def test_other_tensors_go_the_long_way(args):
     """Subclasses, and calls under a torch mode that wants to see them."""
     from torch.utils._python_dispatch import TorchDispatchMode
